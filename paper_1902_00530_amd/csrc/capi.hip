@@ -97,10 +97,10 @@ StepArgs make_step_args(const lbm_params &p, int64_t pitch)
     a.noise_h = (float)(q9 ? p.sigma / 8192.0 : p.sigma / 32768.0);
     a.A16 = (float)p.A * 65536.0f;
     a.B16 = (float)p.B * 65536.0f;
-    a.C = (float)p.C;
+    a.C2 = 2.0f * (float)p.C;
     a.rho_star = p.model == LBM_MIPS ? (float)p.rho_star : 1.0f;
     a.inv_rho_star = p.model == LBM_MIPS ? (float)(1.0 / p.rho_star) : 1.0f;
-    a.u_max = (float)p.u_max;
+    a.u_max2 = 2.0f * (float)p.u_max;
     const double rr = p.storage == LBM_F32 ? 0.0 : p.rho_ref;
     // the float32 rest plane of LBM_BF16_DEV_R32 holds f_0 itself
     const int moving = p.storage == LBM_BF16_DEV_R32 ? LBM_BF16_DEV : p.storage;

@@ -678,7 +678,7 @@ __global__ __launch_bounds__(256) void k_lift_many(const float *__restrict__ coa
     const size_t cp = (size_t)chh * cw;
     const float rho = fmaxf(cf[(size_t)cy * cw + cx], 0.0f);
     const float jx = cf[cp + (size_t)cy * cw + cx], jy = cf[2 * cp + (size_t)cy * cw + cx];
-    const float r = rho > 0.0f ? 1.0f / rho : 0.0f;
+    const float r = rho > 0.0f ? 2.0f / rho : 0.0f;  // the steady state takes 2 u
     float eq[7];
     site_equilibrium(rho, jx * r, jy * r, eq);
     const uint32_t own = (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(256) void k_lift(const float *__restrict__ coarse, 
     const size_t cp = (size_t)chh * cw;
     const float rho = fmaxf(coarse[(size_t)cy * cw + cx], 0.0f);
     const float jx = coarse[cp + (size_t)cy * cw + cx], jy = coarse[2 * cp + (size_t)cy * cw + cx];
-    const float r = rho > 0.0f ? 1.0f / rho : 0.0f;
+    const float r = rho > 0.0f ? 2.0f / rho : 0.0f;  // the steady state takes 2 u
     float eq[7];
     site_equilibrium(rho, jx * r, jy * r, eq);
     const uint32_t own = (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;

@@ -29,12 +29,13 @@ __device__ __forceinline__ void q9_moments(const float f[9], float &rho, float &
 // MIPS target velocity from the eight neighbour densities nb[i] = rho(r + e_i):
 // grad rho = (1/c_s^2) sum_i w_i e_i nb_i, the construction of the paper's
 // isotropic stencil on this lattice, then eq. bu_mips and the U_max clamp.
-__device__ __forceinline__ void q9_mips_ustar(const StepArgs &a, float rho, const float nb[9], float &ux, float &uy)
+// Doubled, as every target velocity (local_ustar).
+__device__ __forceinline__ void q9_mips_ustar(const StepArgs &a, float rho, const float nb[9], float &vx, float &vy)
 {
     const float d5 = nb[5] - nb[7], d6 = nb[6] - nb[8];
     const float gx = (nb[1] - nb[3]) * (1.0f / 3.0f) + (d5 - d6) * (1.0f / 12.0f);
     const float gy = (nb[2] - nb[4]) * (1.0f / 3.0f) + (d5 + d6) * (1.0f / 12.0f);
-    mips_from_gradient(a, rho, gx, gy, ux, uy);
+    mips_from_gradient(a, rho, gx, gy, vx, vy);
 }
 
 // 1/9 as an unevaluated float pair (float(1/9) alone would bias the mass of
@@ -42,27 +43,27 @@ __device__ __forceinline__ void q9_mips_ustar(const StepArgs &a, float rho, cons
 constexpr float kNinthHi = (float)(1.0 / 9.0);
 constexpr float kNinthLo = (float)(1.0 / 9.0 - (double)(float)(1.0 / 9.0));
 
-// Steady state of this lattice in pair form: a_k = e_k.u,
+// Steady state of this lattice in pair form from v = 2 u: a_k = e_k.u,
 // base = 1 - (3/2)|u|^2, xi_{k, opp} = w_k rho (base + (9/2) a_k^2 +- 3 a_k),
-// xi_0 = (4/9) rho base.
-__device__ __forceinline__ void q9_equilibrium(float rho, float ux, float uy, float eq[9])
+// xi_0 = (4/9) rho base; below in d_k = 2 a_k, (9/8) d_k^2 and (3/2) d_k.
+__device__ __forceinline__ void q9_equilibrium(float rho, float vx, float vy, float eq[9])
 {
-    const float usq = ux * ux + uy * uy;
-    const float base = 1.0f - 1.5f * usq;
+    const float vsq = vx * vx + vy * vy;
+    const float base = 1.0f - 0.375f * vsq;
     const float r9 = fmaf(rho, kNinthHi, rho * kNinthLo);
     const float r36 = 0.25f * r9;
     eq[0] = 4.0f * r9 * base;
-    const float a1 = ux, a2 = uy, a5 = ux + uy, a6 = uy - ux;
-    const float b1 = base + 4.5f * a1 * a1, b2 = base + 4.5f * a2 * a2;
-    const float b5 = base + 4.5f * a5 * a5, b6 = base + 4.5f * a6 * a6;
-    eq[1] = r9 * (b1 + 3.0f * a1);
-    eq[3] = r9 * (b1 - 3.0f * a1);
-    eq[2] = r9 * (b2 + 3.0f * a2);
-    eq[4] = r9 * (b2 - 3.0f * a2);
-    eq[5] = r36 * (b5 + 3.0f * a5);
-    eq[7] = r36 * (b5 - 3.0f * a5);
-    eq[6] = r36 * (b6 + 3.0f * a6);
-    eq[8] = r36 * (b6 - 3.0f * a6);
+    const float d1 = vx, d2 = vy, d5 = vx + vy, d6 = vy - vx;
+    const float b1 = base + 1.125f * d1 * d1, b2 = base + 1.125f * d2 * d2;
+    const float b5 = base + 1.125f * d5 * d5, b6 = base + 1.125f * d6 * d6;
+    eq[1] = r9 * (b1 + 1.5f * d1);
+    eq[3] = r9 * (b1 - 1.5f * d1);
+    eq[2] = r9 * (b2 + 1.5f * d2);
+    eq[4] = r9 * (b2 - 1.5f * d2);
+    eq[5] = r36 * (b5 + 1.5f * d5);
+    eq[7] = r36 * (b5 - 1.5f * d5);
+    eq[6] = r36 * (b6 + 1.5f * d6);
+    eq[8] = r36 * (b6 - 1.5f * d6);
 }
 
 // The nine 14-bit draws of one Philox4x32-10 output: draw i is bits
@@ -100,11 +101,11 @@ __device__ __forceinline__ void q9_add_noise(const StepArgs &a, uint32_t site, u
 // population becomes 0, a pair with a negative member becomes
 // (max(d, 0), max(-d, 0)), and a site where a rule fired is rescaled to rho).
 template <int F, int S = kF32>
-__device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float rho, float ux, float uy,
+__device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float rho, float vx, float vy,
                                            uint32_t site, uint32_t t_lo, uint32_t t_hi)
 {
     float eq[9];
-    q9_equilibrium(rho, ux, uy, eq);
+    q9_equilibrium(rho, vx, vy, eq);
     if (F & kUnitTau) {
 #pragma unroll
         for (int i = 0; i < 9; ++i)
@@ -123,23 +124,10 @@ __device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float 
         if (absorb)
             f[0] = rho - (((f[1] + f[3]) + (f[2] + f[4])) + ((f[5] + f[7]) + (f[6] + f[8])));
     }
-    constexpr int kNegative = 0x3c;  // -inf, -normal, -denormal, -0 (as in the D2Q7 body)
-    bool fired = false;
-    if (__builtin_amdgcn_classf(f[0], kNegative)) {
-        f[0] = 0.0f;
-        fired = true;
-    }
-    constexpr int kFirst[4] = {1, 2, 5, 6};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int k = kFirst[q], o = k + 2;
-        if (__builtin_amdgcn_classf(f[k], kNegative) | __builtin_amdgcn_classf(f[o], kNegative)) {
-            const float d = f[k] - f[o];
-            f[k] = fmaxf(d, 0.0f);
-            f[o] = fmaxf(-d, 0.0f);
-            fired = true;
-        }
-    }
+    const float m0 = correct_rest(f[0]), m1 = correct_pair(f[1], f[3]), m2 = correct_pair(f[2], f[4]),
+                m3 = correct_pair(f[5], f[7]), m4 = correct_pair(f[6], f[8]);
+    const bool fired = (int32_t)(__float_as_uint(m0) | __float_as_uint(m1) | __float_as_uint(m2) |
+                                 __float_as_uint(m3) | __float_as_uint(m4)) < 0;
     if constexpr (S != kF32) {
         if (!fired && absorb) {
             float g[9];
