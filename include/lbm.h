@@ -187,16 +187,18 @@ size_t lbm_workspace_bytes(const lbm_params *p, int64_t pitch);
 int32_t lbm_create(const lbm_params *p, void *f_a, void *f_b, int64_t pitch, const lbm_init *init, void *ws,
                    size_t ws_bytes, void *stream, lbm_ctx **out);
 
-/* Enqueue n >= 0 steps on the context's stream (no synchronisation), one
- * kernel launch per step.  Runs of 64 steps replay a HIP graph captured on
- * first use (one per starting buffer); the remainder, and every step while
- * the caller is capturing the stream itself, are launched directly.  Every
- * launch reads its step index (the noise counter) from the workspace's step
- * clock, so graphs replay with unchanged arguments.  The state alternates
- * between the two buffers; lbm_current_buffer() tells which holds it
- * afterwards.  Where the two buffers together exceed 240 MiB (more than the
- * 256 MB Infinity Cache keeps) the steps' stores are non-temporal; the values
- * are the same either way. */
+/* Enqueue n >= 0 steps on the context's stream (no synchronisation).  A launch
+ * takes one step, or two where that is faster (pitch nx; by size, model and
+ * storage), which changes no value: every split of the same steps into calls
+ * and launches gives the same state bit for bit.  Runs of 64 steps replay a
+ * HIP graph captured on first use (one per starting buffer); the remainder,
+ * and every step while the caller is capturing the stream itself, are launched
+ * directly.  Every launch reads its step index (the noise counter) from the
+ * workspace's step clock, so graphs replay with unchanged arguments.  The
+ * state ends in the buffer that n one-step launches, alternating between the
+ * two, would leave it in; lbm_current_buffer() tells which.  Where the two
+ * buffers together exceed 240 MiB (more than the 256 MB Infinity Cache keeps)
+ * the steps' stores are non-temporal; the values are the same either way. */
 int32_t lbm_step(lbm_ctx *c, int64_t n);
 
 /* Fields and observables of the stored state.  rho, ux, uy: caller-owned

@@ -138,13 +138,61 @@ static size_t ctx_workspace_bytes(const lbm_params &p)
 // the buffer it started from).
 constexpr int64_t kGraphSteps = 64;
 
+// Where lbm_step takes two steps per launch, and on 64 x 8 or 64 x 16 tiles.
+// Two steps halve the passes over the state and the launches; they cost the
+// first step's ring around each tile (a sixteenth to a quarter more site
+// bodies; MIPS a fifth to a third) and a longer chain per launch.  Measured in
+// us per step, one step per launch against two (64 x 8 / 64 x 16 tiles):
+//   CIL F32       180x60 2.49 / 2.49 / 3.21; 256^2 3.09 / 2.61 / 3.32; 1024^2 10.5 / 7.43 / 7.49;
+//                 2048^2 34.4 / 21.7 / 21.6; 4096^2 167 / 96.5 / 96.5
+//   CIL BF16      256^2 2.75 / 2.83 / 3.92; 512^2 4.34 / 3.58 / 4.12; 4096^2 99 / 94 / 87
+//   MIPS F32      256^2 3.48 / 3.55 / 3.63; 512^2 5.62 / 5.21 / 4.22; 4096^2 188 / 135 / 122
+//   MIPS BF16     512^2 5.07 / 5.08 / 4.49; 1024^2 10.0 / 11.4 / 10.4; 2048^2 29.6 / 34.2 / 30.9
+//   D2Q9 CIL F32  256^2 3.63 / 3.02 / 4.15; 1024^2 13.3 / 9.06 / 9.67; 4096^2 207 / 126 / 125
+//   D2Q9 MIPS F32 64^2 5.93 / 3.87 / 3.89; 1024^2 15.3 / 13.1 / 12.0; 4096^2 251 / 171 / 159
+//   D2Q9 MIPS F16 512^2 7.22 / 5.83 / 4.87; 1024^2 13.6 / 13.5 / 12.3; 2048^2 36 / 43 / 40
+// Below the lines the launch is bound by one block's latency, so the shorter
+// one-step chain wins; 16-bit MIPS on large lattices is VALU-bound already, so
+// the ring's extra work loses.  Pitched lattices and buffers of 2^30
+// populations or more (64-bit offsets) keep one step per launch.
+int step2_rows(const lbm_params &p, const StepArgs &a)
+{
+    const bool q9 = p.lattice == LBM_D2Q9, f32 = p.storage == LBM_F32;
+    const int64_t sites = (int64_t)p.nx * p.ny;
+    if (a.pitch != p.nx || (!q9 && (uint64_t)a.plane * 7ull >= (1ull << 30)))
+        return 0;
+    if (p.model == LBM_MIPS) {
+        const int64_t lo = q9 ? 0 : 1 << 17, hi = f32 ? INT64_MAX : q9 ? 3 << 19 : 1 << 19;
+        return sites >= lo && sites < hi ? 16 : 0;
+    }
+    if (sites < (f32 ? 3 << 14 : 1 << 17))
+        return 0;
+    return sites < 1 << 21 ? 8 : 16;
+}
+
 static hipError_t enqueue_steps(lbm_ctx *c, int from, int64_t n, hipStream_t s)
 {
-    for (int64_t k = 0; k < n; ++k) {
-        const int slot = (from + (int)(k & 1)) & 1;
-        hipError_t e = c->p.lattice == LBM_D2Q9
-                           ? launch_step_q9(c->p, c->args, c->buf[slot], c->buf[slot ^ 1], c->clk, slot, s)
-                           : launch_step(c->p, c->args, c->buf[slot], c->buf[slot ^ 1], c->clk, slot, s);
+    const bool q9 = c->p.lattice == LBM_D2Q9;
+    // an even number of two-step launches, so that the state ends in the
+    // buffer that the step count's parity names
+    const int rows = step2_rows(c->p, c->args);
+    int64_t two = rows ? n / 2 : 0;
+    two -= two & 1;
+    int slot = from;
+    for (int64_t done = 0; done < n; slot ^= 1) {
+        const void *src = c->buf[slot];
+        void *dst = c->buf[slot ^ 1];
+        hipError_t e;
+        if (two > 0) {
+            e = q9 ? launch_step2_q9(c->p, c->args, rows, src, dst, c->clk, slot, s)
+                   : launch_step2(c->p, c->args, rows, src, dst, c->clk, slot, s);
+            done += 2;
+            --two;
+        } else {
+            e = q9 ? launch_step_q9(c->p, c->args, src, dst, c->clk, slot, s)
+                   : launch_step(c->p, c->args, src, dst, c->clk, slot, s);
+            done += 1;
+        }
         if (e != hipSuccess)
             return e;
     }

@@ -45,10 +45,10 @@ struct StepClock {
 
 __device__ __forceinline__ uint64_t clock_read(const StepClock *clk, int slot) { return (uint64_t)clk->t[slot]; }
 
-__device__ __forceinline__ void clock_advance(StepClock *clk, int slot, uint64_t t)
+__device__ __forceinline__ void clock_advance(StepClock *clk, int slot, uint64_t t, int steps = 1)
 {
     if ((blockIdx.x | blockIdx.y | threadIdx.x | threadIdx.y) == 0)
-        clk->t[slot ^ 1] = (int64_t)t + 1;
+        clk->t[slot ^ 1] = (int64_t)t + steps;
 }
 
 // ---------------------------------------------------------------------------

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <type_traits>
 
 #include "../../include/lbm.h"
 #include "device.h"
@@ -32,6 +33,17 @@ int step_flags(const StepArgs &a);
 // and the next index goes to the other slot.
 hipError_t launch_step(const lbm_params &p, const StepArgs &a, const void *src, void *dst, StepClock *clk, int slot,
                        hipStream_t s);
+// Tile rows (8 or 16) of the two-step kernels for this lattice, 0 where one
+// step per launch is taken.
+int step2_rows(const lbm_params &p, const StepArgs &a);
+// Two steps src -> dst in one launch on 64 x rows tiles; the clock advances by
+// two.
+hipError_t launch_step2(const lbm_params &p, const StepArgs &a, int rows, const void *src, void *dst, StepClock *clk,
+                        int slot, hipStream_t s);
+hipError_t launch_step2_q9(const lbm_params &p, const StepArgs &a, int rows, const void *src, void *dst, StepClock *clk,
+                           int slot, hipStream_t s);
+// Grid of ntx x nty tiles in row groups (row_group_tile).
+inline dim3 row_group_grid(int ntx, int nty) { return dim3(8u * (unsigned)ntx, (unsigned)((nty + 7) / 8)); }
 // Initial state into dst.
 hipError_t launch_init(const lbm_params &p, const lbm_init &in, const StepArgs &a, void *dst, hipStream_t s);
 // f_i += drho / 7 in place.
@@ -68,6 +80,33 @@ int32_t surrogate_sweep(const lbm_params *ps, int n, const lbm_sweep_opts *o, vo
                         size_t ws_bytes, hipStream_t st, lbm_obs *out);
 // Turn the 8 reduced doubles into an lbm_obs (host).
 void finish_obs(const lbm_params &p, const double *r, int64_t step, lbm_obs *o);
+
+// Runtime storage and flags to compile-time template arguments.
+template <int V>
+using IntTag = std::integral_constant<int, V>;
+
+template <class Fn>
+inline hipError_t with_storage(int storage, Fn &&fn)
+{
+    switch (storage) {
+    case kF32: return fn(IntTag<kF32>{});
+    case kBf16Dev: return fn(IntTag<kBf16Dev>{});
+    case kF16Dev: return fn(IntTag<kF16Dev>{});
+    case kBf16R32: return fn(IntTag<kBf16R32>{});
+    }
+    return hipErrorInvalidValue;
+}
+
+template <class Fn>
+inline hipError_t with_flags(int flags, Fn &&fn)
+{
+    switch (flags) {
+    case 0: return fn(IntTag<0>{});
+    case kUnitTau: return fn(IntTag<kUnitTau>{});
+    case kNoisy: return fn(IntTag<kNoisy>{});
+    default: return fn(IntTag<kUnitTau | kNoisy>{});
+    }
+}
 
 }  // namespace lbm
 

@@ -1,0 +1,127 @@
+"""lbm_step with several steps per launch: one call of n steps equals n calls
+of one step (one step per launch, the kernels the oracle tests hold) bit for
+bit, in the same buffer and with the same clock, at the sizes where the launch
+form changes and around the edges of its tiles."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1902_00530_amd as lib
+    return lib
+
+
+CIL = dict(tau=1.0, sigma=4.0 / 70.0, A=0.125, B=0.3)
+MIPS = dict(tau=2.0, sigma=8.0 / 70.0, C=6.25, rho_star=1.6, u_max=0.3)
+
+
+def _lattice(L, q, model, storage, nx, ny, pitch=None, **kw):
+    k = dict({"cil": CIL, "mips": MIPS, "passive": dict(tau=1.5, sigma=0.0)}[model], **kw)
+    p = L.make_params(nx, ny, {"passive": 0, "mips": 1, "cil": 2}[model], seed=977, storage=storage,
+                      rho_ref=0.9 if storage else 0.0, lattice=L.LBM_D2Q9 if q == 9 else L.LBM_D2Q7, **k)
+    return L.Lattice(p, init=L.make_init(mode=1, rho_mean=0.9, rho_spread=0.2, u_mag=0.1, pop_noise=1e-3),
+                     pitch=pitch)
+
+
+def _bits(lat):
+    return lat.state[:, :, :lat.params.nx].clone().view(torch.int32 if lat.state.dtype == torch.float32 else torch.int16)
+
+
+def _compare(L, calls, *args, **kw):
+    one, many = _lattice(L, *args, **kw), _lattice(L, *args, **kw)
+    for n in calls:
+        for _ in range(n):
+            one.step(1)
+        many.step(n)
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(one), _bits(many))
+    assert L.lbm_current_buffer(one.ctx) == L.lbm_current_buffer(many.ctx)
+    assert one.step_index == many.step_index == sum(calls)
+    one.close()
+    many.close()
+
+
+# sizes on both sides of the two-step lines (3 * 2^14, 2^17 sites for the local
+# models and MIPS), tile edges (64 columns, 8 or 16 rows) and remainders, and
+# the line between the tile heights (2^21)
+LOCAL = [(256, 192), (256, 190), (257, 192), (1001, 50), (64, 770), (65, 2052), (511, 258), (1453, 1444)]
+
+
+@pytest.mark.parametrize("nx,ny", LOCAL)
+@pytest.mark.parametrize("q", [7, 9])
+def test_local_f32(L, q, nx, ny):
+    _compare(L, [4, 7, 1, 2, 6], q, "cil", L.LBM_F32, nx, ny)
+
+
+@pytest.mark.parametrize("q", [7, 9])
+@pytest.mark.parametrize("nx,ny", [(512, 256), (511, 258), (1023, 130), (2049, 66)])
+def test_mips_f32(L, q, nx, ny):
+    _compare(L, [4, 5, 2, 8], q, "mips", L.LBM_F32, nx, ny)
+
+
+@pytest.mark.parametrize("nx,ny", [(2, 2), (3, 3), (5, 17), (64, 16), (65, 15), (67, 18), (130, 49)])
+def test_q9_mips_small(L, nx, ny):
+    _compare(L, [4, 5, 8], 9, "mips", L.LBM_F32, nx, ny)
+
+
+@pytest.mark.parametrize("storage", [1, 2, 3])
+@pytest.mark.parametrize("model", ["cil", "mips"])
+@pytest.mark.parametrize("q", [7, 9])
+def test_16_bit(L, q, model, storage):
+    if q == 9 and storage == 3:
+        pytest.skip("the float32 rest plane storage takes D2Q7")
+    _compare(L, [4, 3, 8], q, model, storage, 515, 258)
+
+
+@pytest.mark.parametrize("kw", [dict(sigma=0.0), dict(tau=1.7), dict(tau=float("inf"), sigma=0.0)])
+@pytest.mark.parametrize("q", [7, 9])
+def test_flags(L, q, kw):
+    _compare(L, [4, 6], q, "cil", L.LBM_F32, 300, 170, **kw)
+    _compare(L, [4, 6], q, "passive", L.LBM_F32, 300, 170)
+
+
+def test_pitched_lattice_and_graph_runs(L):
+    _compare(L, [4, 67], 7, "cil", L.LBM_F32, 300, 170, pitch=320)
+    _compare(L, [64, 130, 3, 65], 7, "cil", L.LBM_F32, 300, 170)
+    _compare(L, [67, 64, 129], 9, "mips", L.LBM_F32, 70, 33)
+
+
+def test_under_stream_capture(L):
+    """Steps captured by the caller: replays continue the clock and the state."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        one, many = (_lattice(L, 7, "cil", L.LBM_F32, 300, 170) for _ in range(2))
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            many.step(6)
+        for _ in range(4):
+            g.replay()
+            for _ in range(6):
+                one.step(1)
+            s.synchronize()
+            assert torch.equal(_bits(one), _bits(many))
+    one.close()
+    many.close()
+
+
+def test_large_lattice_against_oracle(L, orc):
+    """Four steps in two launches against the FP64 oracle (a linearly stable
+    ordered state: 1e-6 of the population scale per step)."""
+    nx, ny = 320, 170
+    po = orc.make_params(nx, ny, orc.CIL, tau=1.0, sigma=4.0 / 700.0, A=0.125, B=0.3, seed=5)
+    f0 = orc.initialise(po, mode=2, rho_mean=0.74, rho_spread=0.1, angle_std=0.05).astype(np.float32)
+    lat = L.Lattice(L.make_params(nx, ny, L.LBM_CIL, tau=1.0, sigma=4.0 / 700.0, A=0.125, B=0.3, seed=5))
+    lat.set_state(torch.from_numpy(f0).cuda())
+    lat.step(4)
+    got = lat.state.double().cpu().numpy()
+    lat.close()
+    ref = orc.run(po, f0.astype(np.float64), 4)
+    assert np.abs(got - ref).max() <= 4e-6 * np.abs(ref).max()
