@@ -188,11 +188,12 @@ int32_t lbm_create(const lbm_params *p, void *f_a, void *f_b, int64_t pitch, con
                    size_t ws_bytes, void *stream, lbm_ctx **out);
 
 /* Enqueue n >= 0 steps on the context's stream (no synchronisation).  A launch
- * takes one step, or two where that is faster (pitch nx; by size, model and
- * storage), which changes no value: every split of the same steps into calls
- * and launches gives the same state bit for bit.  Runs of 64 steps replay a
- * HIP graph captured on first use (one per starting buffer); the remainder,
- * and every step while the caller is capturing the stream itself, are launched
+ * takes one step, or up to eight where that is faster (pitch nx; by size,
+ * model and storage), which changes no value: every split of the same steps
+ * into calls and launches gives the same state bit for bit.  From a context's
+ * first call of 512 steps or more on, runs of 64 steps replay a HIP graph (one
+ * per starting buffer); the remainder, shorter calls before that, and every
+ * step while the caller is capturing the stream itself, are launched
  * directly.  Every launch reads its step index (the noise counter) from the
  * workspace's step clock, so graphs replay with unchanged arguments.  The
  * state ends in the buffer that n one-step launches, alternating between the

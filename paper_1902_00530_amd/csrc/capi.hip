@@ -137,8 +137,15 @@ static size_t ctx_workspace_bytes(const lbm_params &p)
 // Steps per captured graph of lbm_step (even, so a replay leaves the state in
 // the buffer it started from).
 constexpr int64_t kGraphSteps = 64;
+// Steps of the call that first captures it.  Capturing and instantiating takes
+// about 0.4 ms and a direct launch about 3 us of the host against 5 us and more
+// of the GPU, so a graph only frees the host: shorter runs are launched
+// directly (64^2 MIPS, the first 100 steps of a new context: 742 us with one
+// launch a step and a graph, 155 us now).
+constexpr int64_t kGraphFirst = 512;
 
-// Where lbm_step takes two steps per launch, and on 64 x 8 or 64 x 16 tiles.
+// Where lbm_step takes two steps per launch, and on 64 x 8 or 64 x 16 tiles
+// (lattices small enough for multi_for_lattice take more steps per launch).
 // Two steps halve the passes over the state and the launches; they cost the
 // first step's ring around each tile (a sixteenth to a quarter more site
 // bodies; MIPS a fifth to a third) and a longer chain per launch.  Measured in
@@ -170,29 +177,31 @@ int step2_rows(const lbm_params &p, const StepArgs &a)
     return sites < 1 << 21 ? 8 : 16;
 }
 
+// n steps from buffer `from`, in as few launches as the context's form allows.
+// The launches alternate between the buffers and are an odd number where n is,
+// so that the state ends where n one-step launches would leave it; the steps
+// are dealt evenly over them (a launch of one step takes the one-step kernel).
 static hipError_t enqueue_steps(lbm_ctx *c, int from, int64_t n, hipStream_t s)
 {
     const bool q9 = c->p.lattice == LBM_D2Q9;
-    // an even number of two-step launches, so that the state ends in the
-    // buffer that the step count's parity names
-    const int rows = step2_rows(c->p, c->args);
-    int64_t two = rows ? n / 2 : 0;
-    two -= two & 1;
-    int slot = from;
-    for (int64_t done = 0; done < n; slot ^= 1) {
+    const int64_t most = c->multi.T ? c->multi.T : c->rows ? 2 : 1;
+    int64_t launches = (n + most - 1) / most;
+    launches += (launches ^ n) & 1;
+    for (int64_t k = 0; k < launches; ++k) {
+        const int slot = (from + (int)(k & 1)) & 1;
         const void *src = c->buf[slot];
         void *dst = c->buf[slot ^ 1];
+        const int steps = (int)(n / launches + (k < n % launches ? 1 : 0));
         hipError_t e;
-        if (two > 0) {
-            e = q9 ? launch_step2_q9(c->p, c->args, rows, src, dst, c->clk, slot, s)
-                   : launch_step2(c->p, c->args, rows, src, dst, c->clk, slot, s);
-            done += 2;
-            --two;
-        } else {
+        if (steps == 1)
             e = q9 ? launch_step_q9(c->p, c->args, src, dst, c->clk, slot, s)
                    : launch_step(c->p, c->args, src, dst, c->clk, slot, s);
-            done += 1;
-        }
+        else if (c->multi.T)
+            e = q9 ? launch_multi_q9(c->p, c->args, c->multi, steps, src, dst, c->clk, slot, s)
+                   : launch_multi(c->p, c->args, c->multi, steps, src, dst, c->clk, slot, s);
+        else
+            e = q9 ? launch_step2_q9(c->p, c->args, c->rows, src, dst, c->clk, slot, s)
+                   : launch_step2(c->p, c->args, c->rows, src, dst, c->clk, slot, s);
         if (e != hipSuccess)
             return e;
     }
@@ -291,6 +300,8 @@ int32_t lbm_create(const lbm_params *p, void *f_a, void *f_b, int64_t pitch, con
     c->d_result = (double *)(w + kWsResult);
     c->d_scratch = (double *)(w + kWsScratch);
     c->graph[0] = c->graph[1] = nullptr;
+    c->multi = multi_for_lattice(*p, c->args);
+    c->rows = step2_rows(*p, c->args);
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess)
         e = launch_set_clock(c->clk, 0, 0, c->stream);
@@ -312,15 +323,15 @@ int32_t lbm_step(lbm_ctx *c, int64_t n)
         return fail(LBM_ESTATE, "null context");
     if (n < 0)
         return fail(LBM_EINVAL, "negative step count");
-    // whole graphs of kGraphSteps steps, then single launches; a stream that
-    // the caller is capturing gets single launches only
+    // whole graphs of kGraphSteps steps, then direct launches; a stream that
+    // the caller is capturing gets direct launches only
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
         (void)hipGetLastError();
         cs = hipStreamCaptureStatusNone;
     }
     int64_t left = n;
-    if (cs == hipStreamCaptureStatusNone && n >= kGraphSteps) {
+    if (cs == hipStreamCaptureStatusNone && n >= kGraphSteps && (c->graph[c->cur] || n >= kGraphFirst)) {
         if (!c->graph[c->cur])
             LBM_HIP_TRY(capture_steps(c, c->cur));
         for (; left >= kGraphSteps; left -= kGraphSteps)

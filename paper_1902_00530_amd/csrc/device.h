@@ -317,13 +317,11 @@ enum StepFlags : int { kUnitTau = 1, kNoisy = 2 };
 // one fires, the rescale to rho sets the mass); with a float32 rest plane
 // (kBf16R32) at every site, after the correction.  tau = +inf keeps the
 // populations as they are.
+// nz: the site's noise (read with kNoisy only).
 template <int F, int S = kF32>
-__device__ __forceinline__ void site_collide(const StepArgs &a, float f[7], float rho, float vx, float vy,
-                                             uint32_t site, uint32_t t_lo, uint32_t t_hi)
+__device__ __forceinline__ void site_relax(const StepArgs &a, float f[7], float rho, float vx, float vy,
+                                           const float nz[7])
 {
-    float nz[7];
-    if (F & kNoisy)
-        site_noise(a, site, t_lo, t_hi, nz);
     if (F & kUnitTau) {
         // tau = 1 (the paper's CIL runs): the relaxation lands on xi exactly,
         // and the noise is added by the last product of xi
@@ -388,6 +386,16 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, float f[7], floa
             f[0] = fmaxf(rho - ((g[1] + g[4]) + ((g[2] + g[5]) + (g[3] + g[6]))), 0.0f);
         }
     }
+}
+
+template <int F, int S = kF32>
+__device__ __forceinline__ void site_collide(const StepArgs &a, float f[7], float rho, float vx, float vy,
+                                             uint32_t site, uint32_t t_lo, uint32_t t_hi)
+{
+    float nz[7];
+    if (F & kNoisy)
+        site_noise(a, site, t_lo, t_hi, nz);
+    site_relax<F, S>(a, f, rho, vx, vy, nz);
 }
 
 // Streaming sources (step (i)): after streaming, population i at site r is

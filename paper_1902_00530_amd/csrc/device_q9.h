@@ -84,25 +84,26 @@ __device__ __forceinline__ void q9_draws(const Philox4 &w, float h[9])
 
 // Zero-sum noise (eq. noiseDensityConservation) over nine directions: raw
 // draws sigma (2 h_i + 1 - 16384) / 16384, minus their mean, is
-// sigma (9 h_i - H) / 73728, H = sum h_i; the integers are exact in float.
-__device__ __forceinline__ void q9_add_noise(const StepArgs &a, uint32_t site, uint32_t t_lo, uint32_t t_hi,
-                                             float f[9])
+// sigma (9 h_i - H) / 73728, H = sum h_i; nz_i = 9 h_i - H, an integer exact
+// in float.
+__device__ __forceinline__ void q9_noise(const StepArgs &a, uint32_t site, uint32_t t_lo, uint32_t t_hi, float nz[9])
 {
     float h[9];
     q9_draws(philox4x32_10(site, t_lo, t_hi, 0u, a.key0, a.key1), h);
     const float H = (((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]))) + h[8];
 #pragma unroll
     for (int i = 0; i < 9; ++i)
-        f[i] = fmaf(fmaf(h[i], 9.0f, -H), a.noise_scale, f[i]);
+        nz[i] = fmaf(h[i], 9.0f, -H);
 }
 
 // BGK relaxation towards xi(rho, u*), noise, and the negative correction
 // (closed pair form of the appendix "Negative Correction": a negative rest
 // population becomes 0, a pair with a negative member becomes
 // (max(d, 0), max(-d, 0)), and a site where a rule fired is rescaled to rho).
+// nz: the site's noise integers (read with kNoisy only).
 template <int F, int S = kF32>
-__device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float rho, float vx, float vy,
-                                           uint32_t site, uint32_t t_lo, uint32_t t_hi)
+__device__ __forceinline__ void q9_relax(const StepArgs &a, float f[9], float rho, float vx, float vy,
+                                         const float nz[9])
 {
     float eq[9];
     q9_equilibrium(rho, vx, vy, eq);
@@ -116,7 +117,9 @@ __device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float 
             f[i] = f[i] - (f[i] - eq[i]) * a.omega;
     }
     if (F & kNoisy)
-        q9_add_noise(a, site, t_lo, t_hi, f);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            f[i] = fmaf(nz[i], a.noise_scale, f[i]);
     // the rest population is rho minus the moving ones (as on D2Q7: float32
     // here; the 16-bit storages below, at sites where no rule fired)
     const bool absorb = (F & kUnitTau) || a.omega != 0.0f;
@@ -146,6 +149,16 @@ __device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float 
         for (int i = 0; i < 9; ++i)
             f[i] *= r;
     }
+}
+
+template <int F, int S = kF32>
+__device__ __forceinline__ void q9_collide(const StepArgs &a, float f[9], float rho, float vx, float vy,
+                                           uint32_t site, uint32_t t_lo, uint32_t t_hi)
+{
+    float nz[9];
+    if (F & kNoisy)
+        q9_noise(a, site, t_lo, t_hi, nz);
+    q9_relax<F, S>(a, f, rho, vx, vy, nz);
 }
 
 // Streaming sources (step (i)) with 32-bit element offsets within a plane:

@@ -44,6 +44,29 @@ hipError_t launch_step2_q9(const lbm_params &p, const StepArgs &a, int rows, con
                            int slot, hipStream_t s);
 // Grid of ntx x nty tiles in row groups (row_group_tile).
 inline dim3 row_group_grid(int ntx, int nty) { return dim3(8u * (unsigned)ntx, (unsigned)((nty + 7) / 8)); }
+// Several steps per launch on small tiles (multi.h).  Geometry of one launch: T
+// steps on tx x ty tiles; the region a block holds is w x h = (tx + 2 R T) x
+// (ty + 2 R T), R = 1 (MIPS 2); mag[k] divides by the width of the box after k
+// steps, s / width = (s mag) >> 22 for s < 4096.
+constexpr int kMultiMaxT = 8;
+struct MultiGeom {
+    int32_t T, tx, ty, w, h;
+    uint32_t mag[kMultiMaxT + 1];
+};
+MultiGeom multi_geom(int model, int T, int tx, int ty);
+// The geometry for lattices of these sizes launched together: T steps per
+// launch (0: none) and its estimated time per step.
+struct MultiChoice {
+    int T = 0, tx = 0, ty = 0;
+    double us = 0.0;
+};
+MultiChoice multi_choose(int model, const int (*sizes)[2], int n);
+// The same for one lattice of lbm_step, T = 0 where another form is faster.
+MultiChoice multi_for_lattice(const lbm_params &p, const StepArgs &a);
+hipError_t launch_multi(const lbm_params &p, const StepArgs &a, const MultiChoice &c, int steps, const void *src, void *dst,
+                        StepClock *clk, int slot, hipStream_t s);
+hipError_t launch_multi_q9(const lbm_params &p, const StepArgs &a, const MultiChoice &c, int steps, const void *src,
+                           void *dst, StepClock *clk, int slot, hipStream_t s);
 // Initial state into dst.
 hipError_t launch_init(const lbm_params &p, const lbm_init &in, const StepArgs &a, void *dst, hipStream_t s);
 // f_i += drho / 7 in place.
@@ -126,4 +149,7 @@ struct lbm_ctx {
     // graphs of kGraphSteps steps starting from buffer 0 and from buffer 1,
     // captured on first use
     hipGraphExec_t graph[2];
+    // how steps are grouped into launches (enqueue_steps)
+    lbm::MultiChoice multi;  // several steps per launch on small tiles (T = 0: not)
+    int rows;                // else two steps per launch on 64 x rows tiles (0: one)
 };
