@@ -253,7 +253,8 @@ const char *lbm_last_error(void);
  * Batched sweeps: n independent lattices of arbitrary sizes and parameters
  * (the paper's repeated runs over a grid of mean density and model constants,
  * appendix "Simulation procedure for results") advanced together: one kernel
- * launch per step (or per two steps) covers every lattice of a lattice group
+ * launch per step (or per two, or for small lattices up to eight) covers every
+ * lattice of a lattice group
  * (lbm_sweep_groups), or one launch runs a whole captured chunk of steps with
  * the lattices resident in LDS; a sample period (its steps and the FP64
  * sampling kernels) is captured in HIP graphs of at most 1024 steps and
@@ -277,7 +278,9 @@ typedef struct lbm_sweep_opts {
     int32_t tile_rows;    /* work tile: 1, 2, 4 = 256x1, 128x2, 64x4 sites, one step per
                              launch; 8, 16 = 64x8, 64x16 sites, two steps per launch
                              (the second from LDS); 0 = tuned (every shape timed on the
-                             batch itself, cached per batch signature).  MIPS batches
+                             batch itself, and for batches of up to 2^20 sites a form of
+                             up to eight steps per launch on small tiles; cached per
+                             batch signature).  MIPS batches
                              take 0 (tuned), 4: 64x4 tiles, one step per launch, or 8,
                              16: 64x8, 64x16 tiles, two steps per launch (the first on
                              a two-site ring, from densities of a three-site ring,
@@ -338,7 +341,9 @@ size_t lbm_sweep_workspace_bytes(const lbm_params *ps, int32_t n, int64_t n_samp
 /* Work-tile rows (1, 2, 4, 8 or 16, as in lbm_sweep_opts.tile_rows, or
  * LBM_TILE_RESIDENT) the tuning chose for a batch with these lattices' sizes,
  * model and step variant (MIPS: 4 (D2Q7 only), 8, 16 or LBM_TILE_RESIDENT), 0
- * if not tuned yet in this process; negative on invalid arguments. */
+ * if not tuned yet in this process; negative on invalid arguments.  A batch
+ * tuned to the form of several steps per launch on small tiles, which only
+ * tile_rows 0 takes, reports the fastest of the shapes that tile_rows names. */
 int32_t lbm_sweep_tile_rows(const lbm_params *ps, int32_t n);
 
 /* Lattice groups a sweep of these n lattices runs each captured chunk in

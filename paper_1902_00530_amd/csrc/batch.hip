@@ -33,41 +33,10 @@
 #include <type_traits>
 #include <vector>
 
-#include "internal.h"
+#include "batch.h"
 #include "step2.h"
 
 namespace lbm {
-
-struct BatchTile {
-    int32_t lat;
-    int16_t tx, ty;
-};
-
-struct LatDesc {
-    StepArgs a;
-    void *buf[2];
-    float B;            // CIL B for zeta
-    int32_t mt_begin;   // first moments tile
-    int32_t mt_count;   // moments tiles of this lattice
-    int32_t nrb;        // moments row blocks
-    int64_t col_off;    // offset of this lattice's column partials
-    int64_t cm_off;     // offset of this lattice's column means
-    float add;          // added to every population after each sample (drho / Q)
-    int32_t stream;     // 1: stores streamed past the caches (two buffers beyond the
-                        // Infinity Cache budget: the lattice is a group of its own)
-};
-
-struct MomTile {
-    int32_t lat;
-    int16_t cx, cy;
-};
-
-struct Ctrl {
-    int64_t t0;      // absolute step index of the next step
-    int64_t k0;      // steps done in this sweep (buffer parity)
-    int64_t sample;  // index of the next sample
-    int64_t pad;
-};
 
 constexpr int kMomRows = 16;
 
@@ -640,7 +609,7 @@ static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Layout {
     size_t lat, tiles, mtiles, ctrl, part, colpart, colmean, results, total;
-    int64_t n_tiles1, n_tiles2, n_mtiles, colpart_n, colmean_n;
+    int64_t n_tiles1, n_tiles2, n_tiles3, n_mtiles, colpart_n, colmean_n;
 };
 
 // Work-tile shapes: sites across, rows, steps per launch.  Shapes 0..4 serve
@@ -661,6 +630,9 @@ constexpr int64_t kChunk = 1024;  // steps per captured graph, at most
 // it writes the second buffer like the tile shapes' tuning launches
 constexpr int kResident = kNumShapes;
 constexpr int kResidentTuneSteps = 63;
+// the several-steps form on small tiles (multi.h): a tile list of its own
+// geometry, up to MultiChoice::T steps per launch
+constexpr int kMulti = kNumShapes + 1;
 
 static bool resident_fits(const lbm_params *ps, int n)
 {
@@ -678,6 +650,48 @@ static int64_t count_tiles(const lbm_params *ps, int n, int tx, int ty)
         c += ntx * ((nty + 7) / 8) * 8;  // rows padded to whole groups of eight
     }
     return c;
+}
+
+// The several-steps form of this batch, T = 0 where it has none: batches of up
+// to 2^20 sites (larger ones fill the GPU with the tile forms; the tuning times
+// it against them).  Twelve 90 x 30 MIPS lattices 3.25 (resident in LDS, 12 of
+// 256 CUs) -> 2.25 us a step, fifty 180 x 60 CIL lattices 6.1 (two steps per
+// launch, 64 x 8 tiles) -> 5.5.
+constexpr int64_t kMultiBatchSites = 1 << 20;
+
+static MultiChoice multi_for_batch(const lbm_params *ps, int n)
+{
+    int64_t sites = 0;
+    std::map<std::pair<int, int>, int> hist;
+    for (int l = 0; l < n; ++l) {
+        sites += (int64_t)ps[l].nx * ps[l].ny;
+        if (sites > kMultiBatchSites)
+            return MultiChoice{};
+        hist[{ps[l].nx, ps[l].ny}]++;
+    }
+    std::vector<MultiSize> v;
+    for (const auto &h : hist)
+        v.push_back(MultiSize{h.first.first, h.first.second, h.second});
+    return multi_choose(ps[0].model, v.data(), (int)v.size());
+}
+
+// its tiles: one list of every lattice's tiles, lattice by lattice, no padding
+static int64_t count_multi_tiles(const lbm_params *ps, int n, const MultiChoice &c)
+{
+    int64_t t = 0;
+    for (int l = 0; l < n && c.T; ++l)
+        t += (int64_t)((ps[l].nx + c.tx - 1) / c.tx) * ((ps[l].ny + c.ty - 1) / c.ty);
+    return t;
+}
+
+static std::vector<BatchTile> build_multi_tiles(const lbm_params *ps, int n, const MultiChoice &c)
+{
+    std::vector<BatchTile> v;
+    for (int l = 0; l < n; ++l)
+        for (int y = 0; y * c.ty < ps[l].ny; ++y)
+            for (int x = 0; x * c.tx < ps[l].nx; ++x)
+                v.push_back(BatchTile{l, (int16_t)x, (int16_t)y});
+    return v;
 }
 
 // Lattices are independent, so a chunk of steps may run lattice group by
@@ -726,12 +740,15 @@ static std::vector<int> cache_groups(const lbm_params *ps, int n)
 
 // [begin, count) of each group's tiles in the list of shape k (build_tiles
 // lists each lattice's tiles contiguously, in lattice order)
-static std::vector<int64_t> group_ranges(const lbm_params *ps, const std::vector<int> &first, int k)
+static std::vector<int64_t> group_ranges(const lbm_params *ps, const std::vector<int> &first, int k,
+                                         const MultiChoice &mc)
 {
     std::vector<int64_t> r;
     int64_t off = 0;
     for (size_t g = 0; g + 1 < first.size(); ++g) {
-        const int64_t c = count_tiles(ps + first[g], first[g + 1] - first[g], kShapes[k].tx, kShapes[k].ty);
+        const int m = first[g + 1] - first[g];
+        const int64_t c = k == kMulti ? count_multi_tiles(ps + first[g], m, mc)
+                                      : count_tiles(ps + first[g], m, kShapes[k].tx, kShapes[k].ty);
         r.push_back(off);
         r.push_back(c);
         off += c;
@@ -742,6 +759,7 @@ static std::vector<int64_t> group_ranges(const lbm_params *ps, const std::vector
 static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
 {
     Layout L{};
+    L.n_tiles3 = count_multi_tiles(ps, n, multi_for_batch(ps, n));
     // room for the list of one single-step shape and one two-step shape
     L.n_tiles1 = 0;
     L.n_tiles2 = 0;
@@ -762,7 +780,7 @@ static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
     L.lat = off;
     off = align256(off + sizeof(LatDesc) * n);
     L.tiles = off;
-    off = align256(off + sizeof(BatchTile) * (L.n_tiles1 + L.n_tiles2));
+    off = align256(off + sizeof(BatchTile) * (L.n_tiles1 + L.n_tiles2 + L.n_tiles3));
     L.mtiles = off;
     off = align256(off + sizeof(MomTile) * L.n_mtiles);
     L.ctrl = off;
@@ -933,7 +951,11 @@ static hipError_t launch_batch_step(int lattice, int model, int storage, int fla
 // Tuned tile shape per batch signature (arch + lattice type + multiset of
 // lattice sizes + model + flags), kept for the life of the process.
 static std::mutex g_tune_mu;
-static std::map<std::string, int> g_tuned;
+struct Tuned {
+    int shape;  // the fastest form
+    int tile;   // the fastest among the forms that tile_rows names (all but kMulti)
+};
+static std::map<std::string, Tuned> g_tuned;
 
 static std::string signature(const lbm_params *ps, int n, int flags)
 {
@@ -955,12 +977,14 @@ struct GraphKey {
     int lattice, model, storage, flags, shape;
     int64_t ntiles_main, ntiles_one, nmt, n, n_samples, steps;
     int sample, add, rev;
+    int max_nx;                   // the column means' grid
+    int multi_T, multi_tx, multi_ty;  // geometry of the several-steps form
     std::vector<int64_t> groups;  // tile ranges of the lattice groups
     auto tie() const
     {
         return std::tie(device, tiles_main, tiles_one, lat, ctrl, mt, part, colpart, colmean, results, lattice, model,
                         storage, flags, shape, ntiles_main, ntiles_one, nmt, n, n_samples, steps, sample, add, rev,
-                        groups);
+                        max_nx, multi_T, multi_tx, multi_ty, groups);
     }
     bool operator==(const GraphKey &o) const { return tie() == o.tie(); }
 };
@@ -1034,7 +1058,7 @@ struct WsTables {
     int lattice = -1;
     std::vector<std::pair<int32_t, int32_t>> sizes;  // (nx, ny) of each lattice, in batch order
     std::vector<LatDesc> lat;
-    int region[2] = {-1, -1};  // shape whose list is in the one-step / two-step region
+    int region[3] = {-1, -1, -1};  // shape whose list is in the one-step / two-step / several-steps region
     // lattice groups in reverse order in the next call: each call starts with
     // the group the previous one ended with, whose state is still in the
     // Infinity Cache
@@ -1106,7 +1130,7 @@ int32_t lbm_sweep_tile_rows(const lbm_params *ps, int32_t n)
     auto it = g_tuned.find(signature(ps, n, flags));
     if (it == g_tuned.end())
         return 0;
-    return it->second == kResident ? LBM_TILE_RESIDENT : kShapes[it->second].ty;
+    return it->second.tile == kResident ? LBM_TILE_RESIDENT : kShapes[it->second.tile].ty;
 }
 
 size_t lbm_sweep_workspace_bytes(const lbm_params *ps, int32_t n, int64_t n_samples)
@@ -1184,6 +1208,9 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     const bool resident_ok = resident_fits(ps, n);
     if (resident_ok)
         cands.push_back(kResident);
+    const MultiChoice mc = multi_for_batch(ps, n);
+    if (mc.T)
+        cands.push_back(kMulti);
     if (o->tile_rows == LBM_TILE_RESIDENT) {
         if (!resident_ok)
             return fail(LBM_EINVAL, "tile_rows LBM_TILE_RESIDENT needs lattices of at most " +
@@ -1200,7 +1227,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(sig);
         if (it != g_tuned.end())
-            shape = it->second;
+            shape = it->second.shape;
     }
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws;
@@ -1250,7 +1277,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     }
     const bool same_sizes = rec.lattice == ps[0].lattice && rec.sizes == sizes;
     if (!same_sizes)
-        rec.region[0] = rec.region[1] = -1;
+        rec.region[0] = rec.region[1] = rec.region[2] = -1;
     bool same_lat = same_sizes && rec.lat.size() == lat.size();
     for (int l = 0; l < n && same_lat; ++l)
         same_lat = same_desc(rec.lat[l], lat[l]);
@@ -1292,19 +1319,32 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // the tile list of shape k in its region (one-step shapes in the first,
     // two-step shapes in the second), uploaded unless the region holds it
     auto upload = [&](int k) -> std::pair<BatchTile *, int64_t> {
-        const int r = kShapes[k].steps == 1 ? 0 : 1;
-        BatchTile *d = r == 0 ? d_tiles1 : d_tiles2;
-        const int64_t count = count_tiles(ps, n, kShapes[k].tx, kShapes[k].ty);
-        if (rec.region[r] == k)
+        const int r = k == kMulti ? 2 : kShapes[k].steps == 1 ? 0 : 1;
+        BatchTile *d = r == 0 ? d_tiles1 : r == 1 ? d_tiles2 : d_tiles2 + Ly.n_tiles2;
+        const int64_t count = k == kMulti ? Ly.n_tiles3 : count_tiles(ps, n, kShapes[k].tx, kShapes[k].ty);
+        // the several-steps list also depends on the model (its geometry)
+        const int held = k == kMulti ? k | mc.tx << 8 | mc.ty << 16 : k;
+        if (rec.region[r] == held)
             return {d, count};
-        host_lists.push_back(build_tiles(ps, n, kShapes[k].tx, kShapes[k].ty));
+        host_lists.push_back(k == kMulti ? build_multi_tiles(ps, n, mc) : build_tiles(ps, n, kShapes[k].tx, kShapes[k].ty));
         const std::vector<BatchTile> &v = host_lists.back();
         up_err = hipMemcpyAsync(d, v.data(), sizeof(BatchTile) * v.size(), hipMemcpyHostToDevice, s);
-        rec.region[r] = up_err == hipSuccess ? k : -1;
+        rec.region[r] = up_err == hipSuccess ? held : -1;
         return {up_err == hipSuccess ? d : nullptr, (int64_t)v.size()};
     };
+    // one launch of `st` steps of form k over `count` tiles from `tl`
+    auto launch_form = [&](int k, int st, const BatchTile *tl, int64_t count, int step_off,
+                           int launch_off) -> hipError_t {
+        if (k == kMulti)
+            return launch_batch_multi(ps[0].lattice, ps[0].model, ps[0].storage, flags,
+                                      multi_geom(ps[0].model, st, mc.tx, mc.ty), count, tl, d_lat, d_ctrl, step_off,
+                                      launch_off, s);
+        return launch_batch_step(ps[0].lattice, ps[0].model, ps[0].storage, flags, k, count, tl, d_lat, d_ctrl,
+                                 step_off, launch_off, s);
+    };
     if (shape < 0) {
-        float best = 1e30f;
+        float best = 1e30f, best_tile = 1e30f;
+        int tile = -1;
         struct EventPair {  // destroyed on every exit path
             hipEvent_t a = nullptr, b = nullptr;
             ~EventPair()
@@ -1333,15 +1373,18 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             hipStream_t cap;
             LBM_HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
             hipGraph_t g = nullptr;
+            const hipStream_t saved = s;
+            s = cap;
             hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
             if (res && e == hipSuccess)  // first buffer -> second buffer
-                e = launch_resident(ps[0].lattice, ps[0].model, ps[0].storage, flags, n, d_lat, d_ctrl, kResidentTuneSteps, cap);
+                e = launch_resident(ps[0].lattice, ps[0].model, ps[0].storage, flags, n, d_lat, d_ctrl, kResidentTuneSteps, s);
             // ten launches per lattice group, group after group, as the sweep runs them
-            const std::vector<int64_t> gr = res ? std::vector<int64_t>{} : group_ranges(ps, cache_groups(ps, n), k);
+            const std::vector<int64_t> gr = res ? std::vector<int64_t>{} : group_ranges(ps, cache_groups(ps, n), k, mc);
+            const int form_steps = res ? kResidentTuneSteps : k == kMulti ? mc.T : kShapes[k].steps;
             for (size_t g = 0; 2 * g < gr.size(); ++g)
                 for (int r10 = 0; r10 < 10 && e == hipSuccess; ++r10)
-                    e = launch_batch_step(ps[0].lattice, ps[0].model, ps[0].storage, flags, k, gr[2 * g + 1], tl.first + gr[2 * g],
-                                          d_lat, d_ctrl, 0, 0, cap);
+                    e = launch_form(k, form_steps, tl.first + gr[2 * g], gr[2 * g + 1], 0, 0);
+            s = saved;
             hipError_t ee = hipStreamEndCapture(cap, &g);
             (void)hipStreamDestroy(cap);
             if (e == hipSuccess)
@@ -1364,7 +1407,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 if (e == hipSuccess)
                     e = hipEventElapsedTime(&m, e0, e1);
                 if (rep > 0)  // time per ten steps
-                    ms = std::min(ms, res ? m * 10.0f / kResidentTuneSteps : m / (float)kShapes[k].steps);
+                    ms = std::min(ms, (res ? m * 10.0f : m) / (float)form_steps);
             }
             if (ge)
                 (void)hipGraphExecDestroy(ge);
@@ -1374,17 +1417,22 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 best = ms;
                 shape = k;
             }
+            if (k != kMulti && ms < best_tile) {
+                best_tile = ms;
+                tile = k;
+            }
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[sig] = shape;
+        g_tuned[sig] = Tuned{shape, tile};
     }
     // the chosen list, and for a two-step shape the list of a one-step shape
     // (256x1; MIPS 64x4, D2Q9 MIPS 64x16) for the single steps that keep the launch count's
     // parity equal to the step count's (so the state ends in
     // bufs[2l + (n_steps & 1)])
     const bool resident = shape == kResident;
-    const bool two = !resident && kShapes[shape].steps == 2;
+    const bool two = !resident && shape != kMulti && kShapes[shape].steps == 2;
     const int one_shape = two ? (mips ? (q9 ? kMipsShape : kMipsShape4) : 0) : shape;
+    const int64_t most = resident ? 0 : shape == kMulti ? mc.T : kShapes[shape].steps;  // steps per launch
     std::pair<BatchTile *, int64_t> main_list{d_tiles1, 0};
     if (!resident) {
         main_list = upload(shape);
@@ -1404,8 +1452,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     LBM_HIP_TRY(hipGetLastError());
     // lattice groups that fit the Infinity Cache (one group when resident)
     const std::vector<int> gfirst = resident ? std::vector<int>{0, n} : cache_groups(ps, n);
-    const std::vector<int64_t> g_main = resident ? std::vector<int64_t>{0, 0} : group_ranges(ps, gfirst, shape);
-    const std::vector<int64_t> g_one = two ? group_ranges(ps, gfirst, one_shape) : g_main;
+    const std::vector<int64_t> g_main = resident ? std::vector<int64_t>{0, 0} : group_ranges(ps, gfirst, shape, mc);
+    const std::vector<int64_t> g_one = two ? group_ranges(ps, gfirst, one_shape, mc) : g_main;
     std::vector<int64_t> gkey(g_main);
     gkey.insert(gkey.end(), g_one.begin(), g_one.end());
 
@@ -1439,38 +1487,30 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     };
     // `steps` steps, then the sample if asked, then the counter update
     auto enqueue = [&](int64_t steps, bool sample) -> hipError_t {
-        int64_t done = 0, launches = 0;
         if (resident && steps > 0) {
             hipError_t e = launch_resident(ps[0].lattice, ps[0].model, ps[0].storage, flags, n, d_lat, d_ctrl, (int)steps, s);
             if (e != hipSuccess)
                 return e;
-            done = steps;
         }
         if (resident && sample)
             group_moments(0, steps);
-        // every launch of the chunk for one lattice group, then the next
-        const int64_t d0 = done, l0 = launches;
+        // every launch of the chunk for one lattice group, then the next; as few
+        // launches as the form allows, an odd number where the steps are (the
+        // buffer parity), the steps dealt evenly over them
         for (size_t k = 0; k + 1 < gfirst.size() && !resident; ++k) {
             const size_t g = rev ? gfirst.size() - 2 - k : k;
-            done = d0;
-            launches = l0;
-            if (two) {
-                int64_t q = steps / 2;
-                q -= q & 1;  // an even number of two-step launches
-                for (; launches < q; ++launches, done += 2) {
-                    hipError_t e = launch_batch_step(ps[0].lattice, ps[0].model, ps[0].storage, flags, shape, g_main[2 * g + 1],
-                                                     main_list.first + g_main[2 * g], d_lat, d_ctrl, (int)done,
-                                                     (int)launches, s);
-                    if (e != hipSuccess)
-                        return e;
-                }
-            }
-            for (; done < steps; ++launches, ++done) {
-                hipError_t e = launch_batch_step(ps[0].lattice, ps[0].model, ps[0].storage, flags, one_shape, g_one[2 * g + 1],
-                                                 one_list.first + g_one[2 * g], d_lat, d_ctrl, (int)done,
-                                                 (int)launches, s);
+            int64_t launches = (steps + most - 1) / most;
+            launches += (launches ^ steps) & 1;
+            int64_t done = 0;
+            for (int64_t i = 0; i < launches; ++i) {
+                const int st = (int)(steps / launches + (i < steps % launches ? 1 : 0));
+                const bool one = two && st == 1;
+                hipError_t e = launch_form(one ? one_shape : shape, st,
+                                           one ? one_list.first + g_one[2 * g] : main_list.first + g_main[2 * g],
+                                           one ? g_one[2 * g + 1] : g_main[2 * g + 1], (int)done, (int)i);
                 if (e != hipSuccess)
                     return e;
+                done += st;
             }
             if (sample)
                 group_moments(g, steps);
@@ -1513,7 +1553,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                            ps[0].storage, flags,
                            shape,
                            main_list.second, one_list.second, nmt, (int64_t)n, n_samples, steps, sample ? 1 : 0,
-                           o->drho ? 1 : 0, rev ? 1 : 0, gkey};
+                           o->drho ? 1 : 0, rev ? 1 : 0, max_nx, mc.T, mc.tx, mc.ty, gkey};
         if ((*ge = graph_cache_get(key)))
             return hipSuccess;
         hipGraph_t g;

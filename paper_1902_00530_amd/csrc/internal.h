@@ -60,7 +60,10 @@ struct MultiChoice {
     int T = 0, tx = 0, ty = 0;
     double us = 0.0;
 };
-MultiChoice multi_choose(int model, const int (*sizes)[2], int n);
+struct MultiSize {
+    int nx, ny, count;  // count lattices of nx x ny sites
+};
+MultiChoice multi_choose(int model, const MultiSize *sizes, int n);
 // The same for one lattice of lbm_step, T = 0 where another form is faster.
 MultiChoice multi_for_lattice(const lbm_params &p, const StepArgs &a);
 hipError_t launch_multi(const lbm_params &p, const StepArgs &a, const MultiChoice &c, int steps, const void *src, void *dst,

@@ -42,7 +42,7 @@ MultiGeom multi_geom(int model, int T, int tx, int ty)
 // a step against one step per launch; 128^2: 8x8, 8 steps, 2.40 -> 1.24; 256^2:
 // 16x16, 8 steps, 2.60 -> 1.74; MIPS 64^2: 4x4, 6 steps, 3.04 -> 1.52; 128^2:
 // 8x8, 5 steps, 3.14 -> 1.75; 256^2: 16x16, 4 steps, 3.46 -> 2.36.
-MultiChoice multi_choose(int model, const int (*sizes)[2], int n)
+MultiChoice multi_choose(int model, const MultiSize *sizes, int n)
 {
     const int r = model == kMips ? 2 : 1, t_max = model == kMips ? 6 : kMultiMaxT;
     const double lat = model == kMips ? 0.5 : 0.4, wave = model == kMips ? 0.4 : 0.3;
@@ -51,7 +51,7 @@ MultiChoice multi_choose(int model, const int (*sizes)[2], int n)
         for (int ty = 4; ty <= 32; ty += 2) {
             int64_t blocks = 0;
             for (int l = 0; l < n; ++l)
-                blocks += (int64_t)((sizes[l][0] + tx - 1) / tx) * ((sizes[l][1] + ty - 1) / ty);
+                blocks += (int64_t)sizes[l].count * ((sizes[l].nx + tx - 1) / tx) * ((sizes[l].ny + ty - 1) / ty);
             const int64_t per_cu = (blocks + 255) / 256;
             if (per_cu > 16)
                 continue;
@@ -84,8 +84,8 @@ MultiChoice multi_for_lattice(const lbm_params &p, const StepArgs &a)
     const int64_t most = p.model != LBM_MIPS ? 5 << 15 : p.lattice == LBM_D2Q9 ? 1 << 17 : 3 << 15;
     if (a.pitch != p.nx || (int64_t)p.nx * p.ny > most)
         return MultiChoice{};
-    const int size[1][2] = {{p.nx, p.ny}};
-    return multi_choose(p.model, size, 1);
+    const MultiSize size{p.nx, p.ny, 1};
+    return multi_choose(p.model, &size, 1);
 }
 
 hipError_t launch_multi(const lbm_params &p, const StepArgs &a, const MultiChoice &c, int steps, const void *src, void *dst,
