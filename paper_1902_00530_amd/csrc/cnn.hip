@@ -6,16 +6,26 @@
 // Boltzmann step itself.
 //
 // Layout: activations NCHW float32; weights stored as bfloat16 (the Adam
-// step keeps float32 master copies) and widened once per pass to float32, so
-// every product is a bf16 x f32 -> f32 product with float32 accumulation.
-// Convolutions (bf16 operands: the weights, and each activation split into
-// three bf16 parts) and weight gradients (FP32 operands) are matrix products
-// on the matrix cores over 16 x 8 pixel tiles staged in LDS with their halo.
-// Reductions (weight gradients, loss) use fixed partitions and orders, so
-// results are deterministic.
+// step keeps float32 master copies), so every product is a bf16 x f32 -> f32
+// product with float32 accumulation.  Convolutions (bf16 operands: the
+// weights, and each activation split into three bf16 parts) and weight
+// gradients (FP32 operands) are matrix products on the matrix cores over
+// 16 x 8 pixel tiles staged in LDS with their halo.  Reductions (weight
+// gradients, loss) use fixed partitions and orders, so results are
+// deterministic.
+//
+// A pass is a few launches: the forward pass one (k_cnn_forward, with the
+// normalisation before it and the loss, or the return to physical fields,
+// after it), the input gradients one (k_cnn_dgrad), the weight gradients one
+// (k_cnn_wgrad), their sums, the loss and Adam one (k_cnn_reduce).  The fields
+// are small (tens of pixels a side), so a pass of one kernel per layer was
+// bound by launches, staging and gaps: 64 samples of 32 x 32 took 36.1 us to
+// predict (6 launches; now 15.2 us, 1 launch) and 132.4 us to train on (18
+// launches; now 73.5 us, 4 launches).
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/lbm_cnn.h"
 #include "internal.h"
@@ -29,88 +39,83 @@ namespace lbm {
 // m + l + r with |r| < 2^-24 |x| (h: x with its low 16 bits cleared, m and l
 // the same of the exact remainders), and the product of each part with the
 // weight is exact, so the three products together give the float32 product
-// and only the order of the float32 sums differs from the definition.  A
-// 16 x 8 pixel tile of one sample per block (four waves, one 32-pixel slab
-// each: two image rows of 16), its input split and stored channel-last in
-// LDS with the one-pixel circular halo, every channel at once (ci, co <= 32).
+// and only the order of the float32 sums differs from the definition.
 //
-// Convolution as a matrix product per slab: D[pixel][o] = sum_k A[pixel][k]
-// B[k][o], k = tap * CP + c (tap = 3 ky + kx, c < CP = ci rounded up to 16
-// with zero channels), A the input at the pixel shifted by the tap, B[k][o]
-// = wb[o][tap][c] (bf16).  TR = 0 weights: wb[o][tap][c] = w[o][c][tap]: y =
-// b[o] + sum_c sum_tap w[o,c,tap] x[n,c,i+ky-1,j+kx-1].  The input gradient
-// of a convolution whose weights are w[c][o][tap] takes wb[o][tap][c] =
-// w[c][o][8 - tap], the transposed, flipped weights (both written by
-// k_widen).  Epilogue in order: bias, ReLU, + resid[n, o] (first co channels
-// of a tensor with resid_c channels), * (mask[n, o] > 0).
+// A block owns a 16 x 8 pixel tile of one sample.  A layer's output on the
+// tile widened by R pixels (16 + 2 R by 8 + 2 R, circular) comes from its input
+// on the tile widened by R + 1: consecutive layers run in one block, each on a
+// region one pixel narrower than the last, halo pixels computed again by every
+// block that needs them (at their periodic images, with the same sums, so
+// every block gets the same values), and hidden activations pass through LDS.
+//
+// Convolution as a matrix product per slab of 32 pixels: D[o][pixel] = sum_k
+// A[o][k] B[k][pixel], k = tap * CP + c (tap = 3 ky + kx, c < CP = ci rounded up
+// to 16 with zero channels), A the weights, B the input at the pixel shifted
+// by the tap, channel-last in LDS.  The input gradient of a convolution with
+// weights w[c][o][tap] is the convolution with wt[o][tap][c] = w[c][o][8 - tap].
 //
 // MFMA 32x32x16 operand layout (per lane l of the wave): A row l mod 32 with
 // k = 8 (l / 32) + j, j < 8; B column l mod 32, the same k; result register r
-// holds row 8 (r / 4) + 4 (l / 32) + r mod 4 of column l mod 32.  Each step
-// takes one tap and 16 channels, so a lane's eight A values (channels c0 +
-// 8 (l / 32) ..) and eight B values are 16 contiguous bytes of LDS.
+// holds row 8 (r / 4) + 4 (l / 32) + r mod 4 of column l mod 32: a lane has
+// one pixel and, per four registers, four consecutive channels, which go to
+// LDS in one 8-byte write per part and to memory in rows of 16 pixels.
 // ---------------------------------------------------------------------------
 constexpr int kTW = 16, kTH = 8;                   // pixel tile
-constexpr int kHW_ = kTW + 2, kHH = kTH + 2;       // with the halo
+constexpr int kHW_ = kTW + 2, kHH = kTH + 2;       // with a one-pixel halo
 constexpr int kHalo = kHW_ * kHH;                  // 180 pixels
 constexpr int kMaxC = 32;                          // channels
+constexpr int kCnnWaves = 8;                       // waves of a forward / input-gradient block
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// v in [-1, n + kHW_ - 2] wrapped into [0, n); SMALL: n may be smaller than
-// the halo tile, so v may wrap more than once
+// the tile widened by R pixels
+template <int R>
+struct Region {
+    static constexpr int W = kTW + 2 * R, H = kTH + 2 * R, N = W * H;
+    static constexpr int kSlabs = 4 + (N - kTW * kTH + 31) / 32;
+    // Pixel (ry, rx) of the region that column m of slab s takes: slabs 0..3
+    // the tile itself, two image rows of 16 each, the others the ring around
+    // it; false past the ring's end (the pixel is then a valid one all the
+    // same).
+    __device__ static bool pixel(int s, int m, int &ry, int &rx)
+    {
+        if (R == 0 || s < 4) {
+            ry = R + 2 * s + (m >> 4);
+            rx = R + (m & 15);
+            return true;
+        }
+        int e = (s - 4) * 32 + m;
+        const bool live = e < N - kTW * kTH;
+        e = live ? e : 0;
+        if (e < 2 * R * W) {  // the rows above and below
+            const int row = e / W;
+            ry = row < R ? row : H - 2 * R + row;
+            rx = e - row * W;
+        } else {  // the columns left and right
+            constexpr int R2 = R ? 2 * R : 1;
+            e -= 2 * R * W;
+            const int row = e / R2, c = e - row * R2;
+            ry = R + row;
+            rx = c < R ? c : W - 2 * R + c;
+        }
+        return live;
+    }
+};
+
+// v >= -3 wrapped into [0, n); SMALL: n may be smaller than the widened tile,
+// so v may wrap more than once
 template <bool SMALL>
 __device__ __forceinline__ int wrap_index(int v, int n)
 {
     if (SMALL)
-        return (v + n) % n;
+        return (v + 3 * n) % n;
     return v < 0 ? v + n : (v >= n ? v - n : v);
 }
 
-// LDS staging with every global load of a thread in flight before the first
-// LDS write: element e < count (count > 0) of the block's copy is get(e) (a
-// load from an address that is valid for every e < count) stored by put(e).
-template <int NT, int MAXE, class Get, class Put>
-__device__ __forceinline__ void stage(int count, Get get, Put put)
+__device__ __forceinline__ int wrap_index(bool small, int v, int n)
 {
-    constexpr int U = (MAXE + NT - 1) / NT;
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        v[u] = get(min((int)threadIdx.x + u * NT, count - 1));
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int e = threadIdx.x + u * NT;
-        if (e < count)
-            put(e, v[u]);
-    }
-}
-
-// element e = c * kHalo + hy * kHW_ + hx of the input tile of sample n with
-// its circular halo (0 for c >= ci_n); offsets within a sample fit 32 bits
-// (ci h w < 2^31)
-template <bool SMALL>
-__device__ __forceinline__ float halo_value(const float *__restrict__ xn, int ci_n, int H, int W, int i0, int j0, int e)
-{
-    const int c = e / kHalo, r = e - c * kHalo, hy = r / kHW_, hx = r - hy * kHW_;
-    const int gi = wrap_index<SMALL>(i0 + hy - 1, H), gj = wrap_index<SMALL>(j0 + hx - 1, W);
-    const float v = xn[(unsigned)min(c, ci_n - 1) * (unsigned)H * (unsigned)W + (unsigned)gi * (unsigned)W + (unsigned)gj];
-    return c < ci_n ? v : 0.0f;
-}
-
-// the input tile as float32, s[c][hy][hx], c < cpad <= MAXC (halo values of
-// pixels outside the field feed no output)
-template <int NT, int MAXC>
-__device__ __forceinline__ void stage_halo(const float *__restrict__ x, int n, int ci_n, int cpad, int H, int W, int i0,
-                                           int j0, float *s)
-{
-    const float *xn = x + (size_t)n * ci_n * H * W;
-    auto put = [&](int e, float v) { s[e] = v; };
-    if (H >= kHH && W >= kHW_)
-        stage<NT, MAXC * kHalo>(cpad * kHalo, [&](int e) { return halo_value<false>(xn, ci_n, H, W, i0, j0, e); }, put);
-    else
-        stage<NT, MAXC * kHalo>(cpad * kHalo, [&](int e) { return halo_value<true>(xn, ci_n, H, W, i0, j0, e); }, put);
+    return small ? wrap_index<true>(v, n) : wrap_index<false>(v, n);
 }
 
 // the three bf16 parts of x (bit patterns): x = h + m + l + r, |r| < 2^-24 |x|
@@ -125,163 +130,142 @@ __device__ __forceinline__ void split3(float x, uint16_t &h, uint16_t &m, uint16
     l = (uint16_t)(__float_as_uint(r2) >> 16);
 }
 
+// four values split into s (element index e, a multiple of 4) of three parts
+// `parts` elements apart
+__device__ __forceinline__ void put_split4(uint16_t *s, int e, int parts, const float v[4])
+{
+    uint16_t h[4], m[4], l[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        split3(v[u], h[u], m[u], l[u]);
+    auto pack = [](const uint16_t *q) {
+        return make_uint2((uint32_t)q[0] | (uint32_t)q[1] << 16, (uint32_t)q[2] | (uint32_t)q[3] << 16);
+    };
+    *(uint2 *)(s + e) = pack(h);
+    *(uint2 *)(s + parts + e) = pack(m);
+    *(uint2 *)(s + 2 * parts + e) = pack(l);
+}
+
 __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// CP: input channels rounded up to 16 (16 or 32).
+// LDS layouts.  Inputs: [part][pixel][channel], pixels of CS elements;
+// weights: [out][tap][channel], taps of TS elements, rows of WS.  Padded so
+// that eight consecutive lanes' 16-byte reads fall in distinct banks (32
+// channels: also the 2-byte writes of consecutive taps).  CP = 4: at most
+// four channels, held without the zero ones, which lanes 32..63 (and the
+// upper half of the others) take as zeros.
 template <int CP>
-__global__ __launch_bounds__(256) void k_conv3x3(const float *__restrict__ x, int ci_n, const uint16_t *__restrict__ wb,
-                                                 int co_n, const float *__restrict__ bias,
-                                                 const float *__restrict__ resid, int resid_c,
-                                                 const float *__restrict__ mask, int relu, float *__restrict__ y,
-                                                 int H, int W)
+struct ConvLds {
+    static constexpr int CS = CP == 4 ? 4 : CP + 8;
+    static constexpr int TS = CP == 4 ? 4 : CP == 16 ? 24 : 40;
+    static constexpr int WS = 9 * TS + (CP == 4 ? 4 : 8);
+};
+// The first layer's: with 17 to 32 channels no padding of pixels and taps, so
+// that every layer's tiles fit a CU's LDS together.
+template <int CP>
+struct FirstLds : ConvLds<CP> {};
+template <>
+struct FirstLds<32> {
+    static constexpr int CS = 32, TS = 32, WS = 9 * TS + 8;
+};
+
+// One slab: x the LDS input of `parts` elements per part, p the pixel at the
+// lane's top-left tap, RW the input region's width; w the lane's weight row.
+// A tap's operands are read while the previous tap multiplies: left to the
+// compiler, each read was waited on right before its product, and a wave alone
+// on its SIMD took 69 cycles a product instead of the 35 it issues in.
+template <int CP, int CS, int TS, int RW>
+__device__ __forceinline__ f32x16 conv_slab(const uint16_t *x, int parts, int p, const uint16_t *w, int hk)
 {
-    // strides (bf16 elements) padded so that eight consecutive lanes' 16-byte
-    // reads fall in distinct banks
-    constexpr int CPS = CP + 8, WS = 9 * CP + 8;
-    __shared__ __attribute__((aligned(16))) uint16_t s_x[3 * kHalo * CPS];  // [part][pixel][channel]
-    __shared__ __attribute__((aligned(16))) uint16_t s_w[kMaxC * WS];      // [out][tap][channel]
-    const int n = blockIdx.z, i0 = blockIdx.y * kTH, j0 = blockIdx.x * kTW;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    {
-        const float *xn = x + (size_t)n * ci_n * H * W;
-        auto put = [&](int e, float v) {
-            const int c = e / kHalo, pix = e - c * kHalo;
-            uint16_t h, m, l;
-            split3(v, h, m, l);
-            s_x[pix * CPS + c] = h;
-            s_x[(kHalo + pix) * CPS + c] = m;
-            s_x[(2 * kHalo + pix) * CPS + c] = l;
-        };
-        if (H >= kHH && W >= kHW_)
-            stage<256, CP * kHalo>(CP * kHalo, [&](int e) { return halo_value<false>(xn, ci_n, H, W, i0, j0, e); },
-                                   put);
-        else
-            stage<256, CP * kHalo>(CP * kHalo, [&](int e) { return halo_value<true>(xn, ci_n, H, W, i0, j0, e); },
-                                   put);
-    }
-    // B: rows o < co_n of wb (9 CP bf16 each, 16-byte pieces), zero rows after
-    {
-        constexpr int RQ = 9 * CP / 8;  // 16-byte pieces per row
-        const uint4 *src = (const uint4 *)wb;
-        for (int e = threadIdx.x; e < kMaxC * RQ; e += 256) {
-            const int o = e / RQ, q = e - o * RQ;
-            const uint4 v = o < co_n ? src[(size_t)o * RQ + q] : make_uint4(0u, 0u, 0u, 0u);
-            *(uint4 *)(s_w + o * WS + q * 8) = v;
-        }
-    }
-    __syncthreads();
-    const int m = lane & 31, hk = lane >> 5;        // A row (pixel of the slab) / B column, k half
-    const int pr = 2 * wv + (m >> 4), pc = m & 15;  // tile row and column of the A row's pixel
-    const uint16_t *pa = s_x + (pr * kHW_ + pc) * CPS + 8 * hk;
-    const uint16_t *pb = s_w + m * WS + 8 * hk;
+    constexpr int NC = CP <= 16 ? 1 : CP / 16;  // 16-channel steps of a tap
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         acc[r] = 0.0f;
+    const uint16_t *px = x + p * CS + (CP == 4 ? 0 : 8 * hk), *pw = w + (CP == 4 ? 0 : 8 * hk);
+    using Raw = std::conditional_t<CP == 4, uint2, uint4>;
+    Raw fa[2][NC], fb[2][NC][3];
+    auto read = [&](int t) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-#pragma unroll
-        for (int c0 = 0; c0 < CP; c0 += 16) {
-            const bf16x8 b = *(const bf16x8 *)(pb + t * CP + c0);
-            const int off = ((t / 3) * kHW_ + t % 3) * CPS + c0;
+        for (int c = 0; c < NC; ++c) {
+            fa[t & 1][c] = *(const Raw *)(pw + t * TS + 16 * c);
 #pragma unroll
             for (int part = 0; part < 3; ++part)
-                acc = mfma_bf16(*(const bf16x8 *)(pa + part * kHalo * CPS + off), b, acc);
+                fb[t & 1][c][part] = *(const Raw *)(px + part * parts + ((t / 3) * RW + t % 3) * CS + 16 * c);
         }
+    };
+    auto operand = [&](const Raw &v) -> bf16x8 {
+        if constexpr (CP == 4)
+            return __builtin_bit_cast(bf16x8, make_uint4(hk ? 0u : v.x, hk ? 0u : v.y, 0u, 0u));
+        else
+            return __builtin_bit_cast(bf16x8, v);
+    };
+    read(0);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        if (t < 8)
+            read(t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int part = 0; part < 3; ++part)
+                acc = mfma_bf16(operand(fa[t & 1][c]), operand(fb[t & 1][c][part]), acc);
     }
-    // lane: output channel o = m; register group g holds the four pixels
-    // 8 g + 4 hk .. + 3 of the slab, one image row, consecutive columns
-    const int o = m;
-    if (o >= co_n)
-        return;
-    const size_t HW = (size_t)H * W;
-    const float bo = bias ? bias[o] : 0.0f;
-    float *yo = y + ((size_t)n * co_n + o) * HW;
-    const float *ro = resid ? resid + ((size_t)n * resid_c + o) * HW : nullptr;
-    const float *mo = mask ? mask + ((size_t)n * co_n + o) * HW : nullptr;
-    if ((W & 3) == 0) {
-        // four 16-byte groups (j + 3 < W whenever j < W); the residual and
-        // mask loads of all groups are issued before the first use
-        size_t pix[4];
-        bool ok[4];
-        float4 rq[4], mq[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int i = i0 + 2 * wv + (g >> 1), j = j0 + 8 * (g & 1) + 4 * hk;
-            ok[g] = i < H && j < W;
-            pix[g] = ok[g] ? (size_t)i * W + j : 0;
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            rq[g] = ro ? *(const float4 *)(ro + pix[g]) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            mq[g] = mo ? *(const float4 *)(mo + pix[g]) : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v[u] = acc[4 * g + u] + bo;
-                if (relu)
-                    v[u] = fmaxf(v[u], 0.0f);
-            }
-            if (ro)
-                v[0] += rq[g].x, v[1] += rq[g].y, v[2] += rq[g].z, v[3] += rq[g].w;
-            if (mo) {
-                v[0] = mq[g].x > 0.0f ? v[0] : 0.0f, v[1] = mq[g].y > 0.0f ? v[1] : 0.0f;
-                v[2] = mq[g].z > 0.0f ? v[2] : 0.0f, v[3] = mq[g].w > 0.0f ? v[3] : 0.0f;
-            }
-            if (ok[g])
-                *(float4 *)(yo + pix[g]) = make_float4(v[0], v[1], v[2], v[3]);
-        }
-        return;
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int i = i0 + 2 * wv + (g >> 1), j = j0 + 8 * (g & 1) + 4 * hk;
-        if (i >= H || j >= W)
-            continue;
-        const size_t pix = (size_t)i * W + j;
-        float v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            v[u] = acc[4 * g + u] + bo;
-            if (relu)
-                v[u] = fmaxf(v[u], 0.0f);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (j + u >= W)
-                break;
-            float w = v[u];
-            if (ro)
-                w += ro[pix + u];
-            if (mo)
-                w = mo[pix + u] > 0.0f ? w : 0.0f;
-            yo[pix + u] = w;
-        }
-    }
+    return acc;
 }
 
-// ---------------------------------------------------------------------------
-// Weight and bias gradients: dw[o,c,tap] = sum_{n,i,j} dy[n,o,i,j]
-// x[n,c,i+ky-1,j+kx-1], db[o] = sum dy[n,o,i,j].  One block per (sample,
-// 16 x 8 tile) writes its partial sums to part[block][co_n ci_n 9 + co_n];
-// k_grad_reduce adds the blocks in order in float64.  Per block a matrix
-// product on the matrix cores (v_mfma_f32_16x16x4_f32): D[o][k] = sum_p
-// A[o][p] B[p][k], p the tile's 128 pixels in groups of four neighbours
-// (lane group q = l / 16 takes pixel 4 s + q of step s), k = c * 9 + tap.
-// The output is cut into 16 x 16 blocks (rows o, columns k), dealt to the
-// four waves in turn; the bias sums are per-row wave reductions of the dy
-// tile in a fixed order.
-//
-// 16x16x4 operand layout (lane l): A row l mod 16, k = l / 16; B column
-// l mod 16, k = l / 16; result register r holds row 4 (l / 16) + r of
-// column l mod 16.
-// ---------------------------------------------------------------------------
+// bf16 weights [rows][9] of `rows` 3x3 kernels (9 rows a multiple of 8), loaded
+// eight to a thread (16 bytes where the pointer allows it), then handed to
+// put(row, tap, value).  Split in two, so that a block's loads are all in
+// flight before its first LDS write.
+template <int NT, int ROWS>
+struct WeightStage {
+    static constexpr int U = (ROWS * 9 / 8 + NT - 1) / NT;
+    uint4 v[U];
+    __device__ __forceinline__ void load(const uint16_t *__restrict__ w, int rows)
+    {
+        const int last = rows * 9 / 8 - 1;
+        const bool wide = ((uintptr_t)w & 15) == 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = min((int)threadIdx.x + u * NT, last);
+            if (wide) {
+                v[u] = ((const uint4 *)w)[q];
+            } else {
+                uint32_t d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    d[k] = (uint32_t)w[8 * q + 2 * k] | (uint32_t)w[8 * q + 2 * k + 1] << 16;
+                v[u] = make_uint4(d[0], d[1], d[2], d[3]);
+            }
+        }
+    }
+    template <class Put>
+    __device__ __forceinline__ void store(int rows, Put put) const
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = threadIdx.x + u * NT;
+            if (q >= rows * 9 / 8)
+                continue;
+            const uint32_t d[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            int row = 8 * q / 9, t = 8 * q - 9 * row;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                put(row, t, (uint16_t)(d[k >> 1] >> 16 * (k & 1)));
+                if (++t == 9) {
+                    t = 0;
+                    ++row;
+                }
+            }
+        }
+    }
+};
+
 __device__ __forceinline__ double cwave_sum(double v)
 {
 #pragma unroll
@@ -290,122 +274,640 @@ __device__ __forceinline__ double cwave_sum(double v)
     return v;
 }
 
+// ---------------------------------------------------------------------------
+// Forward pass.  kCnnRaw: x as it is; a1, a2 and y out.  kCnnPredict: x
+// normalised on the way in, y the physical fields (channels past the third
+// copied from x), nothing else written.  kCnnTrain: samples idx[n], x and the
+// target normalised; a1, a2, the normalised x (the weight gradient's input),
+// dy = 2 (y - t) / count and each block's float64 sum of (y - t)^2 out.
+//
+// One block per tile, all three layers: LDS holds the input on 22 x 14 pixels
+// (at most four channels: 7 KB), a1 on 20 x 12 and a2 on 18 x 10 (58 and 43
+// KB) and the weights (28 KB), so one block of eight waves fits a CU.  The halo
+// costs 1.4 times the products, which are a few us in all; what the separate
+// layers cost was staging, launches and the normalisation's passes.  A block
+// takes every 256th tile, its weights staged once and the next tile's input
+// loaded during the last layer.  What bounds it: per tile about 16,000 cycles of
+// three phases between barriers with two waves a SIMD, of which the products
+// are 6,000; 17 us for 512 tiles against 45 us of kernels before.
+// ---------------------------------------------------------------------------
+enum CnnMode : int { kCnnRaw = 0, kCnnPredict = 1, kCnnTrain = 2 };
+
+struct CnnForward {
+    const float *x;        // [.][cin][H][W]
+    const int32_t *idx;    // sample numbers, or null (0, 1, ...)
+    const float *norm;     // scale, shift, inverse scale, inverse shift: cin floats each
+    const uint16_t *w[3];  // as stored: [out][in][tap]
+    const float *b[3];
+    float *a1, *a2, *y, *xn, *dy;
+    const float *target;  // [.][cin][H][W]
+    double *loss;         // one partial per tile
+    float dscale;
+    int cin, H, W, tiles;
+};
+
+template <int CP, int MODE>
+__global__ __launch_bounds__(64 * kCnnWaves) void k_cnn_forward(CnnForward q)
+{
+    constexpr int NT = 64 * kCnnWaves;
+    using R3 = Region<3>;
+    using R2 = Region<2>;
+    using R1 = Region<1>;
+    using L1 = FirstLds<CP>;
+    using L2 = ConvLds<32>;
+    constexpr int XP = R3::N * L1::CS;                            // input: elements per part
+    constexpr int CS = L2::CS, P1 = R2::N * CS, P2 = R1::N * CS;  // hidden activations
+    __shared__ __attribute__((aligned(16))) uint16_t s_a1[3 * P1];
+    __shared__ __attribute__((aligned(16))) uint16_t s_xa[3 * (XP > P2 ? XP : P2)];  // input, then a2
+    __shared__ __attribute__((aligned(16))) uint16_t s_w1[32 * L1::WS];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w2[32 * L2::WS];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w3[4 * L2::WS];  // three outputs and a zero row
+    __shared__ float s_b[68];
+    __shared__ double s_red[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 31, hk = lane >> 5;
+    const int H = q.H, W = q.W, cin = q.cin;
+    const size_t HW = (size_t)H * W;
+    const int tiles_j = (W + kTW - 1) / kTW, per = tiles_j * ((H + kTH - 1) / kTH);
+    constexpr bool kNorm = MODE != kCnnRaw;
+    // a thread takes one pixel of the widened tile and every channel: one wrap,
+    // loads of consecutive pixels
+    static_assert(R3::N <= NT, "a thread per pixel");
+    const int xy = tid / R3::W, xx = tid - xy * R3::W;
+    const bool small = H < R3::H || W < R3::W;
+    int n, i0, j0;     // this tile: sample, origin
+    const float *xs;   // its input
+    size_t x_at = 0;   // the thread's pixel of its input
+    float xv[CP];
+    auto load_input = [&](int tile) {
+        n = tile / per;
+        const int r = tile - n * per, ti = r / tiles_j;
+        i0 = ti * kTH;
+        j0 = (r - ti * tiles_j) * kTW;
+        xs = q.x + (size_t)(q.idx ? q.idx[n] : n) * cin * HW;
+        if (tid < R3::N) {
+            x_at = (size_t)wrap_index(small, i0 + xy - 3, H) * W + wrap_index(small, j0 + xx - 3, W);
+#pragma unroll
+            for (int c = 0; c < CP; ++c)
+                xv[c] = xs[(size_t)min(c, cin - 1) * HW + x_at];
+        }
+    };
+    auto store_input = [&]() {
+        if (tid >= R3::N)
+            return;
+        const bool own = xy >= 3 && xy < 3 + kTH && xx >= 3 && xx < 3 + kTW && i0 + xy - 3 < H && j0 + xx - 3 < W;
+#pragma unroll
+        for (int c0 = 0; c0 < CP; c0 += 4) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = min(c0 + u, cin - 1);
+                v[u] = kNorm ? fmaf(xv[c0 + u], q.norm[c], q.norm[cin + c]) : xv[c0 + u];
+                if (MODE == kCnnTrain && own && c0 + u < cin)
+                    q.xn[((size_t)n * cin + c) * HW + x_at] = v[u];
+                v[u] = c0 + u < cin ? v[u] : 0.0f;
+            }
+            put_split4(s_xa, tid * L1::CS + c0, XP, v);
+        }
+    };
+    load_input(blockIdx.x);
+    {
+        WeightStage<NT, 32 * CP> w1;
+        WeightStage<NT, 32 * 32> w2;
+        WeightStage<NT, 3 * 32> w3;
+        w1.load(q.w[0], 32 * cin);
+        w2.load(q.w[1], 32 * 32);
+        w3.load(q.w[2], 3 * 32);
+        if (CP != 4 || cin < 4) {  // channels past cin
+            for (int e = tid; e < 32 * L1::WS; e += NT)
+                s_w1[e] = 0;
+            __syncthreads();
+        }
+        for (int e = tid; e < L2::WS; e += NT)
+            s_w3[3 * L2::WS + e] = 0;
+        if (tid < 67)
+            s_b[tid] = tid < 32 ? q.b[0][tid] : tid < 64 ? q.b[1][tid - 32] : q.b[2][tid - 64];
+        w1.store(32 * cin, [&](int row, int t, uint16_t v) {
+            const int o = row / cin, c = row - o * cin;
+            s_w1[o * L1::WS + t * L1::TS + c] = v;
+        });
+        w2.store(32 * 32, [&](int row, int t, uint16_t v) { s_w2[(row >> 5) * L2::WS + t * L2::TS + (row & 31)] = v; });
+        w3.store(3 * 32, [&](int row, int t, uint16_t v) { s_w3[(row >> 5) * L2::WS + t * L2::TS + (row & 31)] = v; });
+    }
+    store_input();
+
+    // layers 1 and 2: v = relu(acc + b) on region R, into LDS and (the tile's
+    // own pixels) memory
+    auto hidden = [&](const f32x16 &acc, const float *b, bool live, int s, int pix, uint16_t *lds, int parts,
+                      float *out) {
+        const int gi = i0 + 2 * s + (m >> 4), gj = j0 + (m & 15);
+        float *o = MODE != kCnnPredict && s < 4 && gi < H && gj < W
+                       ? out + (size_t)n * 32 * HW + (size_t)gi * W + gj
+                       : nullptr;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int ch = 8 * g + 4 * hk;
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                v[u] = fmaxf(acc[4 * g + u] + b[ch + u], 0.0f);
+            if (live)
+                put_split4(lds, pix * CS + ch, parts, v);
+            if (o)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    o[(size_t)(ch + u) * HW] = v[u];
+        }
+    };
+    for (int tile = blockIdx.x;;) {
+        __syncthreads();
+        for (int s = wv; s < R2::kSlabs; s += kCnnWaves) {
+            int ry, rx;
+            const bool live = R2::pixel(s, m, ry, rx);
+            const f32x16 acc =
+                conv_slab<CP, L1::CS, L1::TS, R3::W>(s_xa, XP, ry * R3::W + rx, s_w1 + m * L1::WS, hk);
+            hidden(acc, s_b, live, s, ry * R2::W + rx, s_a1, P1, q.a1);
+        }
+        __syncthreads();
+        for (int s = wv; s < R1::kSlabs; s += kCnnWaves) {
+            int ry, rx;
+            const bool live = R1::pixel(s, m, ry, rx);
+            const f32x16 acc =
+                conv_slab<32, CS, L2::TS, R2::W>(s_a1, P1, ry * R2::W + rx, s_w2 + m * L2::WS, hk);
+            hidden(acc, s_b + 32, live, s, ry * R1::W + rx, s_xa, P2, q.a2);
+        }
+        // layer 3's residual and target, and the next tile's input, arrive
+        // while the block waits and multiplies
+        const int gi = i0 + 2 * wv + (m >> 4), gj = j0 + (m & 15);
+        const bool mine = wv < 4 && hk == 0 && gi < H && gj < W;
+        const size_t at = mine ? (size_t)gi * W + gj : 0;
+        const int n_this = n, block_this = tile;
+        const float *xs_this = xs;
+        float xr[CP == 4 ? 4 : 3], tr[3];
+        if (wv < 4) {
+#pragma unroll
+            for (int o = 0; o < (CP == 4 ? 4 : 3); ++o)
+                xr[o] = xs_this[(size_t)min(o, cin - 1) * HW + at];
+            if (MODE == kCnnTrain)
+#pragma unroll
+                for (int o = 0; o < 3; ++o)
+                    tr[o] = q.target[((size_t)(q.idx ? q.idx[n] : n) * cin + o) * HW + at];
+        }
+        tile += gridDim.x;
+        const bool more = tile < q.tiles;
+        if (more)
+            load_input(tile);
+        __syncthreads();
+        double sum = 0.0;
+        if (wv < 4) {
+            int ry, rx;
+            Region<0>::pixel(wv, m, ry, rx);
+            const f32x16 acc =
+                conv_slab<32, CS, L2::TS, R1::W>(s_xa, P2, ry * R1::W + rx, s_w3 + min(m, 3) * L2::WS, hk);
+            if (mine) {
+#pragma unroll
+                for (int o = 0; o < 3; ++o) {
+                    float v = acc[o] + s_b[64 + o];
+                    v += kNorm ? fmaf(xr[o], q.norm[o], q.norm[cin + o]) : xr[o];
+                    if (MODE == kCnnRaw) {
+                        q.y[((size_t)n_this * 3 + o) * HW + at] = v;
+                    } else if (MODE == kCnnPredict) {
+                        q.y[((size_t)n_this * cin + o) * HW + at] = fmaf(v, q.norm[2 * cin + o], q.norm[3 * cin + o]);
+                    } else {
+                        const float d = v - fmaf(tr[o], q.norm[o], q.norm[cin + o]);
+                        q.dy[((size_t)n_this * 3 + o) * HW + at] = d * q.dscale;
+                        sum += (double)d * (double)d;
+                    }
+                }
+                if (MODE == kCnnPredict && cin > 3)
+                    q.y[((size_t)n_this * cin + 3) * HW + at] = xr[3];
+            }
+        }
+        if (MODE == kCnnTrain) {
+            sum = cwave_sum(sum);
+            if (lane == 0 && wv < 4)
+                s_red[wv] = sum;
+        }
+        if (MODE == kCnnTrain || more)
+            __syncthreads();
+        if (MODE == kCnnTrain && tid == 0)
+            q.loss[block_this] = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
+        if (!more)
+            break;
+        store_input();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Input gradients: dz2 = (a2 > 0) conv(dy, w3 flipped), dz1 = (a1 > 0)
+// conv(dz2, w2 flipped), one block per tile as the forward pass; dz2 and dz1
+// out for the weight gradients.  75 KB of LDS: two blocks a CU.  15 us for 512
+// tiles (25 us as a kernel per layer), about half of it the first loads.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(64 * kCnnWaves) void k_cnn_dgrad(const float *__restrict__ dy, const float *__restrict__ a1,
+                                                              const float *__restrict__ a2,
+                                                              const uint16_t *__restrict__ w2,
+                                                              const uint16_t *__restrict__ w3, float *__restrict__ dz2,
+                                                              float *__restrict__ dz1, int H, int W)
+{
+    constexpr int NT = 64 * kCnnWaves;
+    using R2 = Region<2>;
+    using R1 = Region<1>;
+    using L1 = ConvLds<4>;
+    using L2 = ConvLds<32>;
+    constexpr int P1 = R2::N * 4, CS = L2::CS, P2 = R1::N * CS;
+    __shared__ __attribute__((aligned(16))) uint16_t s_dy[3 * P1];
+    __shared__ __attribute__((aligned(16))) uint16_t s_dz[3 * P2];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w3[32 * L1::WS];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w2[32 * L2::WS];
+    const int n = blockIdx.z, i0 = blockIdx.y * kTH, j0 = blockIdx.x * kTW;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 31, hk = lane >> 5;
+    const size_t HW = (size_t)H * W;
+    const bool small = H < Region<3>::H || W < Region<3>::W;
+    // every load of the block first: dy on the widened tile, the weights, and
+    // the activations that mask a lane's pixel (dz2: slab wv of R1; dz1: the
+    // tile's own, waves 0..3, the same pixel)
+    static_assert(R1::kSlabs <= kCnnWaves, "a slab per wave");
+    float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (tid < R2::N) {
+        const int ry = tid / R2::W, rx = tid - ry * R2::W;
+        const size_t at = (size_t)wrap_index(small, i0 + ry - 2, H) * W + wrap_index(small, j0 + rx - 2, W);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            dv[c] = dy[((size_t)n * 3 + c) * HW + at];
+    }
+    WeightStage<NT, 32 * 32> sw2;
+    WeightStage<NT, 3 * 32> sw3;
+    sw2.load(w2, 32 * 32);
+    sw3.load(w3, 3 * 32);
+    int ry, rx;
+    const bool live = R1::pixel(min(wv, R1::kSlabs - 1), m, ry, rx);
+    const int i = i0 + ry - 1, j = j0 + rx - 1;
+    const size_t at = (size_t)wrap_index(small, i, H) * W + wrap_index(small, j, W);
+    const bool own = wv < 4 && i < H && j < W;
+    // the lane's 16 channels of pixel `at` of sample n
+    auto channel = [&](int r) { return ((size_t)n * 32 + 8 * (r >> 2) + 4 * hk + (r & 3)) * HW + at; };
+    float m2[16], m1[16];
+    if (wv < R1::kSlabs)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            m2[r] = a2[channel(r)];
+    if (wv < 4)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            m1[r] = a1[channel(r)];
+    if (tid < R2::N)
+        put_split4(s_dy, tid * 4, P1, dv);
+    for (int e = tid; e < 32 * 9; e += NT)  // the fourth channel's weights
+        s_w3[(e / 9) * L1::WS + (e % 9) * 4 + 3] = 0;
+    sw2.store(32 * 32, [&](int row, int t, uint16_t v) {  // row = c * 32 + o
+        s_w2[(row & 31) * L2::WS + (8 - t) * L2::TS + (row >> 5)] = v;
+    });
+    sw3.store(3 * 32, [&](int row, int t, uint16_t v) {
+        s_w3[(row & 31) * L1::WS + (8 - t) * L1::TS + (row >> 5)] = v;
+    });
+    __syncthreads();
+    if (wv < R1::kSlabs) {
+        const f32x16 acc = conv_slab<4, 4, L1::TS, R2::W>(s_dy, P1, ry * R2::W + rx, s_w3 + m * L1::WS, hk);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v[u] = m2[4 * g + u] > 0.0f ? acc[4 * g + u] : 0.0f;
+                if (own)
+                    dz2[channel(4 * g + u)] = v[u];
+            }
+            if (live)
+                put_split4(s_dz, (ry * R1::W + rx) * CS + 8 * g + 4 * hk, P2, v);
+        }
+    }
+    __syncthreads();
+    if (wv < 4) {
+        // the lane's pixel has its top-left tap at (ry - 1, rx - 1) of R1
+        const f32x16 acc =
+            conv_slab<32, CS, L2::TS, R1::W>(s_dz, P2, (ry - 1) * R1::W + rx - 1, s_w2 + m * L2::WS, hk);
+        if (own)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                dz1[channel(r)] = m1[r] > 0.0f ? acc[r] : 0.0f;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Weight and bias gradients of the three layers in one launch (blockIdx.y):
+// dw[o,c,tap] = sum_{n,i,j} dy[n,o,i,j] x[n,c,i+ky-1,j+kx-1], db[o] = sum
+// dy[n,o,i,j].  One block per (sample, 16 x 8 tile) writes its partial sums to
+// part[block][co ci 9 + co]; k_cnn_reduce adds the blocks in order in
+// float64.  Per block a matrix product on the matrix cores
+// (v_mfma_f32_16x16x4_f32): D[o][k] = sum_p A[o][p] B[p][k], p the tile's 128
+// pixels in groups of four neighbours (lane group q = l / 16 takes pixel 4 s +
+// q of step s), k = c * 9 + tap.  Each wave takes 16 columns k at a time for
+// every row o, so the A operands stay in registers over its columns and each
+// B operand read from LDS feeds both row blocks: with one 16 x 16 block at a
+// time, both operands read again for each, the products waited on LDS.  The
+// bias sums are per-row wave reductions of the dy tile in a fixed order.  For
+// 512 tiles 34 us (53 us as a launch per layer): the tiles' loads (60 MB) and
+// partials (23 MB) and the FP32 products (12 us) hardly overlap.
+//
+// 16x16x4 operand layout (lane l): A row l mod 16, k = l / 16; B column
+// l mod 16, k = l / 16; result register r holds row 4 (l / 16) + r of
+// column l mod 16.
+// ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWgWaves = 4;
 
-__global__ __launch_bounds__(64 * kWgWaves) void k_conv3x3_wgrad(const float *__restrict__ dy, int co_n,
-                                                                 const float *__restrict__ x, int ci_n, int H, int W,
-                                                                 float *__restrict__ part)
+struct WgradJobs {
+    const float *dy[3], *x[3];
+    float *part[3];
+    int co[3], ci[3];
+};
+
+// The 16 columns from 16 cb of row blocks rb0 .. rb0 + NRB - 1 (16 rows each).
+template <int NRB>
+__device__ __forceinline__ void wgrad_columns(const float *s_x, const float av[][kTW * kTH / 4], int rb0, int K, int cb,
+                                               int l16, int q, float *__restrict__ out)
 {
-    constexpr int NT = 64 * kWgWaves, NP = kTW * kTH, DS = NP + 1;  // threads, pixels, dy row stride
+    constexpr int NS = kTW * kTH / 4;
+    const int col = cb * 16 + l16;  // this lane's B column k
+    const int cc = col < K ? col / 9 : 0, t = col < K ? col - cc * 9 : 0, ty = t / 3, tx = t - ty * 3;
+    const float *pb = s_x + cc * kHalo + ty * kHW_ + tx + q;
+    float bv[NS];
+#pragma unroll
+    for (int s4 = 0; s4 < NS; ++s4)  // pixel 4 s4 + q: row s4 / 4, column 4 s4 mod 16 + q
+        bv[s4] = pb[(s4 >> 2) * kHW_ + ((4 * s4) & 15)];
+    __builtin_amdgcn_sched_barrier(0);  // every read in flight before the first product
+    f32x4 acc[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+        acc[rb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s4 = 0; s4 < NS; ++s4)
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rb][s4], bv[s4], acc[rb], 0, 0, 0);
+    if (col < K)
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                out[(size_t)((rb0 + rb) * 16 + 4 * q + r) * K + col] = acc[rb][r];
+}
+
+// 32 rows: columns 16 at a time, four waves' worth of them with both row
+// blocks each; of what is left, (column block, row block) pairs.
+__device__ __forceinline__ void wgrad_32rows(const float *s_x, const float *s_d, int DS, int K, int wv, int l16, int q,
+                                             float *__restrict__ out)
+{
+    constexpr int NS = kTW * kTH / 4;
+    float av[2][NS];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int s4 = 0; s4 < NS; ++s4)
+            av[rb][s4] = s_d[(rb * 16 + l16) * DS + q + 4 * s4];
+    const int ncb = (K + 15) >> 4, whole = ncb / kWgWaves * kWgWaves;
+    for (int cb = wv; cb < whole; cb += kWgWaves)
+        wgrad_columns<2>(s_x, av, 0, K, cb, l16, q, out);
+    for (int i = wv; i < 2 * (ncb - whole); i += kWgWaves) {
+        if (i & 1)
+            wgrad_columns<1>(s_x, av + 1, 1, K, whole + (i >> 1), l16, q, out);
+        else
+            wgrad_columns<1>(s_x, av, 0, K, whole + (i >> 1), l16, q, out);
+    }
+}
+
+// Three rows (the output layer): v_mfma_f32_4x4x1_16b_f32, a row o = l mod 4
+// and a column of its own per lane, one pixel per product: the sum over
+// pixels runs in the same order, one fma each, as in the 16x16x4 products
+// (equal bit for bit), at 4 rows of matrix work instead of 16.
+// 4x4x1 operand layout (lane l, block l / 4): A row l mod 4; B column l mod 4;
+// result register r holds row r of column l mod 4.
+__device__ __forceinline__ void wgrad_3rows(const float *s_x, const float *s_d, int DS, int K, int wv, int lane,
+                                            float *__restrict__ out)
+{
+    constexpr int NP = kTW * kTH;
+    for (int c0 = wv * 64; c0 < K; c0 += kWgWaves * 64) {
+        const int col = c0 + lane;
+        const int cc = col < K ? col / 9 : 0, t = col < K ? col - cc * 9 : 0, ty = t / 3, tx = t - ty * 3;
+        const float *pb = s_x + cc * kHalo + ty * kHW_ + tx, *pa = s_d + (lane & 3) * DS;
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        float av[2][16], bv[2][16];  // a tile row of operands, read while the last one multiplies
+        auto read = [&](int y) {
+#pragma unroll
+            for (int x = 0; x < 16; x += 4) {
+                const float4 v = *(const float4 *)(pa + 16 * y + x);
+                av[y & 1][x] = v.x, av[y & 1][x + 1] = v.y, av[y & 1][x + 2] = v.z, av[y & 1][x + 3] = v.w;
+            }
+#pragma unroll
+            for (int x = 0; x < 16; ++x)
+                bv[y & 1][x] = pb[y * kHW_ + x];
+        };
+        read(0);
+#pragma unroll
+        for (int y = 0; y < kTH; ++y) {
+            if (y + 1 < kTH)
+                read(y + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < 16; ++x)
+                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(av[y & 1][x], bv[y & 1][x], acc, 0, 0, 0);
+        }
+        if (col < K)
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+                out[(size_t)o * K + col] = acc[o];
+    }
+    static_assert(NP == 16 * kTH, "tile rows of 16 pixels");
+}
+
+__global__ __launch_bounds__(64 * kWgWaves) void k_cnn_wgrad(WgradJobs jobs, int H, int W)
+{
+    // dy rows of DS floats: lanes (l mod 16, l / 16) read 64 distinct banks
+    constexpr int NT = 64 * kWgWaves, NP = kTW * kTH, DS = NP + 4;
     __shared__ float s_x[kMaxC * kHalo];
-    __shared__ float s_d[kMaxC * DS];  // dy tile [o][p] (rows o >= co_n zero; pixels outside the field zero)
+    __shared__ __attribute__((aligned(16))) float s_d[kMaxC * DS];  // dy tile [o][p] (rows o >= co_n zero; pixels outside the field zero)
+    const int job = blockIdx.y;
+    const float *dy = jobs.dy[job], *x = jobs.x[job];
+    const int co_n = jobs.co[job], ci_n = jobs.ci[job];
     const int tiles_j = (W + kTW - 1) / kTW, tiles_i = (H + kTH - 1) / kTH;
     const int n = blockIdx.x / (tiles_i * tiles_j), tt = blockIdx.x - n * (tiles_i * tiles_j);
     const int ti = tt / tiles_j;
     const int i0 = ti * kTH, j0 = (tt - ti * tiles_j) * kTW;
     const size_t HW = (size_t)H * W;
-    stage_halo<NT, kMaxC>(x, n, ci_n, ci_n, H, W, i0, j0, s_x);
-    const float *dyn = dy + (size_t)n * co_n * HW;
-    stage<NT, kMaxC * NP>(
-        kMaxC * NP,
-        [&](int e) {
-            const int o = e / NP, pq = e - o * NP, gi = i0 + pq / kTW, gj = j0 + pq % kTW;
-            const bool ok = o < co_n && gi < H && gj < W;
-            const float v = dyn[ok ? (size_t)o * HW + (size_t)gi * W + gj : 0];
-            return ok ? v : 0.0f;
-        },
-        [&](int e, float v) { s_d[(e / NP) * DS + e % NP] = v; });
+    const int tid = threadIdx.x;
+    // every load of the block in flight before its first LDS write: a thread
+    // takes one pixel of the widened input tile and every channel, and one
+    // pixel of the dy tile and every second channel
+    {
+        constexpr int ND = kMaxC * NP / NT;
+        const bool small = H < kHH || W < kHW_;
+        const int ry = tid / kHW_, rx = tid - ry * kHW_;
+        const float *px = x + (size_t)n * ci_n * HW + (size_t)wrap_index(small, i0 + ry - 1, H) * W +
+                          wrap_index(small, j0 + rx - 1, W);
+        const int p = tid % NP, gi = i0 + p / kTW, gj = j0 + p % kTW;
+        const bool in = gi < H && gj < W;
+        const float *pd = dy + (size_t)n * co_n * HW + (in ? (size_t)gi * W + gj : 0);
+        float xv[kMaxC], dv[ND];
+        // NX channels of x, ND2 of this thread's dy rows (those past ci_n and
+        // co_n repeat the last one)
+        auto load = [&](auto nx, auto nd) {
+            if (tid < kHalo)
+#pragma unroll
+                for (int c = 0; c < decltype(nx)::value; ++c)
+                    xv[c] = px[(size_t)min(c, ci_n - 1) * HW];
+#pragma unroll
+            for (int u = 0; u < decltype(nd)::value; ++u)
+                dv[u] = pd[(size_t)min(tid / NP + u * (NT / NP), co_n - 1) * HW];
+        };
+        auto store = [&](auto nx, auto nd) {
+            if (tid < kHalo)
+#pragma unroll
+                for (int c = 0; c < decltype(nx)::value; ++c)
+                    s_x[c * kHalo + tid] = xv[c];
+#pragma unroll
+            for (int u = 0; u < decltype(nd)::value; ++u) {
+                const int o = tid / NP + u * (NT / NP);
+                s_d[o * DS + p] = in && o < co_n ? dv[u] : 0.0f;
+            }
+        };
+        using Few = IntTag<4>;
+        using AllX = IntTag<kMaxC>;
+        using AllD = IntTag<ND>;
+        if (co_n != 32) {  // three rows: four with the zero one
+            load(AllX{}, IntTag<4 / (NT / NP)>{});
+            store(AllX{}, IntTag<4 / (NT / NP)>{});
+        } else if (ci_n <= 4) {
+            load(Few{}, AllD{});
+            store(Few{}, AllD{});
+        } else {
+            load(AllX{}, AllD{});
+            store(AllX{}, AllD{});
+        }
+    }
     __syncthreads();
     const int K = ci_n * 9, nw = co_n * K;
-    float *out = part + (size_t)blockIdx.x * (nw + co_n);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int l16 = lane & 15, q = lane >> 4;
-    const int nrb = (co_n + 15) >> 4, ncb = (K + 15) >> 4;
-    for (int tb = wv; tb < nrb * ncb; tb += kWgWaves) {
-        const int rb = tb / ncb, cb = tb - rb * ncb;
-        const int col = cb * 16 + l16;  // this lane's B column k
-        const int cc = col < K ? col / 9 : 0, t = col < K ? col - cc * 9 : 0, ty = t / 3, tx = t - ty * 3;
-        const float *pa = s_d + (rb * 16 + l16) * DS + q;
-        const float *pb = s_x + cc * kHalo + ty * kHW_ + tx + q;
-        // all of the block's operands first, then the products
-        float av[NP / 4], bv[NP / 4];
+    float *out = jobs.part[job] + (size_t)blockIdx.x * (nw + co_n);
+    const int lane = tid & 63, wv = tid >> 6;
+    if (co_n == 32)
+        wgrad_32rows(s_x, s_d, DS, K, wv, lane & 15, lane >> 4, out);
+    else
+        wgrad_3rows(s_x, s_d, DS, K, wv, lane, out);
+    // bias: wave w takes rows w, w + 4, ... (all at once: one chain of lane
+    // exchanges, not eight); lane l adds pixels l and l + 64, then a fixed
+    // butterfly over the wave
+    constexpr int NB = kMaxC / kWgWaves;
+    float v[NB];
 #pragma unroll
-        for (int s4 = 0; s4 < NP / 4; ++s4) {  // pixel 4 s4 + q: row s4 / 4, column 4 s4 mod 16 + q
-            av[s4] = pa[4 * s4];
-            bv[s4] = pb[(s4 >> 2) * kHW_ + ((4 * s4) & 15)];
-        }
-        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int s4 = 0; s4 < NP / 4; ++s4)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s4], bv[s4], acc, 0, 0, 0);
-        if (col < K) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int o = rb * 16 + 4 * q + r;
-                if (o < co_n)
-                    out[(size_t)o * K + col] = acc[r];
-            }
-        }
+    for (int k = 0; k < NB; ++k) {
+        const int o = min(wv + k * kWgWaves, co_n - 1);
+        v[k] = s_d[o * DS + lane] + s_d[o * DS + lane + 64];
     }
-    // bias: wave w takes rows w, w + 4, ...; lane l adds pixels l and l + 64,
-    // then a fixed butterfly over the wave
-    for (int o = wv; o < co_n; o += kWgWaves) {
-        float v = s_d[o * DS + lane] + s_d[o * DS + lane + 64];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-            v += __shfl_xor(v, off, 64);
-        if (lane == 0)
-            out[nw + o] = v;
-    }
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            v[k] += __shfl_xor(v[k], off, 64);
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+        if (lane == 0 && wv + k * kWgWaves < co_n)
+            out[nw + wv + k * kWgWaves] = v[k];
 }
 
-// g[e] = the sum over blocks b of part[b][e] (float64); e < nw goes to the
-// weight gradient, e >= nw to the bias gradient.  A block takes kReduceCols
-// entries with 256 / kReduceCols threads each: thread slice s adds blocks s,
-// s + slices, ... in order, then the slices are added in order.
-constexpr int kReduceCols = 16, kReduceSlices = 256 / kReduceCols;
-
-__global__ __launch_bounds__(256) void k_grad_reduce(const float *__restrict__ part, int nblocks, int nw, int nb,
-                                                     float *__restrict__ gw, float *__restrict__ gb)
+// Adam (Kingma & Ba, algorithm 1) on element e of tensor q of the jobs, with
+// gradient gi.
+__device__ __forceinline__ void adam_element(const AdamJobs &j, int q, int64_t e, float gi, const AdamStep &a)
 {
+    float *theta = j.theta[q], *m = j.m[q], *v = j.v[q];
+    const float mi = a.beta1 * m[e] + (1.0f - a.beta1) * gi;
+    const float vi = a.beta2 * v[e] + (1.0f - a.beta2) * gi * gi;
+    m[e] = mi;
+    v[e] = vi;
+    const float th = theta[e] - a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
+    theta[e] = th;
+    if (j.bf16[q])
+        j.bf16[q][e] = float_to_bf16_rne(th);
+}
+
+// The sums over blocks of the three layers' gradient partials (float64, in
+// block order), and of the loss partials.  A block takes kReduceCols entries
+// of one layer with kReduceSlices threads each: thread slice s adds blocks s,
+// s + slices, ... in order, then the slices are added in order.  Entry e <
+// nw of layer k goes to the weight gradient, the others to the bias gradient,
+// each written to g[2 k], g[2 k + 1] of the jobs (ADAM: taken straight into
+// the Adam step of that tensor instead).  The last block adds the loss
+// partials: thread t partials t, t + 256, ... in order, then a fixed tree.
+// 32 columns: whole 128-byte lines of the partials, which blocks of 16
+// columns on different XCDs fetched twice.
+constexpr int kReduceCols = 32, kReduceSlices = 16, kReduceThreads = kReduceCols * kReduceSlices;
+
+struct ReduceJobs {
+    const float *part[3];
+    int nw[3], nb[3], first[3];  // weights, biases, first block
+    float *g[6];
+    const double *loss_part;
+    int nblocks, nloss;
+    int64_t count;  // values under the loss's mean
+    float *loss;
+};
+
+template <bool ADAM>
+__global__ __launch_bounds__(kReduceThreads) void k_cnn_reduce(ReduceJobs r, AdamJobs j, AdamStep a)
+{
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double s_red[4];
+        double s = 0.0;
+        if (threadIdx.x < 256)
+            for (int b = threadIdx.x; b < r.nloss; b += 256)
+                s += r.loss_part[b];
+        s = cwave_sum(s);
+        if ((threadIdx.x & 63) == 0 && threadIdx.x < 256)
+            s_red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            *r.loss = (float)((((s_red[0] + s_red[1]) + s_red[2]) + s_red[3]) / (double)r.count);
+        return;
+    }
     __shared__ double s_sum[kReduceSlices][kReduceCols];
+    const int k = (int)blockIdx.x >= r.first[2] ? 2 : (int)blockIdx.x >= r.first[1] ? 1 : 0;
+    const int nw = r.nw[k], total = nw + r.nb[k];
     const int col = threadIdx.x % kReduceCols, slice = threadIdx.x / kReduceCols;
-    const int e = blockIdx.x * kReduceCols + col;
-    const size_t stride = (size_t)(nw + nb);
+    const int e = ((int)blockIdx.x - r.first[k]) * kReduceCols + col;
     double sum = 0.0;
-    if (e < nw + nb) {
-        const float *p = part + e;
+    if (e < total) {
+        const float *p = r.part[k] + e;
         int b = slice;
-        constexpr int U = 8;  // loads in flight per thread; the additions stay in block order
-        for (; b + (U - 1) * kReduceSlices < nblocks; b += U * kReduceSlices) {
+        constexpr int U = 32;  // loads in flight per thread; the additions stay in block order
+        for (; b + (U - 1) * kReduceSlices < r.nblocks; b += U * kReduceSlices) {
             float v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                v[u] = p[(size_t)(b + u * kReduceSlices) * stride];
+                v[u] = p[(size_t)(b + u * kReduceSlices) * total];
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 sum += (double)v[u];
         }
-        for (; b < nblocks; b += kReduceSlices)
-            sum += (double)p[(size_t)b * stride];
+        for (; b < r.nblocks; b += kReduceSlices)
+            sum += (double)p[(size_t)b * total];
     }
     s_sum[slice][col] = sum;
     __syncthreads();
-    if (slice == 0 && e < nw + nb) {
+    if (slice == 0 && e < total) {
         double t = s_sum[0][col];
-        for (int k = 1; k < kReduceSlices; ++k)
-            t += s_sum[k][col];
-        if (e < nw)
-            gw[e] = (float)t;
+        for (int i = 1; i < kReduceSlices; ++i)
+            t += s_sum[i][col];
+        const int q = 2 * k + (e < nw ? 0 : 1), at = e < nw ? e : e - nw;
+        if (ADAM)
+            adam_element(j, q, at, (float)t, a);
         else
-            gb[e - nw] = (float)t;
+            r.g[q][at] = (float)t;
     }
 }
 
-// Mean squared error: dy = 2 (y - t) / count, per-block float64 partials of
-// sum (y - t)^2; k_mse_final adds them in order.
+// Mean squared error of given outputs: dy = 2 (y - t) / count, per-block
+// float64 partials of sum (y - t)^2, added in order by k_cnn_reduce.
 __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const float *__restrict__ t, int64_t count,
                                              float *__restrict__ dy, double *__restrict__ part)
 {
@@ -425,80 +927,21 @@ __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const 
         part[blockIdx.x] = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
 }
 
-// One block of 256: thread t adds partials t, t + 256, ... in order, then a
-// fixed tree over the threads.
-__global__ __launch_bounds__(256) void k_mse_final(const double *__restrict__ part, int nparts, int64_t count,
-                                                   float *__restrict__ loss)
-{
-    __shared__ double s_red[4];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nparts; b += 256)
-        s += part[b];
-    s = cwave_sum(s);
-    if ((threadIdx.x & 63) == 0)
-        s_red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        *loss = (float)((((s_red[0] + s_red[1]) + s_red[2]) + s_red[3]) / (double)count);
-}
-
-// bf16 weights -> the B layout of a convolution, out[o][tap][c] (c < cp, zero
-// for c >= ci), up to three tensors per launch (blockIdx.y).  tr = 0: the
-// convolution's own weights w[o][c][tap]; tr = 1: the input gradient of a
-// convolution whose weights are w[c][o][tap], out[o][tap][c] = w[c][o][8 -
-// tap].
-struct WidenJobs {
-    const uint16_t *w[3];
-    uint16_t *out[3];
-    int co[3], ci[3], cp[3], tr[3];
-};
-
-__global__ void k_widen(WidenJobs j)
-{
-    const int q = blockIdx.y, co = j.co[q], ci = j.ci[q], cp = j.cp[q];
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= co * 9 * cp)
-        return;
-    const int o = e / (9 * cp), r = e - o * (9 * cp), t = r / cp, c = r - t * cp;
-    uint16_t v = 0;
-    if (c < ci)
-        v = j.tr[q] ? j.w[q][(c * co + o) * 9 + (8 - t)] : j.w[q][(o * ci + c) * 9 + t];
-    j.out[q][e] = v;
-}
-
-// Adam (Kingma & Ba, algorithm 1) on float32 master tensors, up to kAdamMax
-// of them in one launch (blockIdx.y selects the tensor; every tensor has its
-// own moments and gradient); writes the bf16 copy where one is given.
-__global__ void k_adam_many(AdamJobs j, float lr, float beta1, float beta2, float eps, float bc1, float bc2)
+// Adam on float32 master tensors with given gradients, up to kAdamMax of them
+// in one launch (blockIdx.y selects the tensor); writes the bf16 copy where
+// one is given.
+__global__ void k_adam_many(AdamJobs j, AdamStep a)
 {
     const int q = blockIdx.y;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= j.count[q])
-        return;
-    float *theta = j.theta[q], *m = j.m[q], *v = j.v[q];
-    const float gi = j.g[q][e];
-    const float mi = beta1 * m[e] + (1.0f - beta1) * gi;
-    const float vi = beta2 * v[e] + (1.0f - beta2) * gi * gi;
-    m[e] = mi;
-    v[e] = vi;
-    const float th = theta[e] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-    theta[e] = th;
-    if (j.bf16[q])
-        j.bf16[q][e] = float_to_bf16_rne(th);
+    if (e < j.count[q])
+        adam_element(j, q, e, j.g[q][e], a);
 }
 
-hipError_t launch_adam_many(const AdamJobs &j, int n, float lr, float beta1, float beta2, float eps, int64_t t,
-                            hipStream_t s)
+static AdamStep adam_step(float lr, float beta1, float beta2, float eps, int64_t t)
 {
-    const float bc1 = (float)(1.0 - pow((double)beta1, (double)t));
-    const float bc2 = (float)(1.0 - pow((double)beta2, (double)t));
-    int64_t most = 0;
-    for (int q = 0; q < n; ++q)
-        most = std::max(most, j.count[q]);
-    if (n > 0 && most > 0)
-        hipLaunchKernelGGL(k_adam_many, dim3((unsigned)((most + 255) / 256), n), dim3(256), 0, s, j, lr, beta1, beta2,
-                           eps, bc1, bc2);
-    return hipGetLastError();
+    return AdamStep{lr, beta1, beta2, eps, (float)(1.0 - pow((double)beta1, (double)t)),
+                    (float)(1.0 - pow((double)beta2, (double)t))};
 }
 
 // x[n, c, p] = x[n, c, p] * scale[c] + shift[c] for c < nc (in place).
@@ -717,44 +1160,19 @@ static bool shape_ok(const lbm_cnn_shape *s)
     return s && s->n > 0 && s->h > 0 && s->w > 0 && s->hidden == 32 && s->cout == 3 && s->cin >= 3 &&
            s->cin <= 32 && (int64_t)s->h * s->w <= (1 << 26) && s->n <= 65535;
 }
-
-static int pad16(int c) { return c <= 16 ? 16 : 32; }
-
-// wb: bf16 weights in the B layout [co][9][pad16(ci)] (k_widen)
-static hipError_t conv(const float *x, int ci, const uint16_t *wb, int co, const float *b, const float *resid,
-                       int resid_c, const float *mask, int relu, float *y, int N, int H, int W, hipStream_t s)
-{
-    dim3 grd((W + kTW - 1) / kTW, (H + kTH - 1) / kTH, N);
-    if (pad16(ci) == 16)
-        hipLaunchKernelGGL(k_conv3x3<16>, grd, dim3(256), 0, s, x, ci, wb, co, b, resid, resid_c, mask, relu, y, H, W);
-    else
-        hipLaunchKernelGGL(k_conv3x3<32>, grd, dim3(256), 0, s, x, ci, wb, co, b, resid, resid_c, mask, relu, y, H, W);
-    return hipGetLastError();
-}
-
 static int conv_tiles(int H, int W) { return ((H + kTH - 1) / kTH) * ((W + kTW - 1) / kTW); }
 
-// Weight and bias gradients of one layer (co output, ci input channels):
-// per-tile partials, then their ordered sum.
-static hipError_t wgrad(const float *dy, int co, const float *x, int ci, int N, int H, int W, float *part, float *gw,
-                        float *gb, hipStream_t s)
+static int layer_total(const lbm_cnn_shape *s, int k)  // weights and biases of layer k
 {
-    const int blocks = N * conv_tiles(H, W);
-    hipLaunchKernelGGL(k_conv3x3_wgrad, dim3(blocks), dim3(64 * kWgWaves), 0, s, dy, co, x, ci, H, W, part);
-    const int total = co * ci * 9 + co;
-    hipLaunchKernelGGL(k_grad_reduce, dim3((total + kReduceCols - 1) / kReduceCols), dim3(256), 0, s, part, blocks,
-                       co * ci * 9, co, gw, gb);
-    return hipGetLastError();
+    return k == 0 ? 32 * s->cin * 9 + 32 : k == 1 ? 32 * 32 * 9 + 32 : 3 * 32 * 9 + 3;
 }
 
 struct CnnWs {
-    uint16_t *wb[3];   // the layers' weights in the convolutions' B layout [co][9][pad16(ci)]
-    uint16_t *wbt[3];  // the input-gradient convolutions' weights (layers 2 and 3)
-    double *part;      // loss partials
-    float *gpart;      // per-tile gradient partials
-    float *dy;         // dL/dy [n][cout][hw]
-    float *dz2;        // [n][hidden][hw]
-    float *dz1;        // [n][hidden][hw]
+    double *part;     // loss partials
+    float *gpart[3];  // per-tile gradient partials of each layer
+    float *dy;        // dL/dy [n][cout][hw]
+    float *dz2;       // [n][hidden][hw]
+    float *dz1;       // [n][hidden][hw]
     size_t total;
 };
 
@@ -762,8 +1180,8 @@ static const int kMseBlocks = 1024;
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Workspace: the weights in the B layout, loss partials and the backward
-// pass's intermediate gradients.  base == nullptr only measures the size.
+// Workspace of the backward pass: loss and gradient partials, intermediate
+// gradients.  base == nullptr only measures the size.
 static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
 {
     CnnWs L{};
@@ -774,15 +1192,10 @@ static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
         return base ? base + o : nullptr;
     };
     const int64_t hw = (int64_t)s->h * s->w;
-    const int co[3] = {s->hidden, s->hidden, s->cout}, ci[3] = {s->cin, s->hidden, s->hidden};
+    const size_t tiles = (size_t)s->n * conv_tiles(s->h, s->w);
+    L.part = (double *)take(std::max(tiles, (size_t)kMseBlocks) * sizeof(double));
     for (int k = 0; k < 3; ++k)
-        L.wb[k] = (uint16_t *)take((size_t)co[k] * 9 * pad16(ci[k]) * sizeof(uint16_t));
-    for (int k = 1; k < 3; ++k)
-        L.wbt[k] = (uint16_t *)take((size_t)ci[k] * 9 * pad16(co[k]) * sizeof(uint16_t));
-    L.part = (double *)take(kMseBlocks * sizeof(double));
-    // per-tile partials of the largest layer (hidden x max(hidden, cin) weights)
-    L.gpart = (float *)take((size_t)s->n * conv_tiles(s->h, s->w) *
-                            (size_t)(s->hidden * std::max(s->hidden, s->cin) * 9 + s->hidden) * sizeof(float));
+        L.gpart[k] = (float *)take(tiles * (size_t)layer_total(s, k) * sizeof(float));
     L.dy = (float *)take((size_t)s->n * s->cout * hw * sizeof(float));
     L.dz2 = (float *)take((size_t)s->n * s->hidden * hw * sizeof(float));
     L.dz1 = (float *)take((size_t)s->n * s->hidden * hw * sizeof(float));
@@ -790,26 +1203,112 @@ static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
     return L;
 }
 
-// forward: the three layers' convolutions; backward: the input-gradient
-// convolutions of layers 2 and 3 (their output channels are the layer's
-// inputs)
-static hipError_t widen(const lbm_cnn_shape *s, const lbm_cnn_params *p, const CnnWs &L, bool backward,
-                        hipStream_t st)
+static dim3 tile_grid(const lbm_cnn_shape *s)
 {
-    const int co[3] = {s->hidden, s->hidden, s->cout}, ci[3] = {s->cin, s->hidden, s->hidden};
-    WidenJobs j{};
-    int nj = 0, most = 0;
-    for (int k = backward ? 1 : 0; k < 3; ++k, ++nj) {
-        j.w[nj] = p->w[k];
-        j.out[nj] = backward ? L.wbt[k] : L.wb[k];
-        j.co[nj] = backward ? ci[k] : co[k];
-        j.ci[nj] = backward ? co[k] : ci[k];
-        j.cp[nj] = pad16(j.ci[nj]);
-        j.tr[nj] = backward;
-        most = std::max(most, j.co[nj] * 9 * j.cp[nj]);
+    return dim3((s->w + kTW - 1) / kTW, (s->h + kTH - 1) / kTH, s->n);
+}
+
+template <int MODE>
+static hipError_t forward(const lbm_cnn_shape *s, const lbm_cnn_params *p, CnnForward q, hipStream_t st)
+{
+    for (int k = 0; k < 3; ++k) {
+        q.w[k] = p->w[k];
+        q.b[k] = p->b[k];
     }
-    hipLaunchKernelGGL(k_widen, dim3((most + 255) / 256, nj), dim3(256), 0, st, j);
+    q.cin = s->cin;
+    q.H = s->h;
+    q.W = s->w;
+    q.tiles = s->n * conv_tiles(s->h, s->w);
+    // a block fills a CU's LDS: one per CU, each taking every 256th tile
+    const dim3 grd(std::min(q.tiles, 256)), blk(64 * kCnnWaves);
+    if (s->cin <= 4)
+        hipLaunchKernelGGL((k_cnn_forward<4, MODE>), grd, blk, 0, st, q);
+    else if (MODE == kCnnRaw && s->cin <= 16)
+        hipLaunchKernelGGL((k_cnn_forward<16, kCnnRaw>), grd, blk, 0, st, q);
+    else if (MODE == kCnnRaw)
+        hipLaunchKernelGGL((k_cnn_forward<32, kCnnRaw>), grd, blk, 0, st, q);
+    else
+        return hipErrorInvalidValue;  // the surrogate has three or four channels
     return hipGetLastError();
+}
+
+// From dy and the activations to the gradients (adam == nullptr: in g; else
+// taken into the Adam step) and the loss (from nloss partials).
+static hipError_t backward(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, const float *a1,
+                           const float *a2, const CnnWs &L, int nloss, float *loss, const lbm_cnn_grads *g,
+                           const AdamJobs *adam, const AdamStep &step, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_cnn_dgrad, tile_grid(s), dim3(64 * kCnnWaves), 0, st, L.dy, a1, a2, p->w[1], p->w[2], L.dz2,
+                       L.dz1, s->h, s->w);
+    // the layer with the most products first
+    const int order[3] = {1, 2, 0};
+    const float *dys[3] = {L.dz1, L.dz2, L.dy}, *xs[3] = {x, a1, a2};
+    const int co[3] = {32, 32, 3}, ci[3] = {s->cin, 32, 32};
+    WgradJobs w{};
+    ReduceJobs r{};
+    int first = 0;
+    for (int i = 0; i < 3; ++i) {
+        const int k = order[i];
+        w.dy[i] = dys[k];
+        w.x[i] = xs[k];
+        w.part[i] = L.gpart[k];
+        w.co[i] = co[k];
+        w.ci[i] = ci[k];
+        r.part[i] = L.gpart[i];
+        r.nw[i] = co[i] * ci[i] * 9;
+        r.nb[i] = co[i];
+        r.first[i] = first;
+        first += (layer_total(s, i) + kReduceCols - 1) / kReduceCols;
+        if (g) {
+            r.g[2 * i] = g->w[i];
+            r.g[2 * i + 1] = g->b[i];
+        }
+    }
+    r.nblocks = s->n * conv_tiles(s->h, s->w);
+    r.loss_part = L.part;
+    r.nloss = nloss;
+    r.count = (int64_t)s->n * s->cout * s->h * s->w;
+    r.loss = loss;
+    hipLaunchKernelGGL(k_cnn_wgrad, dim3(r.nblocks, 3), dim3(64 * kWgWaves), 0, st, w, s->h, s->w);
+    if (adam)
+        hipLaunchKernelGGL(k_cnn_reduce<true>, dim3(first + 1), dim3(kReduceThreads), 0, st, r, *adam, step);
+    else
+        hipLaunchKernelGGL(k_cnn_reduce<false>, dim3(first + 1), dim3(kReduceThreads), 0, st, r, AdamJobs{}, step);
+    return hipGetLastError();
+}
+
+hipError_t cnn_predict(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, const float *norm, float *y,
+                       hipStream_t st)
+{
+    CnnForward q{};
+    q.x = x;
+    q.norm = norm;
+    q.y = y;
+    return forward<kCnnPredict>(s, p, q, st);
+}
+
+hipError_t cnn_train(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, const float *target,
+                     const int32_t *idx, const float *norm, float *xn, float *a1, float *a2, void *ws,
+                     const AdamJobs &adam, float lr, float beta1, float beta2, float eps, int64_t t, float *loss,
+                     hipStream_t st)
+{
+    const CnnWs L = cnn_layout(s, (char *)ws);
+    CnnForward q{};
+    q.x = x;
+    q.target = target;
+    q.idx = idx;
+    q.norm = norm;
+    q.xn = xn;
+    q.a1 = a1;
+    q.a2 = a2;
+    q.dy = L.dy;
+    q.loss = L.part;
+    q.dscale = (float)(2.0 / (double)((int64_t)s->n * s->cout * s->h * s->w));
+    hipError_t e = forward<kCnnTrain>(s, p, q, st);
+    if (e != hipSuccess)
+        return e;
+    return backward(s, p, xn, a1, a2, L, s->n * conv_tiles(s->h, s->w), loss, nullptr, &adam,
+                    adam_step(lr, beta1, beta2, eps, t), st);
 }
 
 }  // namespace lbm
@@ -835,14 +1334,14 @@ int32_t lbm_cnn_forward(const lbm_cnn_shape *s, const lbm_cnn_params *p, const f
     for (int k = 0; k < 3; ++k)
         if (!p->w[k] || !p->b[k])
             return fail(LBM_EINVAL, "null weight or bias");
-    const CnnWs L = cnn_layout(s, (char *)ws);
-    if (ws_bytes < L.total)
+    if (ws_bytes < cnn_layout(s, nullptr).total)
         return fail(LBM_EINVAL, "workspace smaller than lbm_cnn_workspace_bytes()");
-    hipStream_t st = (hipStream_t)stream;
-    LBM_HIP_TRY(widen(s, p, L, false, st));
-    LBM_HIP_TRY(conv(x, s->cin, L.wb[0], 32, p->b[0], nullptr, 0, nullptr, 1, a1, s->n, s->h, s->w, st));
-    LBM_HIP_TRY(conv(a1, 32, L.wb[1], 32, p->b[1], nullptr, 0, nullptr, 1, a2, s->n, s->h, s->w, st));
-    LBM_HIP_TRY(conv(a2, 32, L.wb[2], 3, p->b[2], x, s->cin, nullptr, 0, y, s->n, s->h, s->w, st));
+    CnnForward q{};
+    q.x = x;
+    q.a1 = a1;
+    q.a2 = a2;
+    q.y = y;
+    LBM_HIP_TRY(forward<kCnnRaw>(s, p, q, (hipStream_t)stream));
     return LBM_OK;
 }
 
@@ -861,20 +1360,9 @@ int32_t lbm_cnn_backward(const lbm_cnn_shape *s, const lbm_cnn_params *p, const 
     if (ws_bytes < L.total)
         return fail(LBM_EINVAL, "workspace smaller than lbm_cnn_workspace_bytes()");
     hipStream_t st = (hipStream_t)stream;
-    const int N = s->n, H = s->h, W = s->w;
-    const int64_t hw = (int64_t)H * W, count = (int64_t)N * s->cout * hw;
-    LBM_HIP_TRY(widen(s, p, L, true, st));
+    const int64_t count = (int64_t)s->n * s->cout * s->h * s->w;
     hipLaunchKernelGGL(k_mse, dim3(kMseBlocks), dim3(256), 0, st, y, target, count, L.dy, L.part);
-    hipLaunchKernelGGL(k_mse_final, dim3(1), dim3(256), 0, st, L.part, kMseBlocks, count, loss);
-    // layer 3: y = x[:cout] + conv(a2, w2) + b2
-    LBM_HIP_TRY(wgrad(L.dy, s->cout, a2, 32, N, H, W, L.gpart, g->w[2], g->b[2], st));
-    LBM_HIP_TRY(conv(L.dy, s->cout, L.wbt[2], 32, nullptr, nullptr, 0, a2, 0, L.dz2, N, H, W, st));
-    // layer 2: a2 = relu(conv(a1, w1) + b1)
-    LBM_HIP_TRY(wgrad(L.dz2, 32, a1, 32, N, H, W, L.gpart, g->w[1], g->b[1], st));
-    LBM_HIP_TRY(conv(L.dz2, 32, L.wbt[1], 32, nullptr, nullptr, 0, a1, 0, L.dz1, N, H, W, st));
-    // layer 1: a1 = relu(conv(x, w0) + b0)
-    LBM_HIP_TRY(wgrad(L.dz1, 32, x, s->cin, N, H, W, L.gpart, g->w[0], g->b[0], st));
-    LBM_HIP_TRY(hipGetLastError());
+    LBM_HIP_TRY(backward(s, p, x, a1, a2, L, kMseBlocks, loss, g, nullptr, AdamStep{}, st));
     return LBM_OK;
 }
 
@@ -892,7 +1380,9 @@ int32_t lbm_cnn_adam(float *theta, float *m, float *v, const float *grad, int64_
     j.g[0] = grad;
     j.count[0] = count;
     j.bf16[0] = bf16_out;
-    LBM_HIP_TRY(launch_adam_many(j, 1, lr, beta1, beta2, eps, t, (hipStream_t)stream));
+    if (count > 0)
+        hipLaunchKernelGGL(k_adam_many, dim3((unsigned)((count + 255) / 256), 1), dim3(256), 0, (hipStream_t)stream, j,
+                           adam_step(lr, beta1, beta2, eps, t));
     LBM_HIP_TRY(hipGetLastError());
     return LBM_OK;
 }

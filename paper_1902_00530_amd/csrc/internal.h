@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "../../include/lbm.h"
+#include "../../include/lbm_cnn.h"
 #include "device.h"
 
 namespace lbm {
@@ -91,7 +92,7 @@ hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *sr
                           float *uy, double *scratch, double *result, hipStream_t s);
 // The surrogate form of lbm_sweep_batch (opts->surrogate set; arguments
 // validated as for a plain sweep).
-// Adam (as lbm_cnn_adam) on up to kAdamMax tensors in one launch.
+// The network's tensors (w1, b1, w2, b2, w3, b3) for an Adam step.
 constexpr int kAdamMax = 6;
 struct AdamJobs {
     float *theta[kAdamMax], *m[kAdamMax], *v[kAdamMax];
@@ -99,8 +100,20 @@ struct AdamJobs {
     int64_t count[kAdamMax];
     uint16_t *bf16[kAdamMax];  // bf16 copies of theta, or null
 };
-hipError_t launch_adam_many(const AdamJobs &j, int n, float lr, float beta1, float beta2, float eps, int64_t t,
-                            hipStream_t s);
+struct AdamStep {
+    float lr, beta1, beta2, eps, bc1, bc2;
+};
+// Physical fields y [n][cin][h][w] from x (norm: scale, shift, inverse scale
+// and inverse shift, cin floats each; at most four channels).
+hipError_t cnn_predict(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, const float *norm, float *y,
+                       hipStream_t st);
+// One Adam step (as lbm_cnn_adam) on samples idx of x and target (idx null:
+// the first n).  xn [n][cin][hw], a1, a2 [n][hidden][hw]: scratch; ws:
+// lbm_cnn_workspace_bytes.
+hipError_t cnn_train(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, const float *target,
+                     const int32_t *idx, const float *norm, float *xn, float *a1, float *a2, void *ws,
+                     const AdamJobs &adam, float lr, float beta1, float beta2, float eps, int64_t t, float *loss,
+                     hipStream_t st);
 
 int32_t surrogate_sweep(const lbm_params *ps, int n, const lbm_sweep_opts *o, void *const *bufs, void *ws,
                         size_t ws_bytes, hipStream_t st, lbm_obs *out);

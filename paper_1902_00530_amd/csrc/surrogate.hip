@@ -64,10 +64,10 @@ static ParamLayout param_layout(int cin)
     return P;
 }
 
-// Workspace: normalised inputs and targets, activations, the network's own
-// workspace, gradients, statistics, and the sweep's coarse fields.
+// Workspace: normalised inputs, activations, the network's own workspace,
+// statistics, and the sweep's coarse fields.
 struct WorkLayout {
-    size_t xn, tn, a1, a2, y, cnn, grad[6], mean, stdev, stats, loss, X, Y, F, err, mask, ptrs, act, total;
+    size_t xn, a1, a2, cnn, mean, stdev, stats, loss, X, Y, F, err, mask, ptrs, act, total;
     size_t cnn_bytes;
 };
 
@@ -77,7 +77,6 @@ static WorkLayout work_layout(const lbm_surrogate_desc &d)
     const int64_t hw = (int64_t)d.h * d.w, mb = d.max_batch;
     lbm_cnn_shape sh{(int32_t)mb, d.cin, kHidden, kOut, d.h, d.w};
     W.cnn_bytes = lbm_cnn_workspace_bytes(&sh);
-    const ParamLayout P = param_layout(d.cin);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
@@ -85,13 +84,9 @@ static WorkLayout work_layout(const lbm_surrogate_desc &d)
         return o;
     };
     W.xn = take(mb * d.cin * hw * sizeof(float));
-    W.tn = take(mb * kOut * hw * sizeof(float));
     W.a1 = take(mb * kHidden * hw * sizeof(float));
     W.a2 = take(mb * kHidden * hw * sizeof(float));
-    W.y = take(mb * kOut * hw * sizeof(float));
     W.cnn = take(W.cnn_bytes);
-    for (int k = 0; k < 6; ++k)
-        W.grad[k] = take(P.count[k] * sizeof(float));
     W.mean = take(d.cin * sizeof(double));
     W.stdev = take(d.cin * sizeof(double));
     W.stats = take(lbm_channel_stats_workspace_bytes(d.cin));
@@ -112,37 +107,6 @@ static bool desc_ok(const lbm_surrogate_desc *d)
     return d && d->cin >= 3 && d->cin <= 4 && d->h > 0 && d->w > 0 && (int64_t)d->h * d->w <= (1 << 20) &&
            d->coarse >= 1 && (d->coarse == 1 || d->coarse % 2 == 0) && d->k >= 1 && d->max_batch >= 1 &&
            d->max_batch <= 65535;
-}
-
-// out[i][c][p] = src[idx ? idx[i] : i][c][p] * scale[c] + shift[c] for
-// c < nc; src holds sc channels per sample, out nc.
-__global__ __launch_bounds__(256) void k_gather_affine(const float *__restrict__ src, int sc, const int32_t *__restrict__ idx,
-                                                       int n, int nc, int64_t hw, const float *__restrict__ scale,
-                                                       const float *__restrict__ shift, float *__restrict__ out)
-{
-    const int64_t total = (int64_t)n * nc * hw;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t p = e % hw;
-        const int c = (int)((e / hw) % nc);
-        const int i = (int)(e / (hw * nc));
-        const int64_t s = idx ? idx[i] : i;
-        out[e] = src[(s * sc + c) * hw + p] * scale[c] + shift[c];
-    }
-}
-
-// y[i][c] = yn[i][c] * inv_scale[c] + inv_shift[c] for the three fields, and
-// the constant channels copied from x.
-__global__ __launch_bounds__(256) void k_denorm_merge(const float *__restrict__ yn, const float *__restrict__ x, int n,
-                                                      int cin, int64_t hw, const float *__restrict__ inv_scale,
-                                                      const float *__restrict__ inv_shift, float *__restrict__ y)
-{
-    const int64_t total = (int64_t)n * cin * hw;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t p = e % hw;
-        const int c = (int)((e / hw) % cin);
-        const int64_t i = e / (hw * cin);
-        y[e] = c < kOut ? yn[(i * kOut + c) * hw + p] * inv_scale[c] + inv_shift[c] : x[e];
-    }
 }
 
 // Normalisation from the channel statistics: inputs to (x - mean) / std,
@@ -198,30 +162,11 @@ struct lbm_surrogate {
 
 namespace lbm {
 
-// Network output for the samples already normalised in W.xn.
-static int32_t forward_n(lbm_surrogate *s, int n)
+static int32_t predict_into(lbm_surrogate *s, const float *x, int n, float *y)
 {
     const lbm_cnn_shape sh = s->shape(n);
     const lbm_cnn_params p = s->cnn_params();
-    return lbm_cnn_forward(&sh, &p, (const float *)(s->ws + s->W.xn), (float *)(s->ws + s->W.a1),
-                           (float *)(s->ws + s->W.a2), (float *)(s->ws + s->W.y), s->ws + s->W.cnn, s->W.cnn_bytes,
-                           s->stream);
-}
-
-static int32_t predict_into(lbm_surrogate *s, const float *x, int n, float *y)
-{
-    const int64_t hw = (int64_t)s->d.h * s->d.w;
-    const float *nm = s->norm();
-    hipLaunchKernelGGL(k_gather_affine, dim3(grid_for((int64_t)n * s->d.cin * hw)), dim3(256), 0, s->stream, x,
-                       s->d.cin, (const int32_t *)nullptr, n, s->d.cin, hw, nm, nm + s->d.cin,
-                       (float *)(s->ws + s->W.xn));
-    LBM_HIP_TRY(hipGetLastError());
-    int32_t rc = forward_n(s, n);
-    if (rc)
-        return rc;
-    hipLaunchKernelGGL(k_denorm_merge, dim3(grid_for((int64_t)n * s->d.cin * hw)), dim3(256), 0, s->stream,
-                       (const float *)(s->ws + s->W.y), x, n, s->d.cin, hw, nm + 2 * s->d.cin, nm + 3 * s->d.cin, y);
-    LBM_HIP_TRY(hipGetLastError());
+    LBM_HIP_TRY(cnn_predict(&sh, &p, x, s->norm(), y, s->stream));
     return LBM_OK;
 }
 
@@ -544,44 +489,20 @@ int32_t lbm_surrogate_train_step(lbm_surrogate *s, const float *x, const float *
         return fail(LBM_EINVAL, "null samples, or n outside 1..max_batch");
     if (!(lr >= 0.0f))
         return fail(LBM_EINVAL, "lr must be >= 0");
-    const int64_t hw = (int64_t)s->d.h * s->d.w;
-    const int cin = s->d.cin;
-    const float *nm = s->norm();
-    float *xn = (float *)(s->ws + s->W.xn), *tn = (float *)(s->ws + s->W.tn);
-    hipLaunchKernelGGL(k_gather_affine, dim3(grid_for((int64_t)n * cin * hw)), dim3(256), 0, s->stream, x, cin, idx, n,
-                       cin, hw, nm, nm + cin, xn);
-    hipLaunchKernelGGL(k_gather_affine, dim3(grid_for((int64_t)n * kOut * hw)), dim3(256), 0, s->stream, target, cin,
-                       idx, n, kOut, hw, nm, nm + cin, tn);
-    LBM_HIP_TRY(hipGetLastError());
-    int32_t rc = forward_n(s, n);
-    if (rc)
-        return rc;
     const lbm_cnn_shape sh = s->shape(n);
     const lbm_cnn_params p = s->cnn_params();
-    lbm_cnn_grads g;
-    for (int k = 0; k < 3; ++k) {
-        g.w[k] = (float *)(s->ws + s->W.grad[2 * k]);
-        g.b[k] = (float *)(s->ws + s->W.grad[2 * k + 1]);
-    }
-    float *d_loss = (float *)(s->ws + s->W.loss);
-    rc = lbm_cnn_backward(&sh, &p, xn, (const float *)(s->ws + s->W.a1), (const float *)(s->ws + s->W.a2),
-                          (const float *)(s->ws + s->W.y), tn, &g, d_loss, s->ws + s->W.cnn, s->W.cnn_bytes,
-                          s->stream);
-    if (rc)
-        return rc;
-    s->t += 1;
     AdamJobs aj{};
     for (int k = 0; k < 6; ++k) {
         aj.theta[k] = (float *)(s->params + s->P.theta[k]);
         aj.m[k] = (float *)(s->params + s->P.m[k]);
         aj.v[k] = (float *)(s->params + s->P.v[k]);
-        aj.g[k] = (const float *)(s->ws + s->W.grad[k]);
         aj.count[k] = s->P.count[k];
         aj.bf16[k] = k % 2 == 0 ? (uint16_t *)(s->params + s->P.wb[k / 2]) : nullptr;
     }
-    LBM_HIP_TRY(launch_adam_many(aj, 6, lr, 0.9f, 0.999f, 1e-8f, s->t, s->stream));
-    if (loss)
-        LBM_HIP_TRY(hipMemcpyAsync(loss, d_loss, sizeof(float), hipMemcpyDeviceToDevice, s->stream));
+    LBM_HIP_TRY(cnn_train(&sh, &p, x, target, idx, s->norm(), (float *)(s->ws + s->W.xn), (float *)(s->ws + s->W.a1),
+                          (float *)(s->ws + s->W.a2), s->ws + s->W.cnn, aj, lr, 0.9f, 0.999f, 1e-8f, s->t + 1,
+                          loss ? loss : (float *)(s->ws + s->W.loss), s->stream));
+    s->t += 1;
     return LBM_OK;
 }
 
