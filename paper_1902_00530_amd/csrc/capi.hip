@@ -162,6 +162,14 @@ constexpr int64_t kGraphFirst = 512;
 // one-step chain wins; 16-bit MIPS on large lattices is VALU-bound already, so
 // the ring's extra work loses.  Pitched lattices and buffers of 2^30
 // populations or more (64-bit offsets) keep one step per launch.
+//
+// D2Q9 MIPS also has 64 x 24 tiles: their ring costs 24% more collisions in the
+// first step against 33% at 16 rows, and two blocks fit a CU either way.  They
+// win wherever the last round of 512 blocks is not much emptier: above 2^21
+// sites, and below where the rounds times the rows are fewer.  us per step,
+// 16 / 24 rows: F32 512^2 4.79 / 5.62; 1000x752 10.3 / 9.8; 1024^2 12.7 / 13.0;
+// 1448^2 23.8 / 22.8; 2048^2 49.1 / 46.8; 4096^2 157 / 152; BF16 1000x752 10.3 /
+// 10.1; 2896^2 88.3 / 83.8.
 int step2_rows(const lbm_params &p, const StepArgs &a)
 {
     const bool q9 = p.lattice == LBM_D2Q9, f32 = p.storage == LBM_F32;
@@ -170,7 +178,10 @@ int step2_rows(const lbm_params &p, const StepArgs &a)
         return 0;
     if (p.model == LBM_MIPS) {
         const int64_t lo = q9 ? 0 : 1 << 17, hi = f32 ? INT64_MAX : q9 ? 3 << 19 : 1 << 19;
-        return sites >= lo && sites < hi ? 16 : 0;
+        if (sites < lo || sites >= hi)
+            return 0;
+        auto rounds = [&](int rows) { return (((p.nx + 63) / 64) * (int64_t)((p.ny + rows - 1) / rows) + 511) / 512; };
+        return q9 && (sites >= 1 << 21 || 24 * rounds(24) < 16 * rounds(16)) ? 24 : 16;
     }
     if (sites < (f32 ? 3 << 14 : 1 << 17))
         return 0;

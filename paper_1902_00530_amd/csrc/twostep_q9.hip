@@ -5,8 +5,8 @@
 
 namespace lbm {
 
-template <int M, int S, int F, int TY>
-__global__ __launch_bounds__(256) void k_q9_step2_local(const typename Store<S>::T *__restrict__ src,
+template <int M, int S, int F, int TY, int NW>
+__global__ __launch_bounds__(64 * NW) void k_q9_step2_local(const typename Store<S>::T *__restrict__ src,
                                                         typename Store<S>::T *__restrict__ dst, StepArgs a,
                                                         StepClock *__restrict__ clk, int slot, int stream)
 {
@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void k_q9_step2_local(const typename Store<S>:
     row_group_tile(txi, tyi);
     if (tyi * TY >= a.ny)  // padding tile rows of the last group: the whole block
         return;
-    q9_step2_tile<M, S, F, TY, 4>(src, dst, a, txi * 64, tyi * TY, t, stream != 0, mid);
+    q9_step2_tile<M, S, F, TY, NW>(src, dst, a, txi * 64, tyi * TY, t, stream != 0, mid);
     clock_advance(clk, slot, t, 2);
 }
 
@@ -35,32 +35,33 @@ __global__ __launch_bounds__(64 * NW) void k_q9_step2_mips(const void *__restric
 }
 
 template <int S, int F>
-static hipError_t launch_q9_sf(const lbm_params &p, const StepArgs &a, int ty, const void *src, void *dst, StepClock *clk,
+static hipError_t launch_q9_sf(const lbm_params &p, const StepArgs &a, int rows, const void *src, void *dst, StepClock *clk,
                                int slot, hipStream_t s)
 {
     using T = typename Store<S>::T;
     const int stream = 2ull * 9ull * (uint64_t)a.plane * sizeof(T) > kStreamStateBytes;
-    const dim3 grd = row_group_grid((p.nx + 63) / 64, (p.ny + ty - 1) / ty);
+    const dim3 grd = row_group_grid((p.nx + 63) / 64, (p.ny + rows - 1) / rows);
     const T *in = (const T *)src;
     T *out = (T *)dst;
-    if (p.model == kMips) {
-        if (ty == 8)
-            hipLaunchKernelGGL((k_q9_step2_mips<S, F, 8, 4>), grd, dim3(256), 0, s, src, dst, a, clk, slot, stream);
+    // TY rows on NW waves
+    auto go = [&](auto ty, auto nw) {
+        constexpr int TY = decltype(ty)::value, NW = decltype(nw)::value;
+        const dim3 blk(64 * NW);
+        if (p.model == kMips)
+            hipLaunchKernelGGL((k_q9_step2_mips<S, F, TY, NW>), grd, blk, 0, s, src, dst, a, clk, slot, stream);
+        else if (p.model == kCil)
+            hipLaunchKernelGGL((k_q9_step2_local<kCil, S, F, TY, NW>), grd, blk, 0, s, in, out, a, clk, slot, stream);
         else
-            hipLaunchKernelGGL((k_q9_step2_mips<S, F, 16, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
-    } else if (p.model == kCil) {
-        if (ty == 8)
-            hipLaunchKernelGGL((k_q9_step2_local<kCil, S, F, 8>), grd, dim3(256), 0, s, in, out, a, clk, slot, stream);
-        else
-            hipLaunchKernelGGL((k_q9_step2_local<kCil, S, F, 16>), grd, dim3(256), 0, s, in, out, a, clk, slot, stream);
-    } else {
-        if (ty == 8)
-            hipLaunchKernelGGL((k_q9_step2_local<kPassive, S, F, 8>), grd, dim3(256), 0, s, in, out, a, clk, slot,
-                               stream);
-        else
-            hipLaunchKernelGGL((k_q9_step2_local<kPassive, S, F, 16>), grd, dim3(256), 0, s, in, out, a, clk, slot,
-                               stream);
-    }
+            hipLaunchKernelGGL((k_q9_step2_local<kPassive, S, F, TY, NW>), grd, blk, 0, s, in, out, a, clk, slot, stream);
+    };
+    if (rows == 8)
+        go(IntTag<8>{}, IntTag<4>{});
+    else if (p.model != kMips)
+        go(IntTag<16>{}, IntTag<4>{});
+    else if (rows == 16)
+        go(IntTag<16>{}, IntTag<8>{});
+    else
+        hipLaunchKernelGGL((k_q9_step2_mips<S, F, 24, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
     return hipGetLastError();
 }
 

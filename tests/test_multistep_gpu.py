@@ -174,3 +174,11 @@ def test_small_graph_runs_and_clock(L):
         a.step(1)
     b.step(12)
     assert torch.equal(_bits(a), _bits(b)) and a.step_index == b.step_index == 2 ** 32 + 9
+
+
+@pytest.mark.parametrize("nx,ny", [(1000, 751), (721, 745), (2049, 1025), (1000, 744)])
+@pytest.mark.parametrize("storage", [0, 1, 2])
+def test_q9_mips_24_rows(L, storage, nx, ny):
+    """Sizes the 64 x 24 tiles take: remainders of rows and columns, none, and
+    above the line of 2^21 sites."""
+    _compare(L, [4, 5], 9, "mips", storage, nx, ny)
