@@ -614,16 +614,19 @@ struct Layout {
 
 // Work-tile shapes: sites across, rows, steps per launch.  Shapes 0..4 serve
 // the local models (CIL, passive); MIPS takes the two-step shapes 3 and 4
-// (64 x 8, 64 x 16) and, for single steps, shape 6 (D2Q7, 64 x 4) or 5
-// (D2Q9, 64 x 16); each model's shapes are tuned among themselves.
+// (64 x 8, 64 x 16; D2Q9 also 7, 64 x 24) and, for single steps, shape 6
+// (D2Q7, 64 x 4) or 5 (D2Q9, 64 x 16); each model's shapes are tuned among
+// themselves.
 struct Shape {
     int tx, ty, steps;
 };
-constexpr int kNumShapes = 7;
+constexpr int kNumShapes = 8;
 constexpr int kNumTuned = 5;
-constexpr int kMipsShape = 5, kMipsShape4 = 6;
+constexpr int kMipsShape = 5, kMipsShape4 = 6, kMipsShape24 = 7;
 static const Shape kShapes[kNumShapes] = {{256, 1, 1}, {128, 2, 1}, {64, 4, 1}, {64, 8, 2},
-                                          {64, 16, 2}, {64, 16, 1}, {64, 4, 1}};
+                                          {64, 16, 2}, {64, 16, 1}, {64, 4, 1}, {64, 24, 2}};
+// the forms that tile_rows names (the others are the tuning's own)
+static bool named_shape(int k) { return k != kMipsShape24 && k <= kNumShapes; }
 constexpr int64_t kChunk = 1024;  // steps per captured graph, at most
 // the LDS-resident form (k_batch_resident): no tile list, every step of a
 // graph chunk in one launch; a tuning launch runs an odd number of steps, so
@@ -738,22 +741,20 @@ static std::vector<int> cache_groups(const lbm_params *ps, int n)
     return first;
 }
 
-// [begin, count) of each group's tiles in the list of shape k (build_tiles
-// lists each lattice's tiles contiguously, in lattice order)
-static std::vector<int64_t> group_ranges(const lbm_params *ps, const std::vector<int> &first, int k,
-                                         const MultiChoice &mc)
+// The lattice at which a group of them (consecutive lattices first .. last - 1)
+// is cut into two branches of about equal sites; last where there is only one.
+static int branch_cut(const lbm_params *ps, int first, int last)
 {
-    std::vector<int64_t> r;
-    int64_t off = 0;
-    for (size_t g = 0; g + 1 < first.size(); ++g) {
-        const int m = first[g + 1] - first[g];
-        const int64_t c = k == kMulti ? count_multi_tiles(ps + first[g], m, mc)
-                                      : count_tiles(ps + first[g], m, kShapes[k].tx, kShapes[k].ty);
-        r.push_back(off);
-        r.push_back(c);
-        off += c;
+    auto sites = [&](int l) { return (int64_t)ps[l].nx * ps[l].ny; };
+    int64_t total = 0, cum = 0;
+    for (int l = first; l < last; ++l)
+        total += sites(l);
+    for (int l = first; l + 1 < last; ++l) {
+        cum += sites(l);
+        if (2 * cum + sites(l + 1) > total)  // cutting after the next one is further from the middle
+            return l + 1;
     }
-    return r;
+    return last - 1 > first ? last - 1 : last;
 }
 
 static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
@@ -907,6 +908,9 @@ static hipError_t launch_batch_q9_f(int model, int shape, int64_t ntiles, const 
     if (model == kMips && sh.steps == 2 && sh.ty == 8)
         hipLaunchKernelGGL((k_batch_step2_mips<Mips2Q9<kF32>, F, 8, 4>), dim3((unsigned)ntiles), dim3(256), 0, s, tiles,
                            lats, ctrl, step_off, launch_off);
+    else if (model == kMips && sh.steps == 2 && sh.ty == 24)
+        hipLaunchKernelGGL((k_batch_step2_mips<Mips2Q9<kF32>, F, 24, 8>), dim3((unsigned)ntiles), dim3(512), 0, s, tiles,
+                           lats, ctrl, step_off, launch_off);
     else if (model == kMips && sh.steps == 2)
         hipLaunchKernelGGL((k_batch_step2_mips<Mips2Q9<kF32>, F, 16, 8>), dim3((unsigned)ntiles), dim3(512), 0, s, tiles,
                            lats, ctrl, step_off, launch_off);
@@ -953,7 +957,8 @@ static hipError_t launch_batch_step(int lattice, int model, int storage, int fla
 static std::mutex g_tune_mu;
 struct Tuned {
     int shape;  // the fastest form
-    int tile;   // the fastest among the forms that tile_rows names (all but kMulti)
+    int split;  // its lattice groups run as two branches
+    int tile;   // the fastest among the forms that tile_rows names (named_shape)
 };
 static std::map<std::string, Tuned> g_tuned;
 
@@ -976,14 +981,14 @@ struct GraphKey {
     const void *tiles_main, *tiles_one, *lat, *ctrl, *mt, *part, *colpart, *colmean, *results;
     int lattice, model, storage, flags, shape;
     int64_t ntiles_main, ntiles_one, nmt, n, n_samples, steps;
-    int sample, add, rev;
+    int sample, add, rev, split;
     int max_nx;                   // the column means' grid
     int multi_T, multi_tx, multi_ty;  // geometry of the several-steps form
     std::vector<int64_t> groups;  // tile ranges of the lattice groups
     auto tie() const
     {
         return std::tie(device, tiles_main, tiles_one, lat, ctrl, mt, part, colpart, colmean, results, lattice, model,
-                        storage, flags, shape, ntiles_main, ntiles_one, nmt, n, n_samples, steps, sample, add, rev,
+                        storage, flags, shape, ntiles_main, ntiles_one, nmt, n, n_samples, steps, sample, add, rev, split,
                         max_nx, multi_T, multi_tx, multi_ty, groups);
     }
     bool operator==(const GraphKey &o) const { return tie() == o.tie(); }
@@ -1191,19 +1196,19 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // this signature, else tuned below: every tuning launch reads the state
     // in the first buffer of each lattice and writes the second (free until
     // the sweep starts), so the state is unchanged.
-    int shape = -1;
+    int shape = -1, split = 0;
     const bool mips = ps[0].model == LBM_MIPS, q9 = ps[0].lattice == LBM_D2Q9;
     // the shapes this model and lattice may take (tuned among themselves):
     // MIPS 64x8 and 64x16 with two steps per launch and, D2Q7 only, 64x4
     // with one; the local models shapes 0..4
     std::vector<int> cands;
     if (mips)
-        cands = q9 ? std::vector<int>{3, 4} : std::vector<int>{kMipsShape4, 3, 4};
+        cands = q9 ? std::vector<int>{3, 4, kMipsShape24} : std::vector<int>{kMipsShape4, 3, 4};
     else
         for (int k = 0; k < kNumTuned; ++k)
             cands.push_back(k);
     for (int k : cands)
-        if (o->tile_rows == kShapes[k].ty)
+        if (named_shape(k) && o->tile_rows == kShapes[k].ty)
             shape = k;
     const bool resident_ok = resident_fits(ps, n);
     if (resident_ok)
@@ -1226,8 +1231,10 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     if (shape < 0) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(sig);
-        if (it != g_tuned.end())
+        if (it != g_tuned.end()) {
             shape = it->second.shape;
+            split = it->second.split;
+        }
     }
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws;
@@ -1333,14 +1340,68 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         return {up_err == hipSuccess ? d : nullptr, (int64_t)v.size()};
     };
     // one launch of `st` steps of form k over `count` tiles from `tl`
-    auto launch_form = [&](int k, int st, const BatchTile *tl, int64_t count, int step_off,
-                           int launch_off) -> hipError_t {
+    auto launch_form = [&](int k, int st, const BatchTile *tl, int64_t count, int step_off, int launch_off,
+                           hipStream_t on) -> hipError_t {
         if (k == kMulti)
             return launch_batch_multi(ps[0].lattice, ps[0].model, ps[0].storage, flags,
                                       multi_geom(ps[0].model, st, mc.tx, mc.ty), count, tl, d_lat, d_ctrl, step_off,
-                                      launch_off, s);
+                                      launch_off, on);
         return launch_batch_step(ps[0].lattice, ps[0].model, ps[0].storage, flags, k, count, tl, d_lat, d_ctrl,
-                                 step_off, launch_off, s);
+                                 step_off, launch_off, on);
+    };
+    // Two branches of a captured graph: a lattice group's launches are cut into
+    // two halves of its lattices, which need not wait for each other, so one
+    // half's launches fill the CUs that the other's last blocks and its next
+    // launch's first loads leave idle.  Taken where the tuning finds it faster:
+    // 48 lattices of 128^2 to 512^2 (50 us launches of three to five rounds of
+    // blocks) 2.42 -> 2.18 ms per 100 steps; more branches, and large lattices
+    // (five of 1024^2), gain nothing.
+    struct Fork {
+        hipStream_t side = nullptr;  // the second branch, while capturing
+        std::vector<hipEvent_t> events;
+        hipError_t after(hipStream_t from, hipStream_t to)  // to's next work waits for from's
+        {
+            hipEvent_t ev = nullptr;
+            hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+            if (e != hipSuccess)
+                return e;
+            events.push_back(ev);
+            e = hipEventRecord(ev, from);
+            return e == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e;
+        }
+        hipError_t open() { return side ? hipSuccess : hipStreamCreateWithFlags(&side, hipStreamNonBlocking); }
+        void close()  // once the capture has ended
+        {
+            for (hipEvent_t ev : events)
+                (void)hipEventDestroy(ev);
+            events.clear();
+            if (side)
+                (void)hipStreamDestroy(side);
+            side = nullptr;
+        }
+        ~Fork() { close(); }
+    } fork;
+    // run(stream, first, last) for lattices first .. last - 1 of a group, as two
+    // branches of the capture on s where fork is open
+    auto branches = [&](int first, int last, auto run) -> hipError_t {
+        const int cut = fork.side ? branch_cut(ps, first, last) : last;
+        if (cut == last)
+            return run(s, first, last);
+        hipError_t e = fork.after(s, fork.side);
+        if (e == hipSuccess)
+            e = run(s, first, cut);
+        if (e == hipSuccess)
+            e = run(fork.side, cut, last);
+        const hipError_t j = fork.after(fork.side, s);
+        return e != hipSuccess ? e : j;
+    };
+    // first tile of lattice l in the list of form k, and the count up to `last`
+    auto tile_range = [&](int k, int l, int last) -> std::pair<int64_t, int64_t> {
+        auto count = [&](int a, int b) {
+            return k == kMulti ? count_multi_tiles(ps + a, b - a, mc)
+                               : count_tiles(ps + a, b - a, kShapes[k].tx, kShapes[k].ty);
+        };
+        return {count(0, l), count(l, last)};
     };
     if (shape < 0) {
         float best = 1e30f, best_tile = 1e30f;
@@ -1362,7 +1423,15 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         // each shape: ten launches captured in a graph (as the sweep runs
         // them), replayed once to warm up and three times timed; the least
         // time per step wins
-        for (int k : cands) {
+        std::vector<std::pair<int, int>> forms;  // shape, split
+        for (int k : cands)
+            forms.push_back({k, 0});
+        for (int k : cands)  // the two-step shapes also as two branches
+            if (n > 1 && k < kNumShapes && kShapes[k].steps == 2 && o->use_graph)
+                forms.push_back({k, 1});
+        const std::vector<int> tfirst = cache_groups(ps, n);
+        for (const auto &form : forms) {
+            const int k = form.first;
             const bool res = k == kResident;
             std::pair<BatchTile *, int64_t> tl{nullptr, 0};
             if (!res) {
@@ -1370,6 +1439,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 if (!tl.first)
                     return hip_fail(up_err, "tile list upload");
             }
+            if (form.second)
+                LBM_HIP_TRY(fork.open());
             hipStream_t cap;
             LBM_HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
             hipGraph_t g = nullptr;
@@ -1379,14 +1450,19 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             if (res && e == hipSuccess)  // first buffer -> second buffer
                 e = launch_resident(ps[0].lattice, ps[0].model, ps[0].storage, flags, n, d_lat, d_ctrl, kResidentTuneSteps, s);
             // ten launches per lattice group, group after group, as the sweep runs them
-            const std::vector<int64_t> gr = res ? std::vector<int64_t>{} : group_ranges(ps, cache_groups(ps, n), k, mc);
             const int form_steps = res ? kResidentTuneSteps : k == kMulti ? mc.T : kShapes[k].steps;
-            for (size_t g = 0; 2 * g < gr.size(); ++g)
-                for (int r10 = 0; r10 < 10 && e == hipSuccess; ++r10)
-                    e = launch_form(k, form_steps, tl.first + gr[2 * g], gr[2 * g + 1], 0, 0);
+            for (size_t g = 0; g + 1 < tfirst.size() && !res && e == hipSuccess; ++g)
+                e = branches(tfirst[g], tfirst[g + 1], [&](hipStream_t on, int first, int last) -> hipError_t {
+                    const auto r = tile_range(k, first, last);
+                    hipError_t le = hipSuccess;
+                    for (int r10 = 0; r10 < 10 && le == hipSuccess; ++r10)
+                        le = launch_form(k, form_steps, tl.first + r.first, r.second, 0, 0, on);
+                    return le;
+                });
             s = saved;
             hipError_t ee = hipStreamEndCapture(cap, &g);
             (void)hipStreamDestroy(cap);
+            fork.close();
             if (e == hipSuccess)
                 e = ee;
             hipGraphExec_t ge = nullptr;
@@ -1416,14 +1492,15 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             if (ms < best) {
                 best = ms;
                 shape = k;
+                split = form.second;
             }
-            if (k != kMulti && ms < best_tile) {
+            if (named_shape(k) && !form.second && ms < best_tile) {
                 best_tile = ms;
                 tile = k;
             }
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[sig] = Tuned{shape, tile};
+        g_tuned[sig] = Tuned{shape, split, tile};
     }
     // the chosen list, and for a two-step shape the list of a one-step shape
     // (256x1; MIPS 64x4, D2Q9 MIPS 64x16) for the single steps that keep the launch count's
@@ -1452,10 +1529,15 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     LBM_HIP_TRY(hipGetLastError());
     // lattice groups that fit the Infinity Cache (one group when resident)
     const std::vector<int> gfirst = resident ? std::vector<int>{0, n} : cache_groups(ps, n);
-    const std::vector<int64_t> g_main = resident ? std::vector<int64_t>{0, 0} : group_ranges(ps, gfirst, shape, mc);
-    const std::vector<int64_t> g_one = two ? group_ranges(ps, gfirst, one_shape, mc) : g_main;
-    std::vector<int64_t> gkey(g_main);
-    gkey.insert(gkey.end(), g_one.begin(), g_one.end());
+    // the graph's launches depend on each lattice's tile ranges in the two lists
+    std::vector<int64_t> gkey;
+    for (size_t g = 0; g + 1 < gfirst.size() && !resident; ++g)
+        for (int l : {gfirst[g], split ? branch_cut(ps, gfirst[g], gfirst[g + 1]) : gfirst[g + 1]})
+            for (int k : {shape, one_shape}) {
+                const auto r = tile_range(k, l, gfirst[g + 1]);
+                gkey.push_back(r.first);
+                gkey.push_back(r.second);
+            }
 
     // the order of the lattice groups in this call, and in the next one
     const bool rev = !resident && gfirst.size() > 2 && rec.rev_next;
@@ -1501,17 +1583,25 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             const size_t g = rev ? gfirst.size() - 2 - k : k;
             int64_t launches = (steps + most - 1) / most;
             launches += (launches ^ steps) & 1;
-            int64_t done = 0;
-            for (int64_t i = 0; i < launches; ++i) {
-                const int st = (int)(steps / launches + (i < steps % launches ? 1 : 0));
-                const bool one = two && st == 1;
-                hipError_t e = launch_form(one ? one_shape : shape, st,
-                                           one ? one_list.first + g_one[2 * g] : main_list.first + g_main[2 * g],
-                                           one ? g_one[2 * g + 1] : g_main[2 * g + 1], (int)done, (int)i);
-                if (e != hipSuccess)
-                    return e;
-                done += st;
-            }
+            hipError_t e = branches(gfirst[g], gfirst[g + 1], [&](hipStream_t on, int first, int last) -> hipError_t {
+                const auto r_main = tile_range(shape, first, last);
+                const auto r_one = two ? tile_range(one_shape, first, last) : r_main;
+                int64_t done = 0;
+                for (int64_t i = 0; i < launches; ++i) {
+                    const int st = (int)(steps / launches + (i < steps % launches ? 1 : 0));
+                    const bool one = two && st == 1;
+                    const hipError_t le =
+                        launch_form(one ? one_shape : shape, st,
+                                    one ? one_list.first + r_one.first : main_list.first + r_main.first,
+                                    one ? r_one.second : r_main.second, (int)done, (int)i, on);
+                    if (le != hipSuccess)
+                        return le;
+                    done += st;
+                }
+                return hipSuccess;
+            });
+            if (e != hipSuccess)
+                return e;
             if (sample)
                 group_moments(g, steps);
         }
@@ -1553,12 +1643,14 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                            ps[0].storage, flags,
                            shape,
                            main_list.second, one_list.second, nmt, (int64_t)n, n_samples, steps, sample ? 1 : 0,
-                           o->drho ? 1 : 0, rev ? 1 : 0, max_nx, mc.T, mc.tx, mc.ty, gkey};
+                           o->drho ? 1 : 0, rev ? 1 : 0, split, max_nx, mc.T, mc.tx, mc.ty, gkey};
         if ((*ge = graph_cache_get(key)))
             return hipSuccess;
         hipGraph_t g;
         hipStream_t cap;
-        hipError_t e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
+        hipError_t e = split ? fork.open() : hipSuccess;
+        if (e == hipSuccess)
+            e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
         if (e != hipSuccess)
             return e;
         hipStream_t saved = s;
@@ -1568,6 +1660,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         hipError_t ee = be == hipSuccess ? hipStreamEndCapture(cap, &g) : be;
         s = saved;
         (void)hipStreamDestroy(cap);
+        fork.close();
         if (ce != hipSuccess)
             return ce;
         if (ee != hipSuccess)
