@@ -34,11 +34,10 @@
 #include <vector>
 
 #include "batch.h"
+#include "moments.h"
 #include "step2.h"
 
 namespace lbm {
-
-constexpr int kMomRows = 16;
 
 // ---------------------------------------------------------------------------
 // Step kernels over the tile list.  step_off: steps of this sample period
@@ -396,79 +395,46 @@ __global__ __launch_bounds__(64 * NW) void k_batch_step2_mips(const BatchTile *_
 // partial sums of M, Jx, Jy, sum |j|, nonfinite and per-column density sums
 // of the streamed populations; then per lattice the fixed-order totals.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double bwave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_down(v, off, 64);
-    return v;
-}
-
 // Q = 7 (triangular) or 9 (square lattice, F32 storage only).  Block b
 // takes moments tile base + b (a launch may cover one lattice group).
-template <int Q, int ST>
-__global__ __launch_bounds__(256) void k_batch_moments(const MomTile *__restrict__ mt, const LatDesc *__restrict__ lats,
-                                                       const Ctrl *__restrict__ ctrl, int node, int base,
-                                                       double *__restrict__ part, double *__restrict__ colpart)
+template <int Q, int ST, int R>
+__global__ __launch_bounds__(mom_lanes(R)) void k_batch_moments(const MomTile *__restrict__ mt,
+                                                             const LatDesc *__restrict__ lats,
+                                                             const Ctrl *__restrict__ ctrl, int node, int base,
+                                                             double *__restrict__ part, double *__restrict__ colpart)
 {
-    __shared__ double lds[4][5];
+    __shared__ MomLds<R> lds;
     const int tile = base + (int)blockIdx.x;
     const MomTile m = mt[tile];
     const LatDesc &L = lats[m.lat];
     const StepArgs a = L.a;
     const int par = (int)((ctrl->k0 + node) & 1);
     const uint32_t plane = (uint32_t)a.plane;
-    const int x = m.cx * 256 + threadIdx.x;
-    const int yb = m.cy * kMomRows;
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (x < a.nx) {
-        double col = 0.0;
-        const int ye = min(yb + kMomRows, a.ny);
-        for (int y = yb; y < ye; ++y) {
-            float f[Q];
-            bool finite = true;
-            float rho, jx, jy;
+    const void *buf = L.buf[par];
+    moments_tile<R, Q>(
+        lds, a.nx, a.ny, m.cx * kMomCols, m.cy * kMomRows,
+        [&](float *f, int x, int y) {
             if constexpr (Q == 7) {
-                const __amdgpu_buffer_rsrc_t src = buffer_rsrc(L.buf[par], (uint32_t)Planes<ST>::bytes(plane));
+                const __amdgpu_buffer_rsrc_t src = buffer_rsrc(buf, (uint32_t)Planes<ST>::bytes(plane));
                 const PullSources32 g = pull_sources32(a, x, y);
 #pragma unroll
                 for (int i = 0; i < 7; ++i)
                     f[i] = Planes<ST>::load(src, g.idx[i], 0u, i, plane, a);
-                site_moments(f, rho, jx, jy);
             } else {
-                const float *src = (const float *)L.buf[par];
                 const Q9Sources g = q9_sources(a, x, y);
 #pragma unroll
                 for (int i = 0; i < 9; ++i)
-                    f[i] = BufIO<float>::load(q9_plane_rsrc(src, i, plane), g.idx[i], 0u);
-                q9_moments(f, rho, jx, jy);
+                    f[i] = BufIO<float>::load(q9_plane_rsrc((const float *)buf, i, plane), g.idx[i], 0u);
             }
-#pragma unroll
-            for (int i = 0; i < Q; ++i)
-                finite = finite && isfinite(f[i]);
-            const double dx = jx, dy = jy;
-            acc[0] += (double)rho;
-            acc[1] += dx;
-            acc[2] += dy;
-            acc[3] += sqrt(dx * dx + dy * dy);
-            acc[4] += finite ? 0.0 : 1.0;
-            col += (double)rho;
-        }
-        colpart[L.col_off + (int64_t)m.cy * a.nx + x] = col;
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 5; ++k)
-        acc[k] = bwave_sum(acc[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < 5; ++k)
-            lds[w][k] = acc[k];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < 5; ++k)
-            part[(int64_t)tile * 5 + k] = ((lds[0][k] + lds[1][k]) + lds[2][k]) + lds[3][k];
+        },
+        [](const float *f, float &rho, float &jx, float &jy) {
+            if constexpr (Q == 7)
+                site_moments(f, rho, jx, jy);
+            else
+                q9_moments(f, rho, jx, jy);
+        },
+        [](int, int, float, float, float) {}, part + (int64_t)tile * kMomParts,
+        colpart + L.col_off + (int64_t)m.cy * a.nx + m.cx * kMomCols);
 }
 
 // Column means rho_y(x) of every lattice: one thread per column (grid y =
@@ -515,7 +481,7 @@ __global__ __launch_bounds__(256) void k_batch_final(const LatDesc *__restrict__
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-        v[k] = bwave_sum(v[k]);
+        v[k] = mom_wave_sum(v[k]);
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < 6; ++k)
@@ -530,7 +496,7 @@ __global__ __launch_bounds__(256) void k_batch_final(const LatDesc *__restrict__
         const double d = cm[x] - mean;
         q += d * d;
     }
-    q = bwave_sum(q);
+    q = mom_wave_sum(q);
     __shared__ double lq[4];
     if (lane == 0)
         lq[w] = q;
@@ -1557,15 +1523,19 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         const int base = gmt[g], cnt = gmt[g + 1] - gmt[g];
         if (cnt <= 0)
             return;
+        auto go = [&](auto q, auto st, auto rows) {
+            constexpr int R = decltype(rows)::value;
+            hipLaunchKernelGGL((k_batch_moments<decltype(q)::value, decltype(st)::value, R>), dim3((unsigned)cnt),
+                               dim3(mom_lanes(R)), 0, s, d_mt, d_lat, d_ctrl, (int)steps, base, d_part, d_colpart);
+        };
+        auto rows = [&](auto q, auto st) {
+            mom_few_tiles(cnt) ? go(q, st, IntTag<4>{}) : go(q, st, IntTag<kMomRows>{});
+            return hipSuccess;
+        };
         if (q9)
-            hipLaunchKernelGGL((k_batch_moments<9, kF32>), dim3((unsigned)cnt), dim3(256), 0, s, d_mt, d_lat, d_ctrl,
-                               (int)steps, base, d_part, d_colpart);
+            rows(IntTag<9>{}, IntTag<kF32>{});
         else
-            (void)with_storage(ps[0].storage, [&](auto st) {
-                hipLaunchKernelGGL((k_batch_moments<7, decltype(st)::value>), dim3((unsigned)cnt), dim3(256), 0, s,
-                                   d_mt, d_lat, d_ctrl, (int)steps, base, d_part, d_colpart);
-                return hipSuccess;
-            });
+            (void)with_storage(ps[0].storage, [&](auto st) { return rows(IntTag<7>{}, st); });
     };
     // `steps` steps, then the sample if asked, then the counter update
     auto enqueue = [&](int64_t steps, bool sample) -> hipError_t {

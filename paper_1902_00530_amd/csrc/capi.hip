@@ -358,12 +358,17 @@ int32_t lbm_moments(lbm_ctx *c, float *rho, float *ux, float *uy, lbm_obs *obs)
 {
     if (!c)
         return fail(LBM_ESTATE, "null context");
-    LBM_HIP_TRY(launch_moments(c->p, c->args, c->buf[c->cur], rho, ux, uy, c->d_scratch, c->d_result, c->stream));
-    if (!obs)
+    auto launch = [&](double *host) {
+        return launch_moments(c->p, c->args, c->buf[c->cur], rho, ux, uy, c->d_scratch, c->d_result, host, c->stream);
+    };
+    if (!obs) {
+        LBM_HIP_TRY(launch(nullptr));
         return LBM_OK;
+    }
+    HostResult host;
+    LBM_HIP_TRY(launch(host.ptr));
     double r[8];
-    LBM_HIP_TRY(hipMemcpyAsync(r, c->d_result, sizeof r, hipMemcpyDeviceToHost, c->stream));
-    LBM_HIP_TRY(hipStreamSynchronize(c->stream));
+    LBM_HIP_TRY(host.read(c->d_result, r, c->stream));
     finish_obs(c->p, r, c->step, obs);
     if (obs->nonfinite)
         return fail(LBM_ENONFINITE, "non-finite populations in the state");

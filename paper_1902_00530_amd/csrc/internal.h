@@ -86,10 +86,23 @@ hipError_t launch_add_density_q9(const lbm_params &p, const StepArgs &a, void *b
 
 // Moments and FP64 reductions.  scratch: device doubles of
 // moments_scratch_doubles(p); result: 8 device doubles
-// {M, Jx, Jy, sum |j|, nonfinite, mean_x rho_y, var_x rho_y, unused}.
+// {M, Jx, Jy, sum |j|, nonfinite, mean_x rho_y, var_x rho_y, unused}, also
+// written to host (HostResult::ptr) where it is not null.
 size_t moments_scratch_doubles(const lbm_params &p);
 hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *src, float *rho, float *ux,
-                          float *uy, double *scratch, double *result, hipStream_t s);
+                          float *uy, double *scratch, double *result, double *host, hipStream_t s);
+// Eight doubles of pinned host memory for one call (ptr null where there are
+// none left).
+struct HostResult {
+    double *ptr = nullptr;
+    int slot = -1;
+    HostResult();
+    ~HostResult();
+    HostResult(const HostResult &) = delete;
+    HostResult &operator=(const HostResult &) = delete;
+    // r[8] once the stream's work is done: from ptr, or copied from result
+    hipError_t read(const double *result, double *r, hipStream_t s);
+};
 // The surrogate form of lbm_sweep_batch (opts->surrogate set; arguments
 // validated as for a plain sweep).
 // The network's tensors (w1, b1, w2, b2, w3, b3) for an Adam step.

@@ -4,114 +4,86 @@
 // zeta and the banding measure (standard deviation over x of the y-averaged
 // density), section "Regime Categorisation in the phase diagram".
 //
-// Pass 1: each block covers 256 columns x kRowsPerBlock rows; lanes hold
-// FP64 sums, reduced across the wavefront with shuffles and across the block
-// through LDS, one partial per block; per-column density sums go to a
-// [row-block][nx] array.  Pass 2 sums each column over the row blocks (one
-// thread per column) and pass 3 (one block) adds the block partials and the
-// column means in a fixed order, so the result does not depend on
-// scheduling.
+// Pass 1 (k_moments): FP64 sums of tiles of 256 columns x 16 rows, one partial
+// per tile, and the tiles' column sums of the density in a [row-block][nx] array.
+// Pass 2 (k_column_means, left to pass 3 where the columns are few) sums each
+// column over the row blocks, and pass 3 (k_moments_final, one block) adds the
+// tile partials and the column means.  All in a fixed order, so the result does
+// not depend on scheduling.
+#include <mutex>
+
 #include "device_q9.h"
 #include "internal.h"
+#include "moments.h"
 
 namespace lbm {
 
-constexpr int kMomBX = 256;
-constexpr int kRowsPerBlock = 16;
-constexpr int kNPart = 5;  // M, Jx, Jy, sum|j|, nonfinite
-
-static int mom_grid_x(const lbm_params &p) { return (p.nx + kMomBX - 1) / kMomBX; }
-static int mom_grid_y(const lbm_params &p) { return (p.ny + kRowsPerBlock - 1) / kRowsPerBlock; }
+static int mom_grid_x(const lbm_params &p) { return (p.nx + kMomCols - 1) / kMomCols; }
+static int mom_grid_y(const lbm_params &p) { return (p.ny + kMomRows - 1) / kMomRows; }
 
 size_t moments_scratch_doubles(const lbm_params &p)
 {
     const size_t blocks = (size_t)mom_grid_x(p) * mom_grid_y(p);
-    return blocks * kNPart + (size_t)mom_grid_y(p) * p.nx + (size_t)p.nx;
+    return blocks * kMomParts + (size_t)mom_grid_y(p) * p.nx + (size_t)p.nx;
 }
 
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_down(v, off, 64);
-    return v;
-}
-
-// Block-wide sum of kNPart doubles, fixed order; result valid in thread 0.
-template <int N>
+// Block-wide sums of N doubles, fixed order; valid in every thread.
+template <int N, int WAVES>
 __device__ __forceinline__ void block_sum(double v[N], double (*lds)[N])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < N; ++k)
-        v[k] = wave_sum(v[k]);
+        v[k] = mom_wave_sum(v[k]);
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < N; ++k)
             lds[wave][k] = v[k];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int k = 0; k < N; ++k) {
-            double s = 0.0;
-            for (int w = 0; w < nw; ++w)
-                s += lds[w][k];
-            v[k] = s;
-        }
+    if (threadIdx.x < N) {
+        double s = lds[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w)
+            s += lds[w][threadIdx.x];
+        lds[0][threadIdx.x] = s;
     }
     __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        v[k] = lds[0][k];
 }
 
-// The streamed populations of site (x, y) and their rho, j and finiteness,
-// on the triangular (Q = 7) or the square (Q = 9) lattice.
-template <int S, int Q>
-__device__ __forceinline__ void gathered_moments(const typename Store<S>::T *src, const StepArgs &a, int x, int y,
-                                                 float &rho, float &jx, float &jy, bool &finite)
+// The triangular (Q = 7) or the square (Q = 9) lattice, R rows a lane.
+template <int S, int Q, int R>
+__global__ __launch_bounds__(mom_lanes(R)) void k_moments(const typename Store<S>::T *__restrict__ src, StepArgs a,
+                                                       float *__restrict__ rho_out, float *__restrict__ ux_out,
+                                                       float *__restrict__ uy_out, double *__restrict__ part,
+                                                       double *__restrict__ colpart)
 {
-    float f[Q];
-    if constexpr (Q == 7) {
-        const PullSources g_src = pull_sources(a, x, y);
+    __shared__ MomLds<R> lds;
+    const int x0 = blockIdx.x * kMomCols;
+    moments_tile<R, Q>(
+        lds, a.nx, a.ny, x0, blockIdx.y * kMomRows,
+        [&](float *f, int x, int y) {
+            if constexpr (Q == 7) {
+                const PullSources g = pull_sources(a, x, y);
 #pragma unroll
-        for (int i = 0; i < 7; ++i)
-            f[i] = Planes<S>::ld(src, g_src.idx[i], i, a.plane, a);
-        site_moments(f, rho, jx, jy);
-    } else {
-        const Q9Sources g_src = q9_sources(a, x, y);
+                for (int i = 0; i < 7; ++i)
+                    f[i] = Planes<S>::ld(src, g.idx[i], i, a.plane, a);
+            } else {
+                const Q9Sources g = q9_sources(a, x, y);
 #pragma unroll
-        for (int i = 0; i < 9; ++i)
-            f[i] = Store<S>::load(src, i * a.plane + g_src.idx[i], q9_wr(a, i));
-        q9_moments(f, rho, jx, jy);
-    }
-    finite = true;
-#pragma unroll
-    for (int i = 0; i < Q; ++i)
-        finite = finite && isfinite(f[i]);
-}
-
-template <int S, int Q>
-__global__ __launch_bounds__(kMomBX) void k_moments(const typename Store<S>::T *__restrict__ src, StepArgs a,
-                                                    float *__restrict__ rho_out, float *__restrict__ ux_out,
-                                                    float *__restrict__ uy_out, double *__restrict__ part,
-                                                    double *__restrict__ colpart)
-{
-    __shared__ double lds[kMomBX / 64][kNPart];
-    const int x = blockIdx.x * kMomBX + threadIdx.x;
-    const int yb = blockIdx.y * kRowsPerBlock;
-    double acc[kNPart] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    double col = 0.0;
-    if (x < a.nx) {
-        const int ye = min(yb + kRowsPerBlock, a.ny);
-        for (int y = yb; y < ye; ++y) {
-            float rho, jx, jy;
-            bool finite;
-            gathered_moments<S, Q>(src, a, x, y, rho, jx, jy, finite);
-            const double dr = rho, dx = jx, dy = jy;
-            acc[0] += dr;
-            acc[1] += dx;
-            acc[2] += dy;
-            acc[3] += sqrt(dx * dx + dy * dy);
-            acc[4] += finite ? 0.0 : 1.0;
-            col += dr;
+                for (int i = 0; i < 9; ++i)
+                    f[i] = Store<S>::load(src, i * a.plane + g.idx[i], q9_wr(a, i));
+            }
+        },
+        [](const float *f, float &rho, float &jx, float &jy) {
+            if constexpr (Q == 7)
+                site_moments(f, rho, jx, jy);
+            else
+                q9_moments(f, rho, jx, jy);
+        },
+        [&](int x, int y, float rho, float jx, float jy) {
             const int64_t o = (int64_t)y * a.nx + x;
             if (rho_out)
                 rho_out[o] = rho;
@@ -119,16 +91,8 @@ __global__ __launch_bounds__(kMomBX) void k_moments(const typename Store<S>::T *
                 ux_out[o] = rho != 0.0f ? jx / rho : 0.0f;
             if (uy_out)
                 uy_out[o] = rho != 0.0f ? jy / rho : 0.0f;
-        }
-        colpart[(int64_t)blockIdx.y * a.nx + x] = col;
-    }
-    block_sum<kNPart>(acc, lds);
-    if (threadIdx.x == 0) {
-        const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-#pragma unroll
-        for (int k = 0; k < kNPart; ++k)
-            part[b * kNPart + k] = acc[k];
-    }
+        },
+        part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kMomParts, colpart + (int64_t)blockIdx.y * a.nx + x0);
 }
 
 // Column means rho_y(x): one thread per column, row blocks in order.
@@ -145,85 +109,161 @@ __global__ __launch_bounds__(256) void k_column_means(const double *__restrict__
     colmean[x] = c / (double)ny;
 }
 
-// One block: fixed-order totals of the block partials and of the column
-// means, then the variance of the column means over x.
-__global__ __launch_bounds__(256) void k_moments_final(const double *__restrict__ part, int nblocks,
-                                                       const double *__restrict__ colmean, int nx,
-                                                       double *__restrict__ result)
+// One block: totals of the tile partials and of the column means in a fixed
+// order, then the variance of the column means over x; with `host`, the result
+// also goes there (host memory that the device can write).  OWN: the column
+// means are summed here, in registers (nx <= kFinLanes, and few enough partials
+// that one CU reads them in the time of a launch, kFinOwn).  1024^2: 11.0 us
+// with the write to the host, against 4.3 and 5.4 for two launches and 4.5 for a
+// copy; with its fields, lbm_moments 51.5 -> 38.3 us, 64^2 41.6 -> 29.0, 4000 x
+// 3000 151 -> 133.
+constexpr int kFinLanes = 1024;
+constexpr int64_t kFinOwn = 1 << 16;
+
+template <bool OWN>
+__global__ __launch_bounds__(kFinLanes) void k_moments_final(const double *__restrict__ part, int nblocks,
+                                                             const double *__restrict__ col, int nrowblocks, int nx,
+                                                             int ny, double *__restrict__ result, double *host)
 {
-    __shared__ double lds[4][kNPart + 1];
-    double v[kNPart + 1] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x)
+    __shared__ double lds[kFinLanes / 64][kMomParts + 1];
+    const int tid = threadIdx.x;
+    double v[kMomParts + 1] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, own = 0.0;
+    for (int b = tid; b < nblocks; b += kFinLanes)
 #pragma unroll
-        for (int k = 0; k < kNPart; ++k)
-            v[k] += part[(int64_t)b * kNPart + k];
-    for (int x = threadIdx.x; x < nx; x += blockDim.x)
-        v[kNPart] += colmean[x];
-    block_sum<kNPart + 1>(v, lds);
-    __shared__ double mean_s;
-    if (threadIdx.x == 0)
-        mean_s = v[kNPart] / (double)nx;
-    __syncthreads();
-    const double mean = mean_s;
-    double q[1] = {0.0};
-    for (int x = threadIdx.x; x < nx; x += blockDim.x) {
-        const double d = colmean[x] - mean;
-        q[0] += d * d;
+        for (int k = 0; k < kMomParts; ++k)
+            v[k] += part[(int64_t)b * kMomParts + k];
+    if (OWN) {
+        if (tid < nx) {
+#pragma unroll 32
+            for (int r = 0; r < nrowblocks; ++r)
+                own += col[(int64_t)r * nx + tid];
+            own /= (double)ny;
+            v[kMomParts] = own;
+        }
+    } else {
+#pragma unroll 4
+        for (int x = tid; x < nx; x += kFinLanes)
+            v[kMomParts] += col[x];
     }
-    __shared__ double lds1[4][1];
-    block_sum<1>(q, lds1);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < kNPart; ++k)
-            result[k] = v[k];
-        result[5] = mean;
-        result[6] = q[0] / (double)nx;
-        result[7] = 0.0;
+    block_sum<kMomParts + 1, kFinLanes / 64>(v, lds);
+    const double mean = v[kMomParts] / (double)nx;
+    double q[1] = {0.0};
+    if (OWN) {
+        if (tid < nx)
+            q[0] = (own - mean) * (own - mean);
+    } else {
+#pragma unroll 4
+        for (int x = tid; x < nx; x += kFinLanes) {
+            const double d = col[x] - mean;
+            q[0] += d * d;
+        }
+    }
+    __shared__ double lds1[kFinLanes / 64][1];
+    block_sum<1, kFinLanes / 64>(q, lds1);
+    if (tid < 8) {
+        double r = tid == 5 ? mean : tid == 6 ? q[0] / (double)nx : 0.0;
+#pragma unroll
+        for (int k = 0; k < kMomParts; ++k)
+            r = tid == k ? v[k] : r;
+        result[tid] = r;
+        if (host)
+            host[tid] = r;
     }
 }
 
 hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *src, float *rho, float *ux,
-                          float *uy, double *scratch, double *result, hipStream_t s)
+                          float *uy, double *scratch, double *result, double *host, hipStream_t s)
 {
     const int gx = mom_grid_x(p), gy = mom_grid_y(p);
     double *part = scratch;
-    double *colpart = part + (size_t)gx * gy * kNPart;
+    double *colpart = part + (size_t)gx * gy * kMomParts;
     double *colmean = colpart + (size_t)gy * p.nx;
-    dim3 grd(gx, gy), blk(kMomBX);
     const bool q9 = p.lattice == LBM_D2Q9;
-    switch (p.storage) {
-    case kF32:
-        if (q9)
-            hipLaunchKernelGGL((k_moments<kF32, 9>), grd, blk, 0, s, (const float *)src, a, rho, ux, uy, part, colpart);
-        else
-            hipLaunchKernelGGL((k_moments<kF32, 7>), grd, blk, 0, s, (const float *)src, a, rho, ux, uy, part, colpart);
-        break;
-    case kBf16Dev:
-        if (q9)
-            hipLaunchKernelGGL((k_moments<kBf16Dev, 9>), grd, blk, 0, s, (const uint16_t *)src, a, rho, ux, uy, part,
-                               colpart);
-        else
-            hipLaunchKernelGGL((k_moments<kBf16Dev, 7>), grd, blk, 0, s, (const uint16_t *)src, a, rho, ux, uy, part,
-                               colpart);
-        break;
-    case kF16Dev:
-        if (q9)
-            hipLaunchKernelGGL((k_moments<kF16Dev, 9>), grd, blk, 0, s, (const _Float16 *)src, a, rho, ux, uy, part,
-                               colpart);
-        else
-            hipLaunchKernelGGL((k_moments<kF16Dev, 7>), grd, blk, 0, s, (const _Float16 *)src, a, rho, ux, uy, part,
-                               colpart);
-        break;
-    case kBf16R32:
-        if (q9)
+    const hipError_t e = with_storage(p.storage, [&](auto st) {
+        constexpr int S = decltype(st)::value;
+        using T = typename Store<S>::T;
+        auto go = [&](auto rows) {
+            constexpr int R = decltype(rows)::value;
+            const dim3 grd(gx, gy), blk(mom_lanes(R));
+            if (!q9) {
+                hipLaunchKernelGGL((k_moments<S, 7, R>), grd, blk, 0, s, (const T *)src, a, rho, ux, uy, part, colpart);
+                return hipSuccess;
+            }
+            if constexpr (S != kBf16R32) {
+                hipLaunchKernelGGL((k_moments<S, 9, R>), grd, blk, 0, s, (const T *)src, a, rho, ux, uy, part, colpart);
+                return hipSuccess;
+            }
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_moments<kBf16R32, 7>), grd, blk, 0, s, (const uint16_t *)src, a, rho, ux, uy, part,
-                           colpart);
-        break;
-    default: return hipErrorInvalidValue;
+        };
+        return mom_few_tiles((int64_t)gx * gy) ? go(IntTag<4>{}) : go(IntTag<kMomRows>{});
+    });
+    if (e != hipSuccess)
+        return e;
+    if (p.nx <= kFinLanes && (int64_t)gy * p.nx <= kFinOwn) {
+        hipLaunchKernelGGL(k_moments_final<true>, dim3(1), dim3(kFinLanes), 0, s, part, gx * gy, colpart, gy, p.nx, p.ny,
+                           result, host);
+    } else {
+        hipLaunchKernelGGL(k_column_means, dim3((p.nx + 255) / 256), dim3(256), 0, s, colpart, gy, colmean, p.nx, p.ny);
+        hipLaunchKernelGGL(k_moments_final<false>, dim3(1), dim3(kFinLanes), 0, s, part, gx * gy, colmean, gy, p.nx, p.ny,
+                           result, host);
     }
-    hipLaunchKernelGGL(k_column_means, dim3((p.nx + 255) / 256), dim3(256), 0, s, colpart, gy, colmean, p.nx, p.ny);
-    hipLaunchKernelGGL(k_moments_final, dim3(1), dim3(256), 0, s, part, gx * gy, colmean, p.nx, result);
     return hipGetLastError();
+}
+
+// Host memory for results that a kernel writes straight to the host: one page
+// of 64 slots of eight doubles, pinned on first use and kept; a slot belongs to
+// one call at a time.  Against a copy of the 64 bytes into pageable memory this
+// takes a device-to-host copy out of every sample.
+constexpr int kHostSlots = 64;
+static std::mutex g_slot_mu;
+static double *g_slot_page;
+static bool g_slot_failed, g_slot_used[kHostSlots];
+
+HostResult::HostResult()
+{
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    if (!g_slot_page && !g_slot_failed) {
+        // another thread may be capturing a graph: this one's allocation has no
+        // part in it
+        void *p = nullptr;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        g_slot_failed = hipHostMalloc(&p, kHostSlots * 8 * sizeof(double), hipHostMallocPortable) != hipSuccess;
+        if (swapped)
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (g_slot_failed)
+            (void)hipGetLastError();
+        else
+            g_slot_page = (double *)p;
+    }
+    for (int k = 0; k < kHostSlots && g_slot_page && slot < 0; ++k)
+        if (!g_slot_used[k]) {
+            g_slot_used[k] = true;
+            slot = k;
+            ptr = g_slot_page + 8 * k;
+        }
+}
+
+HostResult::~HostResult()
+{
+    if (slot < 0)
+        return;
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    g_slot_used[slot] = false;
+}
+
+hipError_t HostResult::read(const double *result, double *r, hipStream_t s)
+{
+    hipError_t e = ptr ? hipSuccess : hipMemcpyAsync(r, result, 8 * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        slot = -1;  // the kernel may still write it: not given back
+        return e;
+    }
+    for (int k = 0; k < 8 && ptr; ++k)
+        r[k] = ((const volatile double *)ptr)[k];
+    return hipSuccess;
 }
 
 void finish_obs(const lbm_params &p, const double *r, int64_t step, lbm_obs *o)

@@ -69,7 +69,7 @@ extern "C" int32_t lbm_observe(const lbm_params *p, const void *f, int64_t pitch
     hipStream_t s = (hipStream_t)stream;
     const StepArgs a = make_step_args(*p, pitch);
     double *result = sc + (need - 8);
-    LBM_HIP_TRY(launch_moments(*p, a, f, rho, ux, uy, sc, result, s));
+    LBM_HIP_TRY(launch_moments(*p, a, f, rho, ux, uy, sc, result, nullptr, s));
     if (!obs)
         return LBM_OK;
     double r[8];
