@@ -624,8 +624,8 @@ static int64_t count_tiles(const lbm_params *ps, int n, int tx, int ty)
 // The several-steps form of this batch, T = 0 where it has none: batches of up
 // to 2^20 sites (larger ones fill the GPU with the tile forms; the tuning times
 // it against them).  Twelve 90 x 30 MIPS lattices 3.25 (resident in LDS, 12 of
-// 256 CUs) -> 2.25 us a step, fifty 180 x 60 CIL lattices 6.1 (two steps per
-// launch, 64 x 8 tiles) -> 5.5.
+// 256 CUs) -> 2.14 us a step, fifty 180 x 60 CIL lattices 6.1 (two steps per
+// launch, 64 x 8 tiles) -> 5.3.
 constexpr int64_t kMultiBatchSites = 1 << 20;
 
 static MultiChoice multi_for_batch(const lbm_params *ps, int n)
