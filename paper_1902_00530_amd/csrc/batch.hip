@@ -1061,9 +1061,10 @@ static bool same_desc(const LatDesc &x, const LatDesc &y)
 static int32_t read_samples(const lbm_params *ps, int n, int64_t n_samples, const double *d_results, hipStream_t s,
                             lbm_obs *out)
 {
-    std::vector<double> res((size_t)n * n_samples * 8);
-    LBM_HIP_TRY(hipMemcpyAsync(res.data(), d_results, sizeof(double) * res.size(), hipMemcpyDeviceToHost, s));
-    LBM_HIP_TRY(hipStreamSynchronize(s));
+    const size_t results = (size_t)n * n_samples;
+    std::vector<double> res(results * 8);
+    HostResult host(results);
+    LBM_HIP_TRY(host.fetch(d_results, res.data(), results, s));
     bool bad = false;
     for (int l = 0; l < n; ++l)
         for (int64_t k = 0; k < n_samples; ++k) {

@@ -365,10 +365,10 @@ int32_t lbm_moments(lbm_ctx *c, float *rho, float *ux, float *uy, lbm_obs *obs)
         LBM_HIP_TRY(launch(nullptr));
         return LBM_OK;
     }
-    HostResult host;
+    HostResult host(1);
     LBM_HIP_TRY(launch(host.ptr));
     double r[8];
-    LBM_HIP_TRY(host.read(c->d_result, r, c->stream));
+    LBM_HIP_TRY(host.read(c->d_result, r, 1, c->stream));
     finish_obs(c->p, r, c->step, obs);
     if (obs->nonfinite)
         return fail(LBM_ENONFINITE, "non-finite populations in the state");

@@ -91,20 +91,21 @@ hipError_t launch_add_density_q9(const lbm_params &p, const StepArgs &a, void *b
 size_t moments_scratch_doubles(const lbm_params &p);
 hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *src, float *rho, float *ux,
                           float *uy, double *scratch, double *result, double *host, hipStream_t s);
-// Eight doubles of pinned host memory for one call (ptr null where there are
-// none left).
+// Pinned host memory for `results` results of eight doubles, for one call (ptr
+// null where there is none left).
 struct HostResult {
     double *ptr = nullptr;
-    int slot = -1;
-    HostResult();
+    int slot = 0, count = 0;
+    explicit HostResult(size_t results);
     ~HostResult();
     HostResult(const HostResult &) = delete;
     HostResult &operator=(const HostResult &) = delete;
-    // r[8] once the stream's work is done: from ptr, or copied from result
-    hipError_t read(const double *result, double *r, hipStream_t s);
+    // r[8 results] once the stream's work is done: from ptr, to which a kernel
+    // has written them, or copied from device memory
+    hipError_t read(const double *result, double *r, size_t results, hipStream_t s);
+    // the same for results in device memory only
+    hipError_t fetch(const double *result, double *r, size_t results, hipStream_t s);
 };
-// The surrogate form of lbm_sweep_batch (opts->surrogate set; arguments
-// validated as for a plain sweep).
 // The network's tensors (w1, b1, w2, b2, w3, b3) for an Adam step.
 constexpr int kAdamMax = 6;
 struct AdamJobs {
@@ -128,6 +129,8 @@ hipError_t cnn_train(const lbm_cnn_shape *s, const lbm_cnn_params *p, const floa
                      const AdamJobs &adam, float lr, float beta1, float beta2, float eps, int64_t t, float *loss,
                      hipStream_t st);
 
+// The surrogate form of lbm_sweep_batch (opts->surrogate set; arguments
+// validated as for a plain sweep).
 int32_t surrogate_sweep(const lbm_params *ps, int n, const lbm_sweep_opts *o, void *const *bufs, void *ws,
                         size_t ws_bytes, hipStream_t st, lbm_obs *out);
 // Turn the 8 reduced doubles into an lbm_obs (host).

@@ -10,6 +10,7 @@
 // column over the row blocks, and pass 3 (k_moments_final, one block) adds the
 // tile partials and the column means.  All in a fixed order, so the result does
 // not depend on scheduling.
+#include <algorithm>
 #include <mutex>
 
 #include "device_q9.h"
@@ -210,17 +211,20 @@ hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *sr
     return hipGetLastError();
 }
 
-// Host memory for results that a kernel writes straight to the host: one page
-// of 64 slots of eight doubles, pinned on first use and kept; a slot belongs to
-// one call at a time.  Against a copy of the 64 bytes into pageable memory this
-// takes a device-to-host copy out of every sample.
-constexpr int kHostSlots = 64;
+// Host memory for results that a kernel writes straight to the host: 64 KB of
+// slots of eight doubles, pinned on first use and kept; a run of slots belongs
+// to one call at a time.  A copy into pageable memory is only enqueued once the
+// host has come to it, and then waits for a staging buffer: 15 us at the end of
+// a call whose kernels have ended.
+constexpr int kHostSlots = 1024;
 static std::mutex g_slot_mu;
 static double *g_slot_page;
 static bool g_slot_failed, g_slot_used[kHostSlots];
 
-HostResult::HostResult()
+HostResult::HostResult(size_t results)
 {
+    if (results > (size_t)kHostSlots)
+        return;
     std::lock_guard<std::mutex> lk(g_slot_mu);
     if (!g_slot_page && !g_slot_failed) {
         // another thread may be capturing a graph: this one's allocation has no
@@ -236,34 +240,56 @@ HostResult::HostResult()
         else
             g_slot_page = (double *)p;
     }
-    for (int k = 0; k < kHostSlots && g_slot_page && slot < 0; ++k)
-        if (!g_slot_used[k]) {
-            g_slot_used[k] = true;
-            slot = k;
-            ptr = g_slot_page + 8 * k;
-        }
+    int run = 0;
+    for (int k = 0; k < kHostSlots && g_slot_page && !ptr; ++k) {
+        run = g_slot_used[k] ? 0 : run + 1;
+        if (run < (int)results)
+            continue;
+        slot = k + 1 - run;
+        count = run;
+        std::fill_n(g_slot_used + slot, count, true);
+        ptr = g_slot_page + 8 * slot;
+    }
 }
 
 HostResult::~HostResult()
 {
-    if (slot < 0)
-        return;
     std::lock_guard<std::mutex> lk(g_slot_mu);
-    g_slot_used[slot] = false;
+    std::fill_n(g_slot_used + slot, count, false);
 }
 
-hipError_t HostResult::read(const double *result, double *r, hipStream_t s)
+hipError_t HostResult::read(const double *result, double *r, size_t results, hipStream_t s)
 {
-    hipError_t e = ptr ? hipSuccess : hipMemcpyAsync(r, result, 8 * sizeof(double), hipMemcpyDeviceToHost, s);
+    const size_t n = 8 * results;
+    hipError_t e = ptr ? hipSuccess : hipMemcpyAsync(r, result, n * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
-        slot = -1;  // the kernel may still write it: not given back
+        count = 0;  // a kernel may still write there: not given back
         return e;
     }
-    for (int k = 0; k < 8 && ptr; ++k)
+    for (size_t k = 0; k < n && ptr; ++k)
         r[k] = ((const volatile double *)ptr)[k];
     return hipSuccess;
+}
+
+__global__ void k_results_to_host(const double *__restrict__ result, int n, double *host)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n)
+        host[k] = result[k];
+}
+
+hipError_t HostResult::fetch(const double *result, double *r, size_t results, hipStream_t s)
+{
+    if (ptr && results) {
+        const int n = 8 * (int)results;
+        hipLaunchKernelGGL(k_results_to_host, dim3((n + 255) / 256), dim3(256), 0, s, result, n, ptr);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return read(result, r, results, s);
 }
 
 void finish_obs(const lbm_params &p, const double *r, int64_t step, lbm_obs *o)

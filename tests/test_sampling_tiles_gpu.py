@@ -71,3 +71,39 @@ def test_coarse_fields(L, nx, ny, c):
         assert (out[k, 3] == -1.0).all()
         L.lbm_coarsen(lat.params, lat.state.data_ptr(), c, one.data_ptr(), st)
         assert torch.equal(one, out[k, :3])
+
+
+def test_results_to_the_host_from_threads_and_streams(L):
+    """Samples from several threads, each on its own stream, more of them at once
+    than the pinned slots hold in places (a batch of 700 samples): every call
+    gets its own."""
+    import threading
+    lats = [_lattice(L, 7, 40 + 2 * k, 18, 40 + k) for k in range(4)]
+    want = [lat.observables() for lat in lats]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(k):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            p = lats[k].params
+            lat = L.Lattice(p)
+            lat.set_state(lats[k].state)
+            b = L.Batch([p])
+            for _ in range(20):
+                if lat.observables() != want[k]:
+                    bad.append(k)
+                b.set_state(0, lats[k].state)
+                b.step_index = 0
+                out = b.run(700, sample_every=1)[0]
+                if len(out) != 700 or [o["step"] for o in out] != list(range(1, 701)):
+                    bad.append(-k)
+            lat.close()
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
+    assert lats[0].params.nx == 40 and L.Batch([lats[0].params]).run(0, sample_every=1) == [[]]
