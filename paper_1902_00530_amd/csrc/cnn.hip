@@ -16,12 +16,12 @@
 //
 // A pass is a few launches: the forward pass one (k_cnn_forward, with the
 // normalisation before it and the loss, or the return to physical fields,
-// after it), the input gradients one (k_cnn_dgrad), the weight gradients one
-// (k_cnn_wgrad), their sums, the loss and Adam one (k_cnn_reduce).  The fields
+// after it), the gradients one (k_cnn_backward), their sums, the loss and Adam
+// one (k_cnn_reduce).  The fields
 // are small (tens of pixels a side), so a pass of one kernel per layer was
 // bound by launches, staging and gaps: 64 samples of 32 x 32 took 36.1 us to
 // predict (6 launches; now 15.2 us, 1 launch) and 132.4 us to train on (18
-// launches; now 73.5 us, 4 launches).
+// launches; now 66.7 us, 3 launches).
 #include <math.h>
 
 #include <algorithm>
@@ -499,136 +499,40 @@ __global__ __launch_bounds__(64 * kCnnWaves) void k_cnn_forward(CnnForward q)
 }
 
 // ---------------------------------------------------------------------------
-// Input gradients: dz2 = (a2 > 0) conv(dy, w3 flipped), dz1 = (a1 > 0)
-// conv(dz2, w2 flipped), one block per tile as the forward pass; dz2 and dz1
-// out for the weight gradients.  75 KB of LDS: two blocks a CU.  15 us for 512
-// tiles (25 us as a kernel per layer), about half of it the first loads.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64 * kCnnWaves) void k_cnn_dgrad(const float *__restrict__ dy, const float *__restrict__ a1,
-                                                              const float *__restrict__ a2,
-                                                              const uint16_t *__restrict__ w2,
-                                                              const uint16_t *__restrict__ w3, float *__restrict__ dz2,
-                                                              float *__restrict__ dz1, int H, int W)
-{
-    constexpr int NT = 64 * kCnnWaves;
-    using R2 = Region<2>;
-    using R1 = Region<1>;
-    using L1 = ConvLds<4>;
-    using L2 = ConvLds<32>;
-    constexpr int P1 = R2::N * 4, CS = L2::CS, P2 = R1::N * CS;
-    __shared__ __attribute__((aligned(16))) uint16_t s_dy[3 * P1];
-    __shared__ __attribute__((aligned(16))) uint16_t s_dz[3 * P2];
-    __shared__ __attribute__((aligned(16))) uint16_t s_w3[32 * L1::WS];
-    __shared__ __attribute__((aligned(16))) uint16_t s_w2[32 * L2::WS];
-    const int n = blockIdx.z, i0 = blockIdx.y * kTH, j0 = blockIdx.x * kTW;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int m = lane & 31, hk = lane >> 5;
-    const size_t HW = (size_t)H * W;
-    const bool small = H < Region<3>::H || W < Region<3>::W;
-    // every load of the block first: dy on the widened tile, the weights, and
-    // the activations that mask a lane's pixel (dz2: slab wv of R1; dz1: the
-    // tile's own, waves 0..3, the same pixel)
-    static_assert(R1::kSlabs <= kCnnWaves, "a slab per wave");
-    float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (tid < R2::N) {
-        const int ry = tid / R2::W, rx = tid - ry * R2::W;
-        const size_t at = (size_t)wrap_index(small, i0 + ry - 2, H) * W + wrap_index(small, j0 + rx - 2, W);
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            dv[c] = dy[((size_t)n * 3 + c) * HW + at];
-    }
-    WeightStage<NT, 32 * 32> sw2;
-    WeightStage<NT, 3 * 32> sw3;
-    sw2.load(w2, 32 * 32);
-    sw3.load(w3, 3 * 32);
-    int ry, rx;
-    const bool live = R1::pixel(min(wv, R1::kSlabs - 1), m, ry, rx);
-    const int i = i0 + ry - 1, j = j0 + rx - 1;
-    const size_t at = (size_t)wrap_index(small, i, H) * W + wrap_index(small, j, W);
-    const bool own = wv < 4 && i < H && j < W;
-    // the lane's 16 channels of pixel `at` of sample n
-    auto channel = [&](int r) { return ((size_t)n * 32 + 8 * (r >> 2) + 4 * hk + (r & 3)) * HW + at; };
-    float m2[16], m1[16];
-    if (wv < R1::kSlabs)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            m2[r] = a2[channel(r)];
-    if (wv < 4)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            m1[r] = a1[channel(r)];
-    if (tid < R2::N)
-        put_split4(s_dy, tid * 4, P1, dv);
-    for (int e = tid; e < 32 * 9; e += NT)  // the fourth channel's weights
-        s_w3[(e / 9) * L1::WS + (e % 9) * 4 + 3] = 0;
-    sw2.store(32 * 32, [&](int row, int t, uint16_t v) {  // row = c * 32 + o
-        s_w2[(row & 31) * L2::WS + (8 - t) * L2::TS + (row >> 5)] = v;
-    });
-    sw3.store(3 * 32, [&](int row, int t, uint16_t v) {
-        s_w3[(row & 31) * L1::WS + (8 - t) * L1::TS + (row >> 5)] = v;
-    });
-    __syncthreads();
-    if (wv < R1::kSlabs) {
-        const f32x16 acc = conv_slab<4, 4, L1::TS, R2::W>(s_dy, P1, ry * R2::W + rx, s_w3 + m * L1::WS, hk);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v[u] = m2[4 * g + u] > 0.0f ? acc[4 * g + u] : 0.0f;
-                if (own)
-                    dz2[channel(4 * g + u)] = v[u];
-            }
-            if (live)
-                put_split4(s_dz, (ry * R1::W + rx) * CS + 8 * g + 4 * hk, P2, v);
-        }
-    }
-    __syncthreads();
-    if (wv < 4) {
-        // the lane's pixel has its top-left tap at (ry - 1, rx - 1) of R1
-        const f32x16 acc =
-            conv_slab<32, CS, L2::TS, R1::W>(s_dz, P2, (ry - 1) * R1::W + rx - 1, s_w2 + m * L2::WS, hk);
-        if (own)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                dz1[channel(r)] = m1[r] > 0.0f ? acc[r] : 0.0f;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Weight and bias gradients of the three layers in one launch (blockIdx.y):
-// dw[o,c,tap] = sum_{n,i,j} dy[n,o,i,j] x[n,c,i+ky-1,j+kx-1], db[o] = sum
-// dy[n,o,i,j].  One block per (sample, 16 x 8 tile) writes its partial sums to
-// part[block][co ci 9 + co]; k_cnn_reduce adds the blocks in order in
-// float64.  Per block a matrix product on the matrix cores
-// (v_mfma_f32_16x16x4_f32): D[o][k] = sum_p A[o][p] B[p][k], p the tile's 128
-// pixels in groups of four neighbours (lane group q = l / 16 takes pixel 4 s +
-// q of step s), k = c * 9 + tap.  Each wave takes 16 columns k at a time for
-// every row o, so the A operands stay in registers over its columns and each
-// B operand read from LDS feeds both row blocks: with one 16 x 16 block at a
-// time, both operands read again for each, the products waited on LDS.  The
-// bias sums are per-row wave reductions of the dy tile in a fixed order.  For
-// 512 tiles 34 us (53 us as a launch per layer): the tiles' loads (60 MB) and
-// partials (23 MB) and the FP32 products (12 us) hardly overlap.
+// Backward pass of one tile: the input gradients dz2 = (a2 > 0) conv(dy, w3
+// flipped) and dz1 = (a1 > 0) conv(dz2, w2 flipped), and the tile's partial sums
+// of the three layers' weight and bias gradients, dw[o,c,tap] = sum_{n,i,j}
+// dz[n,o,i,j] x[n,c,i+ky-1,j+kx-1], db[o] = sum dz[n,o,i,j] (dz: dz1, dz2, dy;
+// x: the layer's input).  The partials of tile t go to part[k] + t (co ci 9 +
+// co); k_cnn_reduce adds the tiles in order in float64.
 //
+// Weight gradients are matrix products on the matrix cores: D[o][k] = sum_p
+// A[o][p] B[p][k], p the tile's 128 pixels, k = c * 9 + tap.  With 32 rows
+// v_mfma_f32_16x16x4_f32, groups of four neighbouring pixels (lane group q =
+// l / 16 takes pixel 4 s + q of step s): a wave takes 16 columns k at a time for
+// both row blocks, so the A operands stay in registers over its columns and
+// each B operand read from LDS feeds two products.
 // 16x16x4 operand layout (lane l): A row l mod 16, k = l / 16; B column
 // l mod 16, k = l / 16; result register r holds row 4 (l / 16) + r of
 // column l mod 16.
+//
+// One block of eight waves a CU (134 KB of LDS), taking every 256th tile; each
+// phase's input tile is loaded during the phase before.  Per tile the products
+// take 15,000 cycles of a SIMD's matrix core (most of them FP32, 32 cycles each),
+// the phases together 34,000, and the first loads and weights 16,000 a block: 42
+// us for 512 tiles.  dz1 and dz2 never leave the CU: as kernels of their own,
+// input and weight gradients waited 6 to 10 us for their first loads and moved
+// 34 MB more, 15 and 34 us.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWgWaves = 4;
-
-struct WgradJobs {
-    const float *dy[3], *x[3];
-    float *part[3];
-    int co[3], ci[3];
-};
+// dz rows of kDS floats: lanes (l mod 16, l / 16) read 64 distinct banks
+constexpr int kDS = kTW * kTH + 4;
 
 // The 16 columns from 16 cb of row blocks rb0 .. rb0 + NRB - 1 (16 rows each).
 template <int NRB>
 __device__ __forceinline__ void wgrad_columns(const float *s_x, const float av[][kTW * kTH / 4], int rb0, int K, int cb,
-                                               int l16, int q, float *__restrict__ out)
+                                              int l16, int q, float *__restrict__ out)
 {
     constexpr int NS = kTW * kTH / 4;
     const int col = cb * 16 + l16;  // this lane's B column k
@@ -656,22 +560,25 @@ __device__ __forceinline__ void wgrad_columns(const float *s_x, const float av[]
                 out[(size_t)((rb0 + rb) * 16 + 4 * q + r) * K + col] = acc[rb][r];
 }
 
-// 32 rows: columns 16 at a time, four waves' worth of them with both row
-// blocks each; of what is left, (column block, row block) pairs.
-__device__ __forceinline__ void wgrad_32rows(const float *s_x, const float *s_d, int DS, int K, int wv, int l16, int q,
+// 32 rows: columns 16 at a time, eight waves' worth of them with both row
+// blocks each; of what is left, (column block, row block) pairs, from wave 4 on
+// (waves 0..3 have the input gradient's slabs besides).
+__device__ __forceinline__ void wgrad_32rows(const float *s_x, const float *s_d, int K, int wv, int l16, int q,
                                              float *__restrict__ out)
 {
-    constexpr int NS = kTW * kTH / 4;
+    constexpr int NS = kTW * kTH / 4, NW = kCnnWaves;
     float av[2][NS];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
         for (int s4 = 0; s4 < NS; ++s4)
-            av[rb][s4] = s_d[(rb * 16 + l16) * DS + q + 4 * s4];
-    const int ncb = (K + 15) >> 4, whole = ncb / kWgWaves * kWgWaves;
-    for (int cb = wv; cb < whole; cb += kWgWaves)
+            av[rb][s4] = s_d[(rb * 16 + l16) * kDS + q + 4 * s4];
+    const int ncb = (K + 15) >> 4, whole = ncb / NW * NW;
+#pragma unroll 1  // one set of operands in registers
+    for (int cb = wv; cb < whole; cb += NW)
         wgrad_columns<2>(s_x, av, 0, K, cb, l16, q, out);
-    for (int i = wv; i < 2 * (ncb - whole); i += kWgWaves) {
+#pragma unroll 1
+    for (int i = (wv + 4) % NW; i < 2 * (ncb - whole); i += NW) {
         if (i & 1)
             wgrad_columns<1>(s_x, av + 1, 1, K, whole + (i >> 1), l16, q, out);
         else
@@ -679,131 +586,59 @@ __device__ __forceinline__ void wgrad_32rows(const float *s_x, const float *s_d,
     }
 }
 
-// Three rows (the output layer): v_mfma_f32_4x4x1_16b_f32, a row o = l mod 4
-// and a column of its own per lane, one pixel per product: the sum over
-// pixels runs in the same order, one fma each, as in the 16x16x4 products
-// (equal bit for bit), at 4 rows of matrix work instead of 16.
+// Three rows (the output layer), the 64 columns from c0:
+// v_mfma_f32_4x4x1_16b_f32, a row o = l mod 4 and a column of its own per lane,
+// one pixel per product: the sum over pixels runs in the same order, one fma
+// each, as in the 16x16x4 products (equal bit for bit), at 4 rows of matrix
+// work instead of 16.
 // 4x4x1 operand layout (lane l, block l / 4): A row l mod 4; B column l mod 4;
 // result register r holds row r of column l mod 4.
-__device__ __forceinline__ void wgrad_3rows(const float *s_x, const float *s_d, int DS, int K, int wv, int lane,
+__device__ __forceinline__ void wgrad_3rows(const float *s_x, const float *s_d, int K, int c0, int lane,
                                             float *__restrict__ out)
 {
-    constexpr int NP = kTW * kTH;
-    for (int c0 = wv * 64; c0 < K; c0 += kWgWaves * 64) {
-        const int col = c0 + lane;
-        const int cc = col < K ? col / 9 : 0, t = col < K ? col - cc * 9 : 0, ty = t / 3, tx = t - ty * 3;
-        const float *pb = s_x + cc * kHalo + ty * kHW_ + tx, *pa = s_d + (lane & 3) * DS;
-        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        float av[2][16], bv[2][16];  // a tile row of operands, read while the last one multiplies
-        auto read = [&](int y) {
+    static_assert(kTW == 16, "tile rows of 16 pixels");
+    const int col = c0 + lane;
+    const int cc = col < K ? col / 9 : 0, t = col < K ? col - cc * 9 : 0, ty = t / 3, tx = t - ty * 3;
+    const float *pb = s_x + cc * kHalo + ty * kHW_ + tx, *pa = s_d + (lane & 3) * kDS;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    float av[2][16], bv[2][16];  // a tile row of operands, read while the last one multiplies
+    auto read = [&](int y) {
 #pragma unroll
-            for (int x = 0; x < 16; x += 4) {
-                const float4 v = *(const float4 *)(pa + 16 * y + x);
-                av[y & 1][x] = v.x, av[y & 1][x + 1] = v.y, av[y & 1][x + 2] = v.z, av[y & 1][x + 3] = v.w;
-            }
-#pragma unroll
-            for (int x = 0; x < 16; ++x)
-                bv[y & 1][x] = pb[y * kHW_ + x];
-        };
-        read(0);
-#pragma unroll
-        for (int y = 0; y < kTH; ++y) {
-            if (y + 1 < kTH)
-                read(y + 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int x = 0; x < 16; ++x)
-                acc = __builtin_amdgcn_mfma_f32_4x4x1f32(av[y & 1][x], bv[y & 1][x], acc, 0, 0, 0);
+        for (int x = 0; x < 16; x += 4) {
+            const float4 v = *(const float4 *)(pa + 16 * y + x);
+            av[y & 1][x] = v.x, av[y & 1][x + 1] = v.y, av[y & 1][x + 2] = v.z, av[y & 1][x + 3] = v.w;
         }
-        if (col < K)
 #pragma unroll
-            for (int o = 0; o < 3; ++o)
-                out[(size_t)o * K + col] = acc[o];
+        for (int x = 0; x < 16; ++x)
+            bv[y & 1][x] = pb[y * kHW_ + x];
+    };
+    read(0);
+#pragma unroll
+    for (int y = 0; y < kTH; ++y) {
+        if (y + 1 < kTH)
+            read(y + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < 16; ++x)
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(av[y & 1][x], bv[y & 1][x], acc, 0, 0, 0);
     }
-    static_assert(NP == 16 * kTH, "tile rows of 16 pixels");
+    if (col < K)
+#pragma unroll
+        for (int o = 0; o < 3; ++o)
+            out[(size_t)o * K + col] = acc[o];
 }
 
-__global__ __launch_bounds__(64 * kWgWaves) void k_cnn_wgrad(WgradJobs jobs, int H, int W)
+// Bias sums of rows o < co: wave w takes rows w, w + 8, ... (all at once: one
+// chain of lane exchanges); lane l adds pixels l and l + 64, then a fixed
+// butterfly over the wave.
+__device__ __forceinline__ void bias_sums(const float *s_d, int co, int wv, int lane, float *__restrict__ out)
 {
-    // dy rows of DS floats: lanes (l mod 16, l / 16) read 64 distinct banks
-    constexpr int NT = 64 * kWgWaves, NP = kTW * kTH, DS = NP + 4;
-    __shared__ float s_x[kMaxC * kHalo];
-    __shared__ __attribute__((aligned(16))) float s_d[kMaxC * DS];  // dy tile [o][p] (rows o >= co_n zero; pixels outside the field zero)
-    const int job = blockIdx.y;
-    const float *dy = jobs.dy[job], *x = jobs.x[job];
-    const int co_n = jobs.co[job], ci_n = jobs.ci[job];
-    const int tiles_j = (W + kTW - 1) / kTW, tiles_i = (H + kTH - 1) / kTH;
-    const int n = blockIdx.x / (tiles_i * tiles_j), tt = blockIdx.x - n * (tiles_i * tiles_j);
-    const int ti = tt / tiles_j;
-    const int i0 = ti * kTH, j0 = (tt - ti * tiles_j) * kTW;
-    const size_t HW = (size_t)H * W;
-    const int tid = threadIdx.x;
-    // every load of the block in flight before its first LDS write: a thread
-    // takes one pixel of the widened input tile and every channel, and one
-    // pixel of the dy tile and every second channel
-    {
-        constexpr int ND = kMaxC * NP / NT;
-        const bool small = H < kHH || W < kHW_;
-        const int ry = tid / kHW_, rx = tid - ry * kHW_;
-        const float *px = x + (size_t)n * ci_n * HW + (size_t)wrap_index(small, i0 + ry - 1, H) * W +
-                          wrap_index(small, j0 + rx - 1, W);
-        const int p = tid % NP, gi = i0 + p / kTW, gj = j0 + p % kTW;
-        const bool in = gi < H && gj < W;
-        const float *pd = dy + (size_t)n * co_n * HW + (in ? (size_t)gi * W + gj : 0);
-        float xv[kMaxC], dv[ND];
-        // NX channels of x, ND2 of this thread's dy rows (those past ci_n and
-        // co_n repeat the last one)
-        auto load = [&](auto nx, auto nd) {
-            if (tid < kHalo)
-#pragma unroll
-                for (int c = 0; c < decltype(nx)::value; ++c)
-                    xv[c] = px[(size_t)min(c, ci_n - 1) * HW];
-#pragma unroll
-            for (int u = 0; u < decltype(nd)::value; ++u)
-                dv[u] = pd[(size_t)min(tid / NP + u * (NT / NP), co_n - 1) * HW];
-        };
-        auto store = [&](auto nx, auto nd) {
-            if (tid < kHalo)
-#pragma unroll
-                for (int c = 0; c < decltype(nx)::value; ++c)
-                    s_x[c * kHalo + tid] = xv[c];
-#pragma unroll
-            for (int u = 0; u < decltype(nd)::value; ++u) {
-                const int o = tid / NP + u * (NT / NP);
-                s_d[o * DS + p] = in && o < co_n ? dv[u] : 0.0f;
-            }
-        };
-        using Few = IntTag<4>;
-        using AllX = IntTag<kMaxC>;
-        using AllD = IntTag<ND>;
-        if (co_n != 32) {  // three rows: four with the zero one
-            load(AllX{}, IntTag<4 / (NT / NP)>{});
-            store(AllX{}, IntTag<4 / (NT / NP)>{});
-        } else if (ci_n <= 4) {
-            load(Few{}, AllD{});
-            store(Few{}, AllD{});
-        } else {
-            load(AllX{}, AllD{});
-            store(AllX{}, AllD{});
-        }
-    }
-    __syncthreads();
-    const int K = ci_n * 9, nw = co_n * K;
-    float *out = jobs.part[job] + (size_t)blockIdx.x * (nw + co_n);
-    const int lane = tid & 63, wv = tid >> 6;
-    if (co_n == 32)
-        wgrad_32rows(s_x, s_d, DS, K, wv, lane & 15, lane >> 4, out);
-    else
-        wgrad_3rows(s_x, s_d, DS, K, wv, lane, out);
-    // bias: wave w takes rows w, w + 4, ... (all at once: one chain of lane
-    // exchanges, not eight); lane l adds pixels l and l + 64, then a fixed
-    // butterfly over the wave
-    constexpr int NB = kMaxC / kWgWaves;
+    constexpr int NB = kMaxC / kCnnWaves;
     float v[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-        const int o = min(wv + k * kWgWaves, co_n - 1);
-        v[k] = s_d[o * DS + lane] + s_d[o * DS + lane + 64];
+        const int o = min(wv + k * kCnnWaves, co - 1);
+        v[k] = s_d[o * kDS + lane] + s_d[o * kDS + lane + 64];
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1)
@@ -812,8 +647,181 @@ __global__ __launch_bounds__(64 * kWgWaves) void k_cnn_wgrad(WgradJobs jobs, int
             v[k] += __shfl_xor(v[k], off, 64);
 #pragma unroll
     for (int k = 0; k < NB; ++k)
-        if (lane == 0 && wv + k * kWgWaves < co_n)
-            out[nw + wv + k * kWgWaves] = v[k];
+        if (lane == 0 && wv + k * kCnnWaves < co)
+            out[wv + k * kCnnWaves] = v[k];
+}
+
+struct CnnBackward {
+    const float *dy, *x, *a1, *a2;
+    const uint16_t *w2, *w3;
+    float *part[3];
+    int cin, H, W, tiles;
+};
+
+// CX: channels of x held (4, or 32 where there are more)
+template <int CX>
+__global__ __launch_bounds__(64 * kCnnWaves) void k_cnn_backward(CnnBackward q)
+{
+    constexpr int NT = 64 * kCnnWaves;
+    using R2 = Region<2>;
+    using R1 = Region<1>;
+    using L1 = ConvLds<4>;
+    using L2 = ConvLds<32>;
+    constexpr int P1 = R2::N * 4, CS = L2::CS, P2 = R1::N * CS;
+    __shared__ __attribute__((aligned(16))) uint16_t s_dy[3 * P1];
+    __shared__ __attribute__((aligned(16))) uint16_t s_dz[3 * P2];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w3[32 * L1::WS];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w2[32 * L2::WS];
+    __shared__ float s_x[kMaxC * kHalo];  // a2, then a1, then x on the tile with its halo
+    // dy, dz2 and dz1 of the tile [o][p] (pixels outside the field zero)
+    __shared__ __attribute__((aligned(16))) float s_d3[4 * kDS];
+    __shared__ float s_d2[kMaxC * kDS], s_d1[kMaxC * kDS];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 31, hk = lane >> 5;
+    const int H = q.H, W = q.W, cin = q.cin;
+    const size_t HW = (size_t)H * W;
+    const int tiles_j = (W + kTW - 1) / kTW, per = tiles_j * ((H + kTH - 1) / kTH);
+    const bool small = H < Region<3>::H || W < Region<3>::W;
+    // input tiles: thread (group g, pixel p) takes channels g, g + 2, ... of its
+    // pixel; dy on the widened tile R2: a thread per pixel
+    static_assert(2 * kHalo <= NT && R2::N <= NT && R1::N == kHalo && R1::kSlabs <= kCnnWaves, "threads and slabs");
+    const int hp = tid % kHalo, hg = tid / kHalo, dyy = tid / R2::W, dyx = tid - dyy * R2::W;
+    int n = 0, i0 = 0, j0 = 0;
+    size_t halo_at = 0, dy_at = 0;
+    float hv[kMaxC / 2], dv[4];
+    dv[3] = 0.0f;
+    auto locate = [&](int tile) {
+        n = tile / per;
+        const int r = tile - n * per, ti = r / tiles_j;
+        i0 = ti * kTH;
+        j0 = (r - ti * tiles_j) * kTW;
+        halo_at = (size_t)wrap_index(small, i0 + hp / kHW_ - 1, H) * W + wrap_index(small, j0 + hp % kHW_ - 1, W);
+        if (tid < R2::N)
+            dy_at = (size_t)wrap_index(small, i0 + dyy - 2, H) * W + wrap_index(small, j0 + dyx - 2, W);
+    };
+    auto load_halo = [&](auto nu, const float *__restrict__ src, int ci) {
+        if (hg < 2)
+#pragma unroll
+            for (int u = 0; u < decltype(nu)::value; ++u)
+                hv[u] = src[((size_t)n * ci + min(hg + 2 * u, ci - 1)) * HW + halo_at];
+    };
+    auto store_halo = [&](auto nu) {
+        if (hg < 2)
+#pragma unroll
+            for (int u = 0; u < decltype(nu)::value; ++u)
+                s_x[(hg + 2 * u) * kHalo + hp] = hv[u];
+    };
+    using All = IntTag<kMaxC / 2>;
+    auto load_first = [&]() {
+        load_halo(All{}, q.a2, 32);
+        if (tid < R2::N)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                dv[c] = q.dy[((size_t)n * 3 + c) * HW + dy_at];
+    };
+    locate(blockIdx.x);
+    load_first();
+    {
+        WeightStage<NT, 32 * 32> sw2;
+        WeightStage<NT, 3 * 32> sw3;
+        sw2.load(q.w2, 32 * 32);
+        sw3.load(q.w3, 3 * 32);
+        for (int e = tid; e < 32 * 9; e += NT)  // the fourth channel's weights
+            s_w3[(e / 9) * L1::WS + (e % 9) * 4 + 3] = 0;
+        sw2.store(32 * 32, [&](int row, int t, uint16_t v) {  // row = c * 32 + o
+            s_w2[(row & 31) * L2::WS + (8 - t) * L2::TS + (row >> 5)] = v;
+        });
+        sw3.store(3 * 32, [&](int row, int t, uint16_t v) {
+            s_w3[(row & 31) * L1::WS + (8 - t) * L1::TS + (row >> 5)] = v;
+        });
+    }
+    // the lane's r-th channel in a result, and its pixel of the tile in slab wv
+    auto channel = [&](int r) { return 8 * (r >> 2) + 4 * hk + (r & 3); };
+    for (int tile = blockIdx.x;;) {
+        store_halo(All{});
+        if (tid < R2::N) {
+            put_split4(s_dy, tid * 4, P1, dv);
+            const int y = dyy - 2, x = dyx - 2;
+            if (y >= 0 && y < kTH && x >= 0 && x < kTW)
+#pragma unroll
+                for (int o = 0; o < 4; ++o)
+                    s_d3[o * kDS + y * kTW + x] = i0 + y < H && j0 + x < W ? dv[o] : 0.0f;
+        }
+        load_halo(All{}, q.a1, 32);
+        __syncthreads();
+        const bool own = i0 + 2 * wv + (m >> 4) < H && j0 + (m & 15) < W;  // slab wv < 4
+        float *out3 = q.part[2] + (size_t)tile * (3 * 288 + 3);
+        // dz2 (waves 0..5), the output layer's gradients (waves 6, 7, then 2..4)
+        if (wv < R1::kSlabs) {
+            int ry, rx;
+            const bool live = R1::pixel(wv, m, ry, rx);
+            const int pix = ry * R1::W + rx;
+            float mask[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                mask[r] = s_x[channel(r) * kHalo + pix];
+            const f32x16 acc = conv_slab<4, 4, L1::TS, R2::W>(s_dy, P1, ry * R2::W + rx, s_w3 + m * L1::WS, hk);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int ch = channel(4 * g + u);
+                    v[u] = mask[4 * g + u] > 0.0f ? acc[4 * g + u] : 0.0f;
+                    if (wv < 4)
+                        s_d2[ch * kDS + wv * 32 + m] = own ? v[u] : 0.0f;
+                }
+                if (live)
+                    put_split4(s_dz, pix * CS + channel(4 * g), P2, v);
+            }
+        }
+        if (wv >= 6)
+            wgrad_3rows(s_x, s_d3, 288, (wv - 6) * 64, lane, out3);
+        else if (wv >= 2 && wv < 5)
+            wgrad_3rows(s_x, s_d3, 288, wv * 64, lane, out3);
+        bias_sums(s_d3, 3, wv, lane, out3 + 3 * 288);
+        __syncthreads();
+        store_halo(All{});
+        load_halo(IntTag<CX / 2>{}, q.x, cin);
+        __syncthreads();
+        // dz1 (waves 0..3), the second layer's gradients
+        float *out2 = q.part[1] + (size_t)tile * (32 * 288 + 32);
+        if (wv < 4) {
+            int ry, rx;
+            Region<0>::pixel(wv, m, ry, rx);
+            const int pix = (ry + 1) * R1::W + rx + 1;
+            float mask[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                mask[r] = s_x[channel(r) * kHalo + pix];
+            // before the other waves' products, which keep the matrix cores busy
+            // while these wait for LDS: else they ended 10,000 cycles later
+            __builtin_amdgcn_s_setprio(3);
+            const f32x16 acc =
+                conv_slab<32, CS, L2::TS, R1::W>(s_dz, P2, ry * R1::W + rx, s_w2 + m * L2::WS, hk);
+            __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                s_d1[channel(r) * kDS + wv * 32 + m] = own && mask[r] > 0.0f ? acc[r] : 0.0f;
+        }
+        wgrad_32rows(s_x, s_d2, 288, wv, lane & 15, lane >> 4, out2);
+        bias_sums(s_d2, 32, wv, lane, out2 + 32 * 288);
+        __syncthreads();
+        store_halo(IntTag<CX / 2>{});
+        float *out1 = q.part[0] + (size_t)tile * (32 * cin * 9 + 32);
+        tile += gridDim.x;
+        const bool more = tile < q.tiles;
+        if (more) {
+            locate(tile);
+            load_first();
+        }
+        __syncthreads();
+        wgrad_32rows(s_x, s_d1, cin * 9, wv, lane & 15, lane >> 4, out1);
+        bias_sums(s_d1, 32, wv, lane, out1 + 32 * cin * 9);
+        if (!more)
+            break;
+        __syncthreads();
+    }
 }
 
 // Adam (Kingma & Ba, algorithm 1) on element e of tensor q of the jobs, with
@@ -1188,8 +1196,6 @@ struct CnnWs {
     double *part;     // loss partials
     float *gpart[3];  // per-tile gradient partials of each layer
     float *dy;        // dL/dy [n][cout][hw]
-    float *dz2;       // [n][hidden][hw]
-    float *dz1;       // [n][hidden][hw]
     size_t total;
 };
 
@@ -1197,8 +1203,7 @@ static const int kMseBlocks = 1024;
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Workspace of the backward pass: loss and gradient partials, intermediate
-// gradients.  base == nullptr only measures the size.
+// Workspace of the backward pass: loss and gradient partials, dL/dy.  base == nullptr only measures the size.
 static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
 {
     CnnWs L{};
@@ -1214,8 +1219,6 @@ static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
     for (int k = 0; k < 3; ++k)
         L.gpart[k] = (float *)take(tiles * (size_t)layer_total(s, k) * sizeof(float));
     L.dy = (float *)take((size_t)s->n * s->cout * hw * sizeof(float));
-    L.dz2 = (float *)take((size_t)s->n * s->hidden * hw * sizeof(float));
-    L.dz1 = (float *)take((size_t)s->n * s->hidden * hw * sizeof(float));
     L.total = off;
     return L;
 }
@@ -1226,11 +1229,6 @@ static void launch_coarsen(const float *f, const float *const *bufs, int n, cons
     const int per = std::max(1, kCoarsenCols / c);
     hipLaunchKernelGGL(k_coarsen, dim3((cw + per - 1) / per, chh, n), dim3(kCoarsenCols), 0, st, f, bufs, a, c, cw, chh,
                        out, out_stride);
-}
-
-static dim3 tile_grid(const lbm_cnn_shape *s)
-{
-    return dim3((s->w + kTW - 1) / kTW, (s->h + kTH - 1) / kTH, s->n);
 }
 
 template <int MODE>
@@ -1263,22 +1261,12 @@ static hipError_t backward(const lbm_cnn_shape *s, const lbm_cnn_params *p, cons
                            const float *a2, const CnnWs &L, int nloss, float *loss, const lbm_cnn_grads *g,
                            const AdamJobs *adam, const AdamStep &step, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_cnn_dgrad, tile_grid(s), dim3(64 * kCnnWaves), 0, st, L.dy, a1, a2, p->w[1], p->w[2], L.dz2,
-                       L.dz1, s->h, s->w);
-    // the layer with the most products first
-    const int order[3] = {1, 2, 0};
-    const float *dys[3] = {L.dz1, L.dz2, L.dy}, *xs[3] = {x, a1, a2};
     const int co[3] = {32, 32, 3}, ci[3] = {s->cin, 32, 32};
-    WgradJobs w{};
     ReduceJobs r{};
+    CnnBackward q{L.dy, x, a1, a2, p->w[1], p->w[2], {}, s->cin, s->h, s->w, s->n * conv_tiles(s->h, s->w)};
     int first = 0;
     for (int i = 0; i < 3; ++i) {
-        const int k = order[i];
-        w.dy[i] = dys[k];
-        w.x[i] = xs[k];
-        w.part[i] = L.gpart[k];
-        w.co[i] = co[k];
-        w.ci[i] = ci[k];
+        q.part[i] = L.gpart[i];
         r.part[i] = L.gpart[i];
         r.nw[i] = co[i] * ci[i] * 9;
         r.nb[i] = co[i];
@@ -1289,12 +1277,16 @@ static hipError_t backward(const lbm_cnn_shape *s, const lbm_cnn_params *p, cons
             r.g[2 * i + 1] = g->b[i];
         }
     }
-    r.nblocks = s->n * conv_tiles(s->h, s->w);
+    r.nblocks = q.tiles;
     r.loss_part = L.part;
     r.nloss = nloss;
     r.count = (int64_t)s->n * s->cout * s->h * s->w;
     r.loss = loss;
-    hipLaunchKernelGGL(k_cnn_wgrad, dim3(r.nblocks, 3), dim3(64 * kWgWaves), 0, st, w, s->h, s->w);
+    const dim3 grd(std::min(q.tiles, 256)), blk(64 * kCnnWaves);
+    if (s->cin <= 4)
+        hipLaunchKernelGGL(k_cnn_backward<4>, grd, blk, 0, st, q);
+    else
+        hipLaunchKernelGGL(k_cnn_backward<kMaxC>, grd, blk, 0, st, q);
     if (adam)
         hipLaunchKernelGGL(k_cnn_reduce<true>, dim3(first + 1), dim3(kReduceThreads), 0, st, r, *adam, step);
     else
