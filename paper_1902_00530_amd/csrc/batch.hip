@@ -574,7 +574,7 @@ __global__ void k_batch_set_ctrl(Ctrl *ctrl, int64_t t0)
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t lat, tiles, mtiles, ctrl, part, colpart, colmean, results, total;
+    size_t lat, tiles, mtiles, ctrl, part, colpart, colmean, tiles3, results, total;
     int64_t n_tiles1, n_tiles2, n_tiles3, n_mtiles, colpart_n, colmean_n;
 };
 
@@ -748,7 +748,7 @@ static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
     L.lat = off;
     off = align256(off + sizeof(LatDesc) * n);
     L.tiles = off;
-    off = align256(off + sizeof(BatchTile) * (L.n_tiles1 + L.n_tiles2 + L.n_tiles3));
+    off = align256(off + sizeof(BatchTile) * (L.n_tiles1 + L.n_tiles2));
     L.mtiles = off;
     off = align256(off + sizeof(MomTile) * L.n_mtiles);
     L.ctrl = off;
@@ -759,6 +759,10 @@ static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
     off = align256(off + sizeof(double) * L.colpart_n);
     L.colmean = off;
     off = align256(off + sizeof(double) * L.colmean_n);
+    // after every table that a workspace's record (WsTables) may take as held: those
+    // stay where they are for other models of the same lattices, this list does not
+    L.tiles3 = off;
+    off = align256(off + sizeof(BatchTile) * L.n_tiles3);
     L.results = off;
     off = align256(off + sizeof(double) * 8 * (size_t)n * (size_t)std::max<int64_t>(n_samples, 1));
     L.total = off;
@@ -1295,7 +1299,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // two-step shapes in the second), uploaded unless the region holds it
     auto upload = [&](int k) -> std::pair<BatchTile *, int64_t> {
         const int r = k == kMulti ? 2 : kShapes[k].steps == 1 ? 0 : 1;
-        BatchTile *d = r == 0 ? d_tiles1 : r == 1 ? d_tiles2 : d_tiles2 + Ly.n_tiles2;
+        BatchTile *d = r == 0 ? d_tiles1 : r == 1 ? d_tiles2 : (BatchTile *)(w + Ly.tiles3);
         const int64_t count = k == kMulti ? Ly.n_tiles3 : count_tiles(ps, n, kShapes[k].tx, kShapes[k].ty);
         // the several-steps list also depends on the model (its geometry)
         const int held = k == kMulti ? k | mc.tx << 8 | mc.ty << 16 : k;
