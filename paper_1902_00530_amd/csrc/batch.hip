@@ -727,7 +727,7 @@ static int branch_cut(const lbm_params *ps, int first, int last)
 static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
 {
     Layout L{};
-    L.n_tiles3 = count_multi_tiles(ps, n, multi_for_batch(ps, n));
+    L.n_tiles3 = kMultiMaxTiles;
     // room for the list of one single-step shape and one two-step shape
     L.n_tiles1 = 0;
     L.n_tiles2 = 0;
@@ -759,8 +759,8 @@ static Layout layout(const lbm_params *ps, int n, int64_t n_samples)
     off = align256(off + sizeof(double) * L.colpart_n);
     L.colmean = off;
     off = align256(off + sizeof(double) * L.colmean_n);
-    // after every table that a workspace's record (WsTables) may take as held: those
-    // stay where they are for other models of the same lattices, this list does not
+    // room for the largest list, whatever the lattices and their model: part of a
+    // batch never needs more workspace than the batch
     L.tiles3 = off;
     off = align256(off + sizeof(BatchTile) * L.n_tiles3);
     L.results = off;
@@ -1300,7 +1300,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     auto upload = [&](int k) -> std::pair<BatchTile *, int64_t> {
         const int r = k == kMulti ? 2 : kShapes[k].steps == 1 ? 0 : 1;
         BatchTile *d = r == 0 ? d_tiles1 : r == 1 ? d_tiles2 : (BatchTile *)(w + Ly.tiles3);
-        const int64_t count = k == kMulti ? Ly.n_tiles3 : count_tiles(ps, n, kShapes[k].tx, kShapes[k].ty);
+        const int64_t count = k == kMulti ? count_multi_tiles(ps, n, mc) : count_tiles(ps, n, kShapes[k].tx, kShapes[k].ty);
         // the several-steps list also depends on the model (its geometry)
         const int held = k == kMulti ? k | mc.tx << 8 | mc.ty << 16 : k;
         if (rec.region[r] == held)

@@ -64,6 +64,8 @@ struct MultiChoice {
 struct MultiSize {
     int nx, ny, count;  // count lattices of nx x ny sites
 };
+// (at most kMultiMaxTiles tiles in all)
+constexpr int kMultiMaxTiles = 16 * 256;
 MultiChoice multi_choose(int model, const MultiSize *sizes, int n);
 // The same for one lattice of lbm_step, T = 0 where another form is faster.
 MultiChoice multi_for_lattice(const lbm_params &p, const StepArgs &a);

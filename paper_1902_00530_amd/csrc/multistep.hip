@@ -52,9 +52,9 @@ MultiChoice multi_choose(int model, const MultiSize *sizes, int n)
             int64_t blocks = 0;
             for (int l = 0; l < n; ++l)
                 blocks += (int64_t)sizes[l].count * ((sizes[l].nx + tx - 1) / tx) * ((sizes[l].ny + ty - 1) / ty);
-            const int64_t per_cu = (blocks + 255) / 256;
-            if (per_cu > 16)
+            if (blocks > kMultiMaxTiles)
                 continue;
+            const int64_t per_cu = (blocks + 255) / 256;
             double t = 3.5;
             for (int T = 1; T <= t_max; ++T) {
                 const int w = tx + 2 * r * T, h = ty + 2 * r * T;
