@@ -955,7 +955,7 @@ struct GraphKey {
     int sample, add, rev, split;
     int max_nx;                   // the column means' grid
     int multi_T, multi_tx, multi_ty;  // geometry of the several-steps form
-    std::vector<int64_t> groups;  // tile ranges of the lattice groups
+    std::vector<int64_t> groups;  // tile ranges of the lattice groups and branches
     auto tie() const
     {
         return std::tie(device, tiles_main, tiles_one, lat, ctrl, mt, part, colpart, colmean, results, lattice, model,
@@ -1523,19 +1523,6 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     LBM_HIP_TRY(hipGetLastError());
     // lattice groups that fit the Infinity Cache (one group when resident)
     const std::vector<int> gfirst = resident ? std::vector<int>{0, n} : cache_groups(ps, n);
-    // the graph's launches depend on each lattice's tile ranges in the two lists
-    std::vector<int64_t> gkey;
-    for (size_t g = 0; g + 1 < gfirst.size() && !resident; ++g)
-        for (int l : {gfirst[g], split ? branch_cut(ps, gfirst[g], gfirst[g + 1]) : gfirst[g + 1]})
-            for (int k : {shape, one_shape}) {
-                const auto r = tile_range(k, l, gfirst[g + 1]);
-                gkey.push_back(r.first);
-                gkey.push_back(r.second);
-            }
-
-    // the order of the lattice groups in this call, and in the next one
-    const bool rev = !resident && gfirst.size() > 2 && rec.rev_next;
-    rec.rev_next = o->use_graph == 2 ? rev : (!resident && gfirst.size() > 2 && !rev);
     // first moments tile of each lattice (the list is in lattice order)
     std::vector<int> first_mt(n + 1, 0);
     for (int l = 0; l < n; ++l)
@@ -1543,6 +1530,22 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // rows of a sampling lane by the tiles of an average group, whatever the form
     // that the steps run in: a batch's sums round the same way in all of them
     const bool few_tiles = mom_few_tiles(nmt / (int64_t)(cache_groups(ps, n).size() - 1));
+    // the graph's launches depend on each group's and branch's tile ranges in the two
+    // lists and in the moments tiles (which do not follow from the former: 128 x 512
+    // and 256 x 256 sites are as many step tiles and half as many moments tiles)
+    std::vector<int64_t> gkey{few_tiles ? 1 : 0};
+    for (size_t g = 0; g + 1 < gfirst.size() && !resident; ++g)
+        for (int l : {gfirst[g], split ? branch_cut(ps, gfirst[g], gfirst[g + 1]) : gfirst[g + 1]})
+            for (int k : {shape, one_shape}) {
+                const auto r = tile_range(k, l, gfirst[g + 1]);
+                gkey.push_back(r.first);
+                gkey.push_back(r.second);
+                gkey.push_back(first_mt[l]);
+            }
+
+    // the order of the lattice groups in this call, and in the next one
+    const bool rev = !resident && gfirst.size() > 2 && rec.rev_next;
+    rec.rev_next = o->use_graph == 2 ? rev : (!resident && gfirst.size() > 2 && !rev);
     // the sample's moments of lattices first .. last - 1: right after their last
     // launch, while their state is still in the Infinity Cache
     auto moments = [&](hipStream_t on, int first, int last, int64_t steps) {
