@@ -52,7 +52,8 @@ typedef struct lbm_cnn_grads {
 size_t lbm_cnn_workspace_bytes(const lbm_cnn_shape *s);
 
 /* Forward pass.  x [n][cin][h][w]; a1, a2 [n][32][h][w] receive the hidden
- * activations (after ReLU, kept for the backward pass); y [n][3][h][w]. */
+ * activations (after ReLU, kept for the backward pass); y [n][3][h][w], which
+ * may lie in x's or a1's memory (then overwritten). */
 int32_t lbm_cnn_forward(const lbm_cnn_shape *s, const lbm_cnn_params *p, const float *x, float *a1, float *a2,
                         float *y, void *ws, size_t ws_bytes, void *stream);
 

@@ -1223,6 +1223,12 @@ static CnnWs cnn_layout(const lbm_cnn_shape *s, char *base)
     return L;
 }
 
+// whether a[na] and b[nb] share memory
+static bool overlap(const float *a, size_t na, const float *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)(b + nb) && (uintptr_t)b < (uintptr_t)(a + na);
+}
+
 static void launch_coarsen(const float *f, const float *const *bufs, int n, const StepArgs &a, int c, int cw, int chh,
                            float *out, int64_t out_stride, hipStream_t st)
 {
@@ -1353,12 +1359,18 @@ int32_t lbm_cnn_forward(const lbm_cnn_shape *s, const lbm_cnn_params *p, const f
             return fail(LBM_EINVAL, "null weight or bias");
     if (ws_bytes < cnn_layout(s, nullptr).total)
         return fail(LBM_EINVAL, "workspace smaller than lbm_cnn_workspace_bytes()");
+    const size_t px = (size_t)s->n * s->h * s->w;
+    // y in x's or a1's memory: a block writes its tile while others still read x
+    // around theirs or write a1, so y comes by way of the workspace
+    const bool aside = overlap(y, 3 * px, x, s->cin * px) || overlap(y, 3 * px, a1, 32 * px);
     CnnForward q{};
     q.x = x;
     q.a1 = a1;
     q.a2 = a2;
-    q.y = y;
+    q.y = aside ? cnn_layout(s, (char *)ws).dy : y;
     LBM_HIP_TRY(forward<kCnnRaw>(s, p, q, (hipStream_t)stream));
+    if (aside)
+        LBM_HIP_TRY(hipMemcpyAsync(y, q.y, 3 * px * sizeof(float), hipMemcpyDeviceToDevice, (hipStream_t)stream));
     return LBM_OK;
 }
 
