@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <string>
 
@@ -170,22 +171,75 @@ constexpr int64_t kGraphFirst = 512;
 // 16 / 24 rows: F32 512^2 4.79 / 5.62; 1000x752 10.3 / 9.8; 1024^2 12.7 / 13.0;
 // 1448^2 23.8 / 22.8; 2048^2 49.1 / 46.8; 4096^2 157 / 152; BF16 1000x752 10.3 /
 // 10.1; 2896^2 88.3 / 83.8.
+//
+// All that holds for lattices that fill their tiles.  A tile's first step is taken
+// on all of its rows and their ring, also past the lattice's edge, where blocks of
+// one step have 256 x 1 sites (local models) or rows that leave at once (MIPS); and
+// tile rows go to the eight XCDs in turn, so that a lattice of few tile rows uses few
+// of them.  Two steps are therefore taken only up to a ratio of the busiest XCD's
+// site bodies (step2_work; a lattice that fills its tiles has 1.1 to 1.2): 1.55, for
+// F32 local models 2.3, for states beyond the Infinity Cache, which two steps read
+// and write half as often, 2.2 at least, for the 16-bit MIPS 1.38 where they gain
+// little.  us per step, one / two: CIL F32 200000x18 36 / 91, 4000000x2 181 / 1307,
+// 5000x66 8.9 / 7.3; CIL BF16 200000x18 25 / 120; MIPS F32 200000x6 80 / 131.  16-bit
+// local lattices within that cache are bound by vector instructions from about 2^20
+// sites on, where only a width that leaves the 256-site blocks half empty pays
+// (0.85): CIL BF16 1448^2 13.5 / 14.5, 2896^2 41.5 / 44.8, 300x10000 25.2 / 20.6, and
+// 3400^2, beyond the cache, 72.2 / 63.4.  Lattices narrower than half a tile wrap
+// several times a load and keep one step: CIL F32 20x60000 16.2 / 19.1.
+static double step2_work(const lbm_params &p, int rows)
+{
+    const bool mips = p.model == LBM_MIPS;
+    auto up = [](int64_t n, int64_t d) { return (n + d - 1) / d; };
+    const int64_t ntx = up(p.nx, 64), nty = up(p.ny, rows), r = up(nty, 8);  // r: tile rows of the busiest XCD
+    const int ring = mips ? 2 : 1;
+    const int64_t first = (64 + 2 * ring) * (rows + 2 * ring) * r, second = 64 * std::min<int64_t>(rows * r, p.ny);
+    // a tile whose reads wrap around the lattice takes a fifth more
+    const int64_t ix = std::max(0, (p.nx - 64 - 2 * ring) / 64), iy = std::max(0, (p.ny - rows - 2 * ring) / rows);
+    const double wraps = 1.0 - (double)(ix * iy) / (double)(ntx * nty);
+    const double two = 0.5 * (double)(ntx * (first + second)) * (1.0 + 0.2 * wraps);
+    double one;
+    if (mips) {
+        const int one_rows = p.lattice == LBM_D2Q7 && ntx * up(p.ny, 16) < 512 ? 4 : 16;
+        one = (double)(ntx * 64 * std::min<int64_t>(one_rows * up(up(p.ny, one_rows), 8), p.ny));
+    } else {
+        const int64_t bx = p.nx >= 256 ? 256 : 64 * up(p.nx, 64), by = 256 / bx;
+        one = (double)(up(p.nx, bx) * bx * by * up(up(p.ny, by), 8));
+    }
+    return two / one;
+}
+
 int step2_rows(const lbm_params &p, const StepArgs &a)
 {
-    const bool q9 = p.lattice == LBM_D2Q9, f32 = p.storage == LBM_F32;
+    const bool q9 = p.lattice == LBM_D2Q9, f32 = p.storage == LBM_F32, mips = p.model == LBM_MIPS;
     const int64_t sites = (int64_t)p.nx * p.ny;
-    if (a.pitch != p.nx || (!q9 && (uint64_t)a.plane * 7ull >= (1ull << 30)))
+    if (a.pitch != p.nx || (!q9 && (uint64_t)a.plane * 7ull >= (1ull << 30)) || p.nx < 33)
         return 0;
-    if (p.model == LBM_MIPS) {
+    const uint64_t state = (uint64_t)sites * (q9 ? 9ull : 7ull) * (f32 ? 4ull : 2ull);
+    const bool cached = 2ull * state <= kStreamStateBytes;
+    int rows;
+    double most;
+    if (mips) {
         const int64_t lo = q9 ? 0 : 1 << 17, hi = f32 ? INT64_MAX : q9 ? 3 << 19 : 1 << 19;
         if (sites < lo || sites >= hi)
             return 0;
-        auto rounds = [&](int rows) { return (((p.nx + 63) / 64) * (int64_t)((p.ny + rows - 1) / rows) + 511) / 512; };
-        return q9 && (sites >= 1 << 21 || 24 * rounds(24) < 16 * rounds(16)) ? 24 : 16;
+        auto rounds = [&](int ty) { return (((p.nx + 63) / 64) * (int64_t)((p.ny + ty - 1) / ty) + 511) / 512; };
+        rows = q9 && (sites >= 1 << 21 || 24 * rounds(24) < 16 * rounds(16)) ? 24 : 16;
+        if (p.ny < rows)
+            return 0;
+        most = !cached ? 2.2 : !f32 && sites >= (q9 ? 1 << 19 : 3 << 16) ? 1.38 : 1.55;
+    } else if (f32) {
+        if (sites < 3 << 14)
+            return 0;
+        rows = sites < 1 << 21 ? 8 : 16;
+        most = 2.3;
+    } else {
+        if (sites < 1 << 17)
+            return 0;
+        rows = cached ? 8 : 16;
+        most = !cached ? 2.2 : sites > (q9 ? 1 << 20 : 5 << 18) ? 0.85 : 1.55;
     }
-    if (sites < (f32 ? 3 << 14 : 1 << 17))
-        return 0;
-    return sites < 1 << 21 ? 8 : 16;
+    return step2_work(p, rows) <= most ? rows : 0;
 }
 
 // n steps from buffer `from`, in as few launches as the context's form allows.

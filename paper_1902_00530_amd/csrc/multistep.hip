@@ -79,10 +79,12 @@ MultiChoice multi_choose(int model, const MultiSize *sizes, int n)
 // (best several-steps geometry against the other forms' best): CIL 384^2 2.70
 // against 2.91, 512^2 3.50 / 3.31; MIPS 256^2 2.36 / 3.45, 384^2 3.93 / 3.85;
 // D2Q9 CIL 384^2 3.17 / 3.66; D2Q9 MIPS 128^2 1.90 / 3.83, 384^2 4.27 / 4.34.
+// Two rows count as the four of the lowest tile in the local models (against one
+// step per launch: CIL 40000x2 3.8 / 4.0, 80000x2 7.9 / 6.2; MIPS 40000x2 9.0 / 15.7).
 MultiChoice multi_for_lattice(const lbm_params &p, const StepArgs &a)
 {
     const int64_t most = p.model != LBM_MIPS ? 5 << 15 : p.lattice == LBM_D2Q9 ? 1 << 17 : 3 << 15;
-    if (a.pitch != p.nx || (int64_t)p.nx * p.ny > most)
+    if (a.pitch != p.nx || (int64_t)p.nx * std::max(p.ny, p.model == LBM_MIPS ? 2 : 4) > most)
         return MultiChoice{};
     const MultiSize size{p.nx, p.ny, 1};
     return multi_choose(p.model, &size, 1);
