@@ -190,11 +190,11 @@ int32_t lbm_create(const lbm_params *p, void *f_a, void *f_b, int64_t pitch, con
 /* Enqueue n >= 0 steps on the context's stream (no synchronisation).  A launch
  * takes one step, or up to eight where that is faster (pitch nx; by size,
  * model and storage), which changes no value: every split of the same steps
- * into calls and launches gives the same state bit for bit.  From a context's
- * first call of 512 steps or more on, runs of 64 steps replay a HIP graph (one
- * per starting buffer); the remainder, shorter calls before that, and every
- * step while the caller is capturing the stream itself, are launched
- * directly.  Every launch reads its step index (the noise counter) from the
+ * into calls and launches gives the same state bit for bit.  Runs of 64 steps
+ * replay a HIP graph, one per starting buffer, each captured by the first call
+ * from that buffer of 512 steps or more (64 or more where a launch takes one
+ * step); the remainder, calls of 64 steps or more before that, and every step
+ * while the caller is capturing the stream itself, are launched directly.  Every launch reads its step index (the noise counter) from the
  * workspace's step clock, so graphs replay with unchanged arguments.  The
  * state ends in the buffer that n one-step launches, alternating between the
  * two, would leave it in; lbm_current_buffer() tells which.  Where the two
