@@ -1068,7 +1068,7 @@ static int32_t read_samples(const lbm_params *ps, int n, int64_t n_samples, cons
 {
     const size_t results = (size_t)n * n_samples;
     std::vector<double> res(results * 8);
-    HostResult host(results);
+    HostResult host(results, s);
     LBM_HIP_TRY(host.fetch(d_results, res.data(), results, s));
     bool bad = false;
     for (int l = 0; l < n; ++l)

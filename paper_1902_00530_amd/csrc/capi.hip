@@ -425,7 +425,7 @@ int32_t lbm_moments(lbm_ctx *c, float *rho, float *ux, float *uy, lbm_obs *obs)
         LBM_HIP_TRY(launch(nullptr));
         return LBM_OK;
     }
-    HostResult host(1);
+    HostResult host(1, c->stream);
     LBM_HIP_TRY(launch(host.ptr));
     double r[8];
     LBM_HIP_TRY(host.read(c->d_result, r, 1, c->stream));

@@ -93,12 +93,12 @@ hipError_t launch_add_density_q9(const lbm_params &p, const StepArgs &a, void *b
 size_t moments_scratch_doubles(const lbm_params &p);
 hipError_t launch_moments(const lbm_params &p, const StepArgs &a, const void *src, float *rho, float *ux,
                           float *uy, double *scratch, double *result, double *host, hipStream_t s);
-// Pinned host memory for `results` results of eight doubles, for one call (ptr
-// null where there is none left).
+// Pinned host memory for `results` results of eight doubles, for one call on
+// stream s (ptr null where there is none left, or s is being captured).
 struct HostResult {
     double *ptr = nullptr;
     int slot = 0, count = 0;
-    explicit HostResult(size_t results);
+    HostResult(size_t results, hipStream_t s);
     ~HostResult();
     HostResult(const HostResult &) = delete;
     HostResult &operator=(const HostResult &) = delete;

@@ -221,9 +221,14 @@ static std::mutex g_slot_mu;
 static double *g_slot_page;
 static bool g_slot_failed, g_slot_used[kHostSlots];
 
-HostResult::HostResult(size_t results)
+HostResult::HostResult(size_t results, hipStream_t s)
 {
-    if (results > (size_t)kHostSlots)
+    // a captured call fails where it waits for its result, with a kernel in the
+    // capture that writes to its slots: it gets none
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess)
+        (void)hipGetLastError();
+    if (results > (size_t)kHostSlots || cs != hipStreamCaptureStatusNone)
         return;
     std::lock_guard<std::mutex> lk(g_slot_mu);
     if (!g_slot_page && !g_slot_failed) {
