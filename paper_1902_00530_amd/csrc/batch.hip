@@ -612,6 +612,19 @@ static bool resident_fits(const lbm_params *ps, int n)
     return true;
 }
 
+// The shapes that a batch of this model and lattice may take (tuned among
+// themselves): MIPS 64x8 and 64x16 with two steps per launch, D2Q7 also 64x4 with
+// one, D2Q9 also 64x24; the local models shapes 0..4.
+static std::vector<int> batch_shapes(const lbm_params &p)
+{
+    if (p.model == LBM_MIPS)
+        return p.lattice == LBM_D2Q9 ? std::vector<int>{3, 4, kMipsShape24} : std::vector<int>{kMipsShape4, 3, 4};
+    std::vector<int> v(kNumTuned);
+    for (int k = 0; k < kNumTuned; ++k)
+        v[k] = k;
+    return v;
+}
+
 static int64_t count_tiles(const lbm_params *ps, int n, int tx, int ty)
 {
     int64_t c = 0;
@@ -1110,6 +1123,40 @@ int32_t lbm_sweep_tile_rows(const lbm_params *ps, int32_t n)
     return it->second.tile == kResident ? LBM_TILE_RESIDENT : kShapes[it->second.tile].ty;
 }
 
+// For the tests alone (in no header): the form and branches that a batch of these
+// lattices was tuned to, 0 where it was not yet; and the same set by hand, as if
+// tuned, for a form that such a batch may take (so that each form is reached on
+// every machine).  Forms: kShapes, kResident, kMulti.
+int32_t lbm_test_tuned(const lbm_params *ps, int32_t n, int32_t *form, int32_t *split)
+{
+    const int flags = ps && n > 0 ? sweep_flags(ps, n) : -1;
+    if (flags < 0 || !form || !split)
+        return fail(LBM_EINVAL, "invalid lbm_test_tuned arguments");
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    auto it = g_tuned.find(signature(ps, n, flags));
+    if (it == g_tuned.end())
+        return 0;
+    *form = it->second.shape;
+    *split = it->second.split;
+    return 1;
+}
+
+int32_t lbm_test_tune(const lbm_params *ps, int32_t n, int32_t form, int32_t split)
+{
+    const int flags = ps && n > 0 ? sweep_flags(ps, n) : -1;
+    if (flags < 0 || split < 0 || split > 1)
+        return fail(LBM_EINVAL, "invalid lbm_test_tune arguments");
+    const std::vector<int> shapes = batch_shapes(ps[0]);
+    const bool tile = std::count(shapes.begin(), shapes.end(), form) > 0;
+    if (!tile && !(form == kResident && resident_fits(ps, n)) && !(form == kMulti && multi_for_batch(ps, n).T))
+        return fail(LBM_EINVAL, "a form that this batch may not take");
+    if (split && !(tile && kShapes[form].steps == 2 && n > 1))
+        return fail(LBM_EINVAL, "branches that this form does not take");
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    g_tuned[signature(ps, n, flags)] = Tuned{form, split, named_shape(form) ? form : shapes[0]};
+    return LBM_OK;
+}
+
 size_t lbm_sweep_workspace_bytes(const lbm_params *ps, int32_t n, int64_t n_samples)
 {
     if (!ps || n <= 0 || n_samples < 0)
@@ -1170,15 +1217,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // the sweep starts), so the state is unchanged.
     int shape = -1, split = 0;
     const bool mips = ps[0].model == LBM_MIPS, q9 = ps[0].lattice == LBM_D2Q9;
-    // the shapes this model and lattice may take (tuned among themselves):
-    // MIPS 64x8 and 64x16 with two steps per launch and, D2Q7 only, 64x4
-    // with one; the local models shapes 0..4
-    std::vector<int> cands;
-    if (mips)
-        cands = q9 ? std::vector<int>{3, 4, kMipsShape24} : std::vector<int>{kMipsShape4, 3, 4};
-    else
-        for (int k = 0; k < kNumTuned; ++k)
-            cands.push_back(k);
+    std::vector<int> cands = batch_shapes(ps[0]);
     for (int k : cands)
         if (named_shape(k) && o->tile_rows == kShapes[k].ty)
             shape = k;
