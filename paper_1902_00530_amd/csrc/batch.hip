@@ -940,9 +940,11 @@ static hipError_t launch_batch_step(int lattice, int model, int storage, int fla
 // lattice sizes + model + flags), kept for the life of the process.
 static std::mutex g_tune_mu;
 struct Tuned {
-    int shape;  // the fastest form
-    int split;  // its lattice groups run as two branches
-    int tile;   // the fastest among the forms that tile_rows names (named_shape)
+    int shape;   // the fastest form
+    int split;   // its lattice groups run as two branches
+    int direct;  // the fastest form without branches, for direct launches
+    int tile;    // the fastest among the forms that tile_rows names (named_shape)
+    bool branches;  // forms with branches were timed too (by a call that runs graphs)
 };
 static std::map<std::string, Tuned> g_tuned;
 
@@ -1124,7 +1126,8 @@ int32_t lbm_sweep_tile_rows(const lbm_params *ps, int32_t n)
 }
 
 // For the tests alone (in no header): the form and branches that a batch of these
-// lattices was tuned to, 0 where it was not yet; and the same set by hand, as if
+// lattices was tuned to, 0 where it was not yet (1: by a call without graphs, which
+// times no branches, 2: by one with them); and the same set by hand, as if
 // tuned, for a form that such a batch may take (so that each form is reached on
 // every machine).  Forms: kShapes, kResident, kMulti.
 int32_t lbm_test_tuned(const lbm_params *ps, int32_t n, int32_t *form, int32_t *split)
@@ -1138,7 +1141,7 @@ int32_t lbm_test_tuned(const lbm_params *ps, int32_t n, int32_t *form, int32_t *
         return 0;
     *form = it->second.shape;
     *split = it->second.split;
-    return 1;
+    return it->second.branches ? 2 : 1;
 }
 
 int32_t lbm_test_tune(const lbm_params *ps, int32_t n, int32_t form, int32_t split)
@@ -1153,7 +1156,7 @@ int32_t lbm_test_tune(const lbm_params *ps, int32_t n, int32_t form, int32_t spl
     if (split && !(tile && kShapes[form].steps == 2 && n > 1))
         return fail(LBM_EINVAL, "branches that this form does not take");
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[signature(ps, n, flags)] = Tuned{form, split, named_shape(form) ? form : shapes[0]};
+    g_tuned[signature(ps, n, flags)] = Tuned{form, split, form, named_shape(form) ? form : shapes[0], true};
     return LBM_OK;
 }
 
@@ -1242,9 +1245,10 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     if (shape < 0) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(sig);
-        if (it != g_tuned.end()) {
-            shape = it->second.shape;
-            split = it->second.split;
+        // what a call without graphs has tuned lacks the branched forms
+        if (it != g_tuned.end() && (it->second.branches || !o->use_graph)) {
+            shape = o->use_graph ? it->second.shape : it->second.direct;
+            split = o->use_graph ? it->second.split : 0;
         }
     }
     hipStream_t s = (hipStream_t)stream;
@@ -1433,8 +1437,8 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
         return {count(0, l), count(l, last)};
     };
     if (shape < 0) {
-        float best = 1e30f, best_tile = 1e30f;
-        int tile = -1;
+        float best = 1e30f, best_direct = 1e30f, best_tile = 1e30f;
+        int direct = -1, tile = -1;
         struct EventPair {  // destroyed on every exit path
             hipEvent_t a = nullptr, b = nullptr;
             ~EventPair()
@@ -1527,13 +1531,17 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 shape = k;
                 split = form.second;
             }
+            if (!form.second && ms < best_direct) {
+                best_direct = ms;
+                direct = k;
+            }
             if (named_shape(k) && !form.second && ms < best_tile) {
                 best_tile = ms;
                 tile = k;
             }
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[sig] = Tuned{shape, split, tile};
+        g_tuned[sig] = Tuned{shape, split, direct, tile, o->use_graph != 0 || n == 1};
     }
     // the chosen list, and for a two-step shape the list of a one-step shape
     // (256x1; MIPS 64x4, D2Q9 MIPS 64x16) for the single steps that keep the launch count's

@@ -116,6 +116,19 @@ def test_two_orders_on_two_branches(L):
             assert torch.equal(one.state(l), two.state(l)), (order[0], l)
 
 
+def test_direct_launches_first(L):
+    """What a call without graphs has tuned, which times no branches, is not what
+    graphs run by afterwards; a call without graphs after that takes no branches."""
+    got, ref = _batch(L, 7, "cil", [(200, 130), (330, 94), (128, 100)])
+    form, split = ctypes.c_int32(-1), ctypes.c_int32(-1)
+    for use_graph, known in ((0, 1), (0, 1), (1, 2), (0, 2), (1, 2)):
+        a = got.run(20, use_graph=use_graph)
+        assert L._lib.lbm_test_tuned(got.params, got.n, ctypes.byref(form), ctypes.byref(split)) == known
+        assert a == ref.run(20, tile_rows=16)
+        for l in range(3):
+            assert torch.equal(got.state(l), ref.state(l)), (use_graph, l)
+
+
 def test_refused_forms(L):
     b, _ = _batch(L, 7, "cil", WIDE[:2])
     for form, split in ((RESIDENT, 0), (MULTI, 0), (5, 0), (6, 0), (7, 0), (0, 1), (10, 0), (-1, 0), (3, 2)):
