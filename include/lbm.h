@@ -375,7 +375,8 @@ int32_t lbm_sweep_groups(const lbm_params *ps, int32_t n);
  * lbm_sweep_samples reads them.  The
  * steps of lattice l use its own seed and the noise counters
  * step0 .. step0 + n_steps - 1, so a lattice gives the same result as
- * lbm_step on its own (bit for bit).  Afterwards lattice l's state is in
+ * lbm_step on its own (bit for bit), and its samples are those of lbm_moments
+ * whatever the batch.  Afterwards lattice l's state is in
  * bufs[2l + (n_steps & 1)].  With out != NULL, synchronises the stream at
  * the end.  Errors: LBM_EINVAL for the conditions above, LBM_EUNSUPPORTED for
  * other storages or lattices, LBM_ENONFINITE if a sample saw a non-finite

@@ -1574,8 +1574,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     std::vector<int> first_mt(n + 1, 0);
     for (int l = 0; l < n; ++l)
         first_mt[l + 1] = first_mt[l] + lat[l].mt_count;
-    // rows of a sampling lane by the tiles of an average group, whatever the form
-    // that the steps run in: a batch's sums round the same way in all of them
+    // rows of a sampling lane by the tiles of an average group (the sums are the same)
     const bool few_tiles = mom_few_tiles(nmt / (int64_t)(cache_groups(ps, n).size() - 1));
     // the graph's launches depend on each group's and branch's tile ranges in the two
     // lists and in the moments tiles (which do not follow from the former: 128 x 512

@@ -22,8 +22,8 @@ inline bool mom_few_tiles(int64_t tiles) { return tiles <= 1024; }
 
 template <int R>
 struct MomLds {
-    double col[kMomRows / R][kMomCols];
-    double part[mom_lanes(R) / 64][kMomParts];
+    double acc[R < kMomRows ? kMomParts : 1][kMomCols];  // the columns' sums so far
+    double part[kMomCols / 64][kMomParts];
 };
 
 __device__ __forceinline__ double mom_wave_sum(double v)
@@ -37,25 +37,37 @@ __device__ __forceinline__ double mom_wave_sum(double v)
 // The tile at column x0 and row y0: load(f, x, y) the streamed populations of a
 // site, moments(f, rho, jx, jy) its fields, out(x, y, rho, jx, jy) takes them;
 // part: the tile's five sums, col: the tile's column sums of rho (col[x - x0]).
-// Fixed order: rows of a lane, then lanes of a wave, then waves; for a column
-// the rows of a lane, then its lanes.
+// One order for every R, so that a lattice's sums do not depend on how many tiles
+// its batch has: the rows of a column in turn (R < 16: passed on from one lane's rows
+// to the next lane's), then the columns of a wave, then waves.
 template <int R, int Q, class Load, class Moments, class Out>
 __device__ __forceinline__ void moments_tile(MomLds<R> &lds, int nx, int ny, int x0, int y0, Load load, Moments moments,
                                              Out out, double *__restrict__ part, double *__restrict__ col)
 {
-    constexpr int B = 4, NW = mom_lanes(R) / 64;  // rows loaded at a time, waves
+    constexpr int B = 4, G = kMomRows / R;  // rows loaded at a time, lanes of a column
+    static_assert(G == 1 || R == B, "one load of rows a lane, or every row");
     const int c = threadIdx.x % kMomCols, group = threadIdx.x / kMomCols;
     const int x = x0 + c;
-    double acc[kMomParts] = {0.0, 0.0, 0.0, 0.0, 0.0}, sum = 0.0;
+    double acc[kMomParts] = {0.0, 0.0, 0.0, 0.0, 0.0}, v[B][kMomParts];
+    int rows = 0;  // of the B last loaded
+    auto add = [&]() {
+#pragma unroll
+        for (int r = 0; r < B; ++r)
+            if (r < rows)
+#pragma unroll
+                for (int k = 0; k < kMomParts; ++k)
+                    acc[k] += v[r][k];
+    };
     if (x < nx)
         for (int y1 = y0 + group * R; y1 < min(y0 + group * R + R, ny); y1 += B) {
             float f[B][Q];
 #pragma unroll
             for (int r = 0; r < B; ++r)
                 load(f[r], x, min(y1 + r, ny - 1));
+            rows = min(B, ny - y1);
 #pragma unroll
             for (int r = 0; r < B; ++r) {
-                if (y1 + r >= ny)
+                if (r >= rows)
                     break;
                 float rho, jx, jy;
                 moments(f[r], rho, jx, jy);
@@ -63,44 +75,48 @@ __device__ __forceinline__ void moments_tile(MomLds<R> &lds, int nx, int ny, int
 #pragma unroll
                 for (int i = 0; i < Q; ++i)
                     finite = finite && isfinite(f[r][i]);
-                const double dr = rho, dx = jx, dy = jy;
-                acc[0] += dr;
-                acc[1] += dx;
-                acc[2] += dy;
-                acc[3] += sqrt(dx * dx + dy * dy);
-                acc[4] += finite ? 0.0 : 1.0;
-                sum += dr;
+                const double dx = jx, dy = jy;
+                v[r][0] = rho;
+                v[r][1] = dx;
+                v[r][2] = dy;
+                v[r][3] = sqrt(dx * dx + dy * dy);
+                v[r][4] = finite ? 0.0 : 1.0;
                 out(x, y1 + r, rho, jx, jy);
             }
+            if (G == 1)
+                add();
         }
-    if (R < kMomRows)
-        lds.col[group][c] = sum;
-    else if (x < nx)
-        col[c] = sum;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < kMomParts; ++k)
-        acc[k] = mom_wave_sum(acc[k]);
-    if (lane == 0)
+    for (int g = 0; g < G && G > 1; ++g) {
+        if (group == g) {
+            if (g > 0)
+#pragma unroll
+                for (int k = 0; k < kMomParts; ++k)
+                    acc[k] = lds.acc[k][c];
+            add();
+            if (g < G - 1)
+#pragma unroll
+                for (int k = 0; k < kMomParts; ++k)
+                    lds.acc[k][c] = acc[k];
+        }
+        if (g < G - 1)
+            __syncthreads();
+    }
+    if (group == G - 1) {
+        if (x < nx)
+            col[c] = acc[0];
 #pragma unroll
         for (int k = 0; k < kMomParts; ++k)
-            lds.part[wave][k] = acc[k];
+            acc[k] = mom_wave_sum(acc[k]);
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int k = 0; k < kMomParts; ++k)
+                lds.part[c >> 6][k] = acc[k];
+    }
     __syncthreads();
-    if (R < kMomRows && group == 0 && x < nx) {
-        double v = lds.col[0][c];
-#pragma unroll
-        for (int g = 1; g < kMomRows / R; ++g)
-            v += lds.col[g][c];
-        col[c] = v;
-    }
-    if (threadIdx.x >= mom_lanes(R) - kMomParts) {
-        const int k = threadIdx.x - (mom_lanes(R) - kMomParts);
-        double v = lds.part[0][k];
-#pragma unroll
-        for (int w = 1; w < NW; ++w)
-            v += lds.part[w][k];
-        part[k] = v;
-    }
+    if (threadIdx.x < kMomParts)
+        part[threadIdx.x] = ((lds.part[0][threadIdx.x] + lds.part[1][threadIdx.x]) + lds.part[2][threadIdx.x]) +
+                            lds.part[3][threadIdx.x];
 }
 
 }  // namespace lbm

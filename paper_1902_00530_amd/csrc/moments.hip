@@ -28,32 +28,6 @@ size_t moments_scratch_doubles(const lbm_params &p)
     return blocks * kMomParts + (size_t)mom_grid_y(p) * p.nx + (size_t)p.nx;
 }
 
-// Block-wide sums of N doubles, fixed order; valid in every thread.
-template <int N, int WAVES>
-__device__ __forceinline__ void block_sum(double v[N], double (*lds)[N])
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        v[k] = mom_wave_sum(v[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < N; ++k)
-            lds[wave][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < N) {
-        double s = lds[0][threadIdx.x];
-#pragma unroll
-        for (int w = 1; w < WAVES; ++w)
-            s += lds[w][threadIdx.x];
-        lds[0][threadIdx.x] = s;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        v[k] = lds[0][k];
-}
-
 // The triangular (Q = 7) or the square (Q = 9) lattice, R rows a lane.
 template <int S, int Q, int R>
 __global__ __launch_bounds__(mom_lanes(R)) void k_moments(const typename Store<S>::T *__restrict__ src, StepArgs a,
@@ -110,15 +84,14 @@ __global__ __launch_bounds__(256) void k_column_means(const double *__restrict__
     colmean[x] = c / (double)ny;
 }
 
-// One block: totals of the tile partials and of the column means in a fixed
-// order, then the variance of the column means over x; with `host`, the result
-// also goes there (host memory that the device can write).  OWN: the column
-// means are summed here, in registers (nx <= kFinLanes, and few enough partials
-// that one CU reads them in the time of a launch, kFinOwn).  1024^2: 11.0 us
-// with the write to the host, against 4.3 and 5.4 for two launches and 4.5 for a
-// copy; with its fields, lbm_moments 51.5 -> 38.3 us, 64^2 41.6 -> 29.0, 4000 x
-// 3000 151 -> 133.
-constexpr int kFinLanes = 1024;
+// One block: totals of the tile partials and of the column means, then the variance
+// of the column means over x; with `host`, the result also goes there (host memory
+// that the device can write).  OWN: the column means are summed here (nx <=
+// kFinLanes, and few enough partials that one CU reads them in the time of a launch,
+// kFinOwn).  The order of every sum is that of k_batch_final, 256 lanes: lane t takes
+// terms t, t + 256, ..., then lanes of a wave, then waves.  Here each quarter of the
+// block takes one of the tiles' first four sums.
+constexpr int kFinLanes = 1024, kFinStride = 256;
 constexpr int64_t kFinOwn = 1 << 16;
 
 template <bool OWN>
@@ -126,46 +99,60 @@ __global__ __launch_bounds__(kFinLanes) void k_moments_final(const double *__res
                                                              const double *__restrict__ col, int nrowblocks, int nx,
                                                              int ny, double *__restrict__ result, double *host)
 {
-    __shared__ double lds[kFinLanes / 64][kMomParts + 1];
-    const int tid = threadIdx.x;
-    double v[kMomParts + 1] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, own = 0.0;
-    for (int b = tid; b < nblocks; b += kFinLanes)
-#pragma unroll
-        for (int k = 0; k < kMomParts; ++k)
-            v[k] += part[(int64_t)b * kMomParts + k];
-    if (OWN) {
-        if (tid < nx) {
+    __shared__ double lds[kMomParts + 2][kFinStride / 64];
+    __shared__ double means[OWN ? kFinLanes : 1];
+    const int tid = threadIdx.x, t = tid % kFinStride, quarter = tid / kFinStride;
+    auto wave_sum = [&](double v, int k) {
+        v = mom_wave_sum(v);
+        if ((tid & 63) == 0)
+            lds[k][t >> 6] = v;
+    };
+    auto total = [&](int k) { return ((lds[k][0] + lds[k][1]) + lds[k][2]) + lds[k][3]; };
+    double own = 0.0;
+    if (OWN && tid < nx) {
 #pragma unroll 32
-            for (int r = 0; r < nrowblocks; ++r)
-                own += col[(int64_t)r * nx + tid];
-            own /= (double)ny;
-            v[kMomParts] = own;
-        }
-    } else {
-#pragma unroll 4
-        for (int x = tid; x < nx; x += kFinLanes)
-            v[kMomParts] += col[x];
+        for (int r = 0; r < nrowblocks; ++r)
+            own += col[(int64_t)r * nx + tid];
+        means[tid] = own / (double)ny;
     }
-    block_sum<kMomParts + 1, kFinLanes / 64>(v, lds);
-    const double mean = v[kMomParts] / (double)nx;
-    double q[1] = {0.0};
-    if (OWN) {
-        if (tid < nx)
-            q[0] = (own - mean) * (own - mean);
-    } else {
+    double v = 0.0, last = 0.0;
 #pragma unroll 4
-        for (int x = tid; x < nx; x += kFinLanes) {
-            const double d = col[x] - mean;
-            q[0] += d * d;
-        }
+    for (int b = t; b < nblocks; b += kFinStride)
+        v += part[(int64_t)b * kMomParts + quarter];
+    wave_sum(v, quarter);
+    if (quarter == 1) {
+#pragma unroll 4
+        for (int b = t; b < nblocks; b += kFinStride)
+            last += part[(int64_t)b * kMomParts + 4];
+        wave_sum(last, 4);
     }
-    __shared__ double lds1[kFinLanes / 64][1];
-    block_sum<1, kFinLanes / 64>(q, lds1);
+    if (OWN)
+        __syncthreads();
+    const double *cm = OWN ? means : col;
+    if (quarter == 0) {
+        double m = 0.0;
+#pragma unroll 8
+        for (int x = t; x < nx; x += kFinStride)
+            m += cm[x];
+        wave_sum(m, kMomParts);
+    }
+    __syncthreads();
+    const double mean = total(kMomParts) / (double)nx;
+    if (quarter == 0) {
+        double q = 0.0;
+#pragma unroll 8
+        for (int x = t; x < nx; x += kFinStride) {
+            const double d = cm[x] - mean;
+            q += d * d;
+        }
+        wave_sum(q, kMomParts + 1);
+    }
+    __syncthreads();
     if (tid < 8) {
-        double r = tid == 5 ? mean : tid == 6 ? q[0] / (double)nx : 0.0;
-#pragma unroll
-        for (int k = 0; k < kMomParts; ++k)
-            r = tid == k ? v[k] : r;
+        const double r = tid < kMomParts ? total(tid)
+                         : tid == 5      ? mean
+                         : tid == 6      ? total(kMomParts + 1) / (double)nx
+                                         : 0.0;
         result[tid] = r;
         if (host)
             host[tid] = r;
