@@ -172,10 +172,10 @@ static int64_t steps_per_launch(const lbm_ctx *c) { return c->multi.T ? c->multi
 // D2Q9 MIPS also has 64 x 24 tiles: their ring costs 24% more collisions in the
 // first step against 33% at 16 rows, and two blocks fit a CU either way.  They
 // win wherever the last round of 512 blocks is not much emptier: above 2^21
-// sites, and below where the rounds times the rows are fewer.  us per step,
-// 16 / 24 rows: F32 512^2 4.79 / 5.62; 1000x752 10.3 / 9.8; 1024^2 12.7 / 13.0;
-// 1448^2 23.8 / 22.8; 2048^2 49.1 / 46.8; 4096^2 157 / 152; BF16 1000x752 10.3 /
-// 10.1; 2896^2 88.3 / 83.8.
+// sites (F32; 16-bit lattices take one step per launch there), and below where
+// the rounds times the rows are fewer.  us per step, 16 / 24 rows: F32 512^2 5.0 /
+// 5.8; 721x720 9.3 / 8.7; 1024^2 12.3 / 12.7; 1448^2 22.0 / 21.4; 2048^2 46.6 / 44.4;
+// 4096^2 161 / 152; BF16 721x720 9.8 / 9.4; 1448x724 14.8 / 13.5.
 //
 // All that holds for lattices that fill their tiles.  A tile's first step is taken
 // on all of its rows and their ring, also past the lattice's edge, where blocks of
@@ -185,8 +185,8 @@ static int64_t steps_per_launch(const lbm_ctx *c) { return c->multi.T ? c->multi
 // site bodies (step2_work; a lattice that fills its tiles has 1.1 to 1.2): 1.55, for
 // F32 local models 2.3, for states beyond the Infinity Cache, which two steps read
 // and write half as often, 2.2 at least, for the 16-bit MIPS 1.38 where they gain
-// little.  us per step, one / two: CIL F32 200000x18 36 / 91, 4000000x2 181 / 1307,
-// 5000x66 8.9 / 7.3; CIL BF16 200000x18 25 / 120; MIPS F32 200000x6 80 / 131.  16-bit
+// little.  us per step, one / two: CIL F32 100000x18 19.6 / 29.0, 100000x2 7.1 / 22.3,
+// 5000x66 5.8 / 4.8; CIL BF16 100000x18 14.9 / 37.1; MIPS F32 400000x6 151 / 260.  16-bit
 // local lattices within that cache are bound by vector instructions from about 2^20
 // sites on, where only a width that leaves the 256-site blocks half empty pays
 // (0.85): CIL BF16 1448^2 13.5 / 14.5, 2896^2 41.5 / 44.8, 300x10000 25.2 / 20.6, and

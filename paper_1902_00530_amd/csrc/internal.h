@@ -34,8 +34,8 @@ int step_flags(const StepArgs &a);
 // and the next index goes to the other slot.
 hipError_t launch_step(const lbm_params &p, const StepArgs &a, const void *src, void *dst, StepClock *clk, int slot,
                        hipStream_t s);
-// Tile rows (8, 16; D2Q9 MIPS also 24) of the two-step kernels for this
-// lattice, 0 where one step per launch is taken.
+// Tile rows (local models 8, 16; MIPS 16, on D2Q9 also 24) of the two-step kernels
+// for this lattice, 0 where one step per launch is taken.
 int step2_rows(const lbm_params &p, const StepArgs &a);
 // Two steps src -> dst in one launch on 64 x rows tiles; the clock advances by
 // two.

@@ -40,10 +40,7 @@ static hipError_t launch_sf(const lbm_params &p, const StepArgs &a, int ty, cons
     const int stream = 2ull * Planes<S>::bytes(a.plane) > kStreamStateBytes;
     const dim3 grd = row_group_grid((p.nx + 63) / 64, (p.ny + ty - 1) / ty);
     if (p.model == kMips) {
-        if (ty == 8)
-            hipLaunchKernelGGL((k_step2_mips<S, F, 8, 4>), grd, dim3(256), 0, s, src, dst, a, clk, slot, stream);
-        else
-            hipLaunchKernelGGL((k_step2_mips<S, F, 16, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
+        hipLaunchKernelGGL((k_step2_mips<S, F, 16, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
     } else if (p.model == kCil) {
         if (ty == 8)
             hipLaunchKernelGGL((k_step2_local<kCil, S, F, 8>), grd, dim3(256), 0, s, src, dst, a, clk, slot, stream);

@@ -43,25 +43,24 @@ static hipError_t launch_q9_sf(const lbm_params &p, const StepArgs &a, int rows,
     const dim3 grd = row_group_grid((p.nx + 63) / 64, (p.ny + rows - 1) / rows);
     const T *in = (const T *)src;
     T *out = (T *)dst;
-    // TY rows on NW waves
-    auto go = [&](auto ty, auto nw) {
-        constexpr int TY = decltype(ty)::value, NW = decltype(nw)::value;
-        const dim3 blk(64 * NW);
-        if (p.model == kMips)
-            hipLaunchKernelGGL((k_q9_step2_mips<S, F, TY, NW>), grd, blk, 0, s, src, dst, a, clk, slot, stream);
-        else if (p.model == kCil)
-            hipLaunchKernelGGL((k_q9_step2_local<kCil, S, F, TY, NW>), grd, blk, 0, s, in, out, a, clk, slot, stream);
+    if (p.model == kMips) {
+        if (rows == 16)
+            hipLaunchKernelGGL((k_q9_step2_mips<S, F, 16, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
         else
-            hipLaunchKernelGGL((k_q9_step2_local<kPassive, S, F, TY, NW>), grd, blk, 0, s, in, out, a, clk, slot, stream);
+            hipLaunchKernelGGL((k_q9_step2_mips<S, F, 24, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
+        return hipGetLastError();
+    }
+    auto local = [&](auto model) {
+        constexpr int M = decltype(model)::value;
+        if (rows == 8)
+            hipLaunchKernelGGL((k_q9_step2_local<M, S, F, 8, 4>), grd, dim3(256), 0, s, in, out, a, clk, slot, stream);
+        else
+            hipLaunchKernelGGL((k_q9_step2_local<M, S, F, 16, 4>), grd, dim3(256), 0, s, in, out, a, clk, slot, stream);
     };
-    if (rows == 8)
-        go(IntTag<8>{}, IntTag<4>{});
-    else if (p.model != kMips)
-        go(IntTag<16>{}, IntTag<4>{});
-    else if (rows == 16)
-        go(IntTag<16>{}, IntTag<8>{});
+    if (p.model == kCil)
+        local(IntTag<kCil>{});
     else
-        hipLaunchKernelGGL((k_q9_step2_mips<S, F, 24, 8>), grd, dim3(512), 0, s, src, dst, a, clk, slot, stream);
+        local(IntTag<kPassive>{});
     return hipGetLastError();
 }
 
