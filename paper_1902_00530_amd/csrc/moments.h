@@ -1,12 +1,13 @@
 // Sums of one moments tile (256 columns x 16 rows of a lattice), shared by the
 // single-lattice (moments.hip) and the batched (batch.hip) sampling kernels.
 //
-// A lane takes R rows of a column, four rows' populations loaded before the
-// first is used.  R = 4, 1024 lanes: where the tiles are few (mom_few_tiles) and
-// one lane walking 16 rows would wait on memory with one wave a SIMD: 1024^2
-// with its fields written (42 MB, 8.5 us at the rate of a large copy) 17.4 us
-// with 16 rows, one load at a time, 11.0 with four.  R = 16, 256 lanes, takes a
-// quarter of the lane sums: 4000 x 3000 in BF16 80 us against 92.
+// A lane takes R rows of a column.  R = 4, 1024 lanes, every row loaded before the
+// first is used: where the tiles are no more than the CUs (mom_few_tiles) and one lane
+// walking 16 rows would wait on memory with one wave a SIMD.  R = 16, 256 lanes, row by
+// row, where more tiles hide each other's loads: it needs half the registers and passes
+// no sums between lanes.  lbm_moments with its fields, us, R = 16 / 4: F32 512^2 (64
+// tiles) 16.4 / 13.1, 1024^2 (256) 26.1 / 21.1, 1024x1280 (320) 25.4 / 25.4, 1448^2 (546)
+// 31.8 / 37.1, 2000^2 (1000) 46.5 / 52.4; BF16 1024^2 25.5 / 20.1, 2000^2 40.1 / 47.6.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,8 +18,8 @@ constexpr int kMomCols = 256, kMomRows = 16;  // columns and rows of a tile
 constexpr int kMomParts = 5;                   // M, Jx, Jy, sum |j|, nonfinite
 
 constexpr int mom_lanes(int R) { return kMomCols * kMomRows / R; }
-// four rows a lane: up to four tiles a CU
-inline bool mom_few_tiles(int64_t tiles) { return tiles <= 1024; }
+// four rows a lane: up to a tile a CU
+inline bool mom_few_tiles(int64_t tiles) { return tiles <= 256; }
 
 template <int R>
 struct MomLds {
@@ -44,8 +45,7 @@ template <int R, int Q, class Load, class Moments, class Out>
 __device__ __forceinline__ void moments_tile(MomLds<R> &lds, int nx, int ny, int x0, int y0, Load load, Moments moments,
                                              Out out, double *__restrict__ part, double *__restrict__ col)
 {
-    constexpr int B = 4, G = kMomRows / R;  // rows loaded at a time, lanes of a column
-    static_assert(G == 1 || R == B, "one load of rows a lane, or every row");
+    constexpr int G = kMomRows / R, B = G == 1 ? 1 : R;  // lanes of a column, rows loaded at a time
     const int c = threadIdx.x % kMomCols, group = threadIdx.x / kMomCols;
     const int x = x0 + c;
     double acc[kMomParts] = {0.0, 0.0, 0.0, 0.0, 0.0}, v[B][kMomParts];
