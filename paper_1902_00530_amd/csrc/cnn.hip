@@ -1065,9 +1065,43 @@ __global__ void k_fill_channel(float *__restrict__ x, int n, int C, int ch, int6
 // and put their rho, jx, jy into LDS, where one lane per cell and field adds
 // its cell's sites row by row.  One lane per cell loading its own sites read
 // 7 c^2 scattered values in turn: 64 lattices of 256^2 in cells of 8 x 8 (117 MB)
-// 61 -> 21 us.
+// 61 -> 21 us.  Cells of one site, of two a side (of states that the caches hold) and
+// of four on lattices narrower than a wave take a lane each all the same
+// (k_coarsen_cells): there its loads are within a line of their neighbours' and LDS and
+// barriers cost more.  us, a lane a cell / rows: 4096^2, c = 1 115 / 185, c = 2 110 / 100;
+// 1024^2, c = 2 7.5 / 8.4; 64x8192, c = 2 5.5 / 9.4; 256^2, c = 2 3.7 / 4.3, c = 4 5.9 /
+// 4.7; 16x30000, c = 4 16.4 / 17.9.  The sums and their order are the same.
 // ---------------------------------------------------------------------------
 constexpr int kCoarsenCols = 256, kCoarsenRows = 4;
+
+__global__ __launch_bounds__(kCoarsenCols) void k_coarsen_cells(const float *f, const float *const *__restrict__ bufs,
+                                                                StepArgs a, int cs, int cw, int chh,
+                                                                float *__restrict__ out, int64_t out_stride)
+{
+    const int cx = blockIdx.x * kCoarsenCols + threadIdx.x, cy = blockIdx.y;
+    if (cx >= cw)
+        return;
+    if (bufs)
+        f = bufs[blockIdx.z];
+    float sums[3] = {0.0f, 0.0f, 0.0f};
+    for (int dy = 0; dy < cs; ++dy)
+        for (int dx = 0; dx < cs; ++dx) {
+            const PullSources32 g = pull_sources32(a, cx * cs + dx, cy * cs + dy);
+            float v[7], m[3];
+#pragma unroll
+            for (int i = 0; i < 7; ++i)
+                v[i] = ld32(f + (size_t)i * (uint32_t)a.plane, g.idx[i]);
+            site_moments(v, m[0], m[1], m[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                sums[k] += m[k];
+        }
+    const float inv = 1.0f / (float)(cs * cs);
+    float *o = out + (int64_t)blockIdx.z * out_stride + (size_t)cy * cw + cx;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        o[(size_t)k * chh * cw] = sums[k] * inv;
+}
 
 __global__ __launch_bounds__(kCoarsenCols) void k_coarsen(const float *f, const float *const *__restrict__ bufs,
                                                           StepArgs a, int cs, int cw, int chh, float *__restrict__ out,
@@ -1232,6 +1266,11 @@ static bool overlap(const float *a, size_t na, const float *b, size_t nb)
 static void launch_coarsen(const float *f, const float *const *bufs, int n, const StepArgs &a, int c, int cw, int chh,
                            float *out, int64_t out_stride, hipStream_t st)
 {
+    if (c == 1 || (c == 2 && (int64_t)n * a.nx * a.ny < 1 << 23) || (c == 4 && a.nx < 64)) {
+        hipLaunchKernelGGL(k_coarsen_cells, dim3((cw + kCoarsenCols - 1) / kCoarsenCols, chh, n), dim3(kCoarsenCols), 0,
+                           st, f, bufs, a, c, cw, chh, out, out_stride);
+        return;
+    }
     const int per = std::max(1, kCoarsenCols / c);
     hipLaunchKernelGGL(k_coarsen, dim3((cw + per - 1) / per, chh, n), dim3(kCoarsenCols), 0, st, f, bufs, a, c, cw, chh,
                        out, out_stride);
