@@ -129,6 +129,24 @@ def test_direct_launches_first(L):
             assert torch.equal(got.state(l), ref.state(l)), (use_graph, l)
 
 
+def test_first_call(L):
+    """A batch's first call times the forms, each a few times at most: two 4096 x 4096
+    lattices, where that is nearly all GPU time, within 20 calls' time (36 with six
+    replays of every form and its branches)."""
+    import time
+    ps = [L.make_params(4096, 4096, L.LBM_CIL, seed=l, **KW["cil"]) for l in range(2)]
+    b = L.Batch(ps)
+    for l in range(2):
+        b.buffers[2 * l].fill_(0.1)
+    took = []
+    for _ in range(6):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        b.run(20)
+        took.append(time.perf_counter() - t)
+    assert took[0] <= 20 * min(took[1:]), took
+
+
 def test_refused_forms(L):
     b, _ = _batch(L, 7, "cil", WIDE[:2])
     for form, split in ((RESIDENT, 0), (MULTI, 0), (5, 0), (6, 0), (7, 0), (0, 1), (10, 0), (-1, 0), (3, 2)):
