@@ -198,9 +198,10 @@ def time_single(L, torch, cfgs, steps, warmup, storage=0, lattice=0, whole=False
         for lat in lats:
             lat.step(warmup)
             if whole:
-                # lbm_step replays a graph of 64 steps captured on first use:
-                # capture it (an even count keeps the buffer parity) before timing
-                lat.step(64)
+                # lbm_step captures its graph of 64 steps in the first call of
+                # 512 from a buffer: capture it (an even count keeps the buffer
+                # parity) before timing
+                lat.step(512)
                 continue
             s.synchronize()
             g = torch.cuda.CUDAGraph()

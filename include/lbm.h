@@ -55,9 +55,9 @@
  *  - A population buffer is [9][ny][pitch]; every plane must be below 2^32
  *    bytes (ny * pitch < 2^30 for F32, < 2^31 for the 16-bit storages).
  *  - lbm_add_density adds drho/9 to every population.
- *  - Batched sweeps run D2Q9 with one or two steps per launch, or resident
- *    in LDS up to 3072 sites; the coarse-field calls take D2Q7 only
- *    (LBM_EUNSUPPORTED).
+ *  - Batched sweeps run D2Q9 with one or two steps per launch (batches of up
+ *    to 2^20 sites also several), or resident in LDS up to 3072 sites; the
+ *    coarse-field calls take D2Q7 only (LBM_EUNSUPPORTED).
  *
  * Memory ownership.  The library never allocates or frees device memory.
  * The caller owns every device buffer passed in (population buffers, field
@@ -65,6 +65,9 @@
  * and keeps them alive until the context that uses them is destroyed.  A
  * context owns a host object and the HIP graphs it captures; its device
  * scratch (step clock, reduction partials) lives in the caller's workspace.
+ * The first call of a process that returns observables (lbm_moments with obs,
+ * lbm_sweep_batch with out, lbm_sweep_samples) pins 64 KB of host memory, which
+ * serves every later one, of any thread and device, until the process ends.
  *
  * Errors.  Every entry point returns an int32_t status: LBM_OK (0) or a
  * negative code.  The message of the last error on the calling thread is
@@ -194,12 +197,13 @@ int32_t lbm_create(const lbm_params *p, void *f_a, void *f_b, int64_t pitch, con
  * replay a HIP graph, one per starting buffer, each captured by the first call
  * from that buffer of 512 steps or more (64 or more where a launch takes one
  * step); the remainder, calls of 64 steps or more before that, and every step
- * while the caller is capturing the stream itself, are launched directly.  Every launch reads its step index (the noise counter) from the
- * workspace's step clock, so graphs replay with unchanged arguments.  The
- * state ends in the buffer that n one-step launches, alternating between the
- * two, would leave it in; lbm_current_buffer() tells which.  Where the two
- * buffers together exceed 240 MiB (more than the 256 MB Infinity Cache keeps)
- * the steps' stores are non-temporal; the values are the same either way. */
+ * while the caller is capturing the stream itself, are launched directly.
+ * Every launch reads its step index (the noise counter) from the workspace's
+ * step clock, so graphs replay with unchanged arguments.  The state ends in the
+ * buffer that n one-step launches, alternating between the two, would leave it
+ * in; lbm_current_buffer() tells which.  Where the two buffers together exceed
+ * 240 MiB (more than the 256 MB Infinity Cache keeps) the steps' stores are
+ * non-temporal; the values are the same either way. */
 int32_t lbm_step(lbm_ctx *c, int64_t n);
 
 /* Fields and observables of the stored state.  rho, ux, uy: caller-owned
@@ -254,8 +258,7 @@ const char *lbm_last_error(void);
  * (the paper's repeated runs over a grid of mean density and model constants,
  * appendix "Simulation procedure for results") advanced together: one kernel
  * launch per step (or per two, or for small lattices up to eight) covers every
- * lattice of a lattice group
- * (lbm_sweep_groups), or one launch runs a whole captured chunk of steps with
+ * lattice of a lattice group (lbm_sweep_groups), or one launch runs a whole captured chunk of steps with
  * the lattices resident in LDS; a sample period (its steps and the FP64
  * sampling kernels) is captured in HIP graphs of at most 1024 steps and
  * replayed.
