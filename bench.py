@@ -300,11 +300,11 @@ def copy_probe(torch, copies):
 
 # the sources the batched step kernels are built from (their bodies, the
 # parameters the host prepares for them, and the launch code)
-KERNEL_SOURCES = ("batch.hip", "capi.hip", "device.h", "internal.h")
+KERNEL_SOURCES = ("batch.hip", "step2.h", "capi.hip", "device.h", "internal.h")
 # sources of the square-lattice (D2Q9) step kernels
 Q9_SOURCES = ("q9.hip", "device_q9.h", "device.h", "capi.hip", "internal.h")
 # sources of the batched D2Q9 kernels
-KERNEL_SOURCES_Q9B = ("batch.hip", "device_q9.h", "device.h", "capi.hip", "internal.h")
+KERNEL_SOURCES_Q9B = ("batch.hip", "step2.h", "device_q9.h", "device.h", "capi.hip", "internal.h")
 # sources of the single-lattice D2Q7 step kernels (lbm_step)
 STEP_SOURCES = ("step.hip", "device.h", "capi.hip", "internal.h")
 

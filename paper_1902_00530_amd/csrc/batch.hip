@@ -1040,7 +1040,7 @@ static void graph_cache_put(const GraphKey &k, const GraphPtr &g)
 }
 
 // What this library last wrote into the tables of a workspace (lattice
-// descriptors, moments tiles and the tile list held in each of the two list
+// descriptors, moments tiles and the tile list held in each of the three list
 // regions), per device and workspace address.  A call with keep_tables set
 // takes the record at its word (its caller has not written into the
 // workspace since) and uploads only the tables that differ, so a repeated
@@ -1338,8 +1338,9 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     rec.lat = lat;
     BatchTile *d_tiles1 = d_tiles, *d_tiles2 = d_tiles + Ly.n_tiles1;
     hipError_t up_err = hipSuccess;
-    // the tile list of shape k in its region (one-step shapes in the first,
-    // two-step shapes in the second), uploaded unless the region holds it
+    // the tile list of shape k in its region (one-step shapes in the first, two-step
+    // shapes in the second, the several-steps form in the third), uploaded unless the
+    // region holds it
     auto upload = [&](int k) -> std::pair<BatchTile *, int64_t> {
         const int r = k == kMulti ? 2 : kShapes[k].steps == 1 ? 0 : 1;
         BatchTile *d = r == 0 ? d_tiles1 : r == 1 ? d_tiles2 : (BatchTile *)(w + Ly.tiles3);
