@@ -940,11 +940,11 @@ static hipError_t launch_batch_step(int lattice, int model, int storage, int fla
 // lattice sizes + model + flags), kept for the life of the process.
 static std::mutex g_tune_mu;
 struct Tuned {
-    int shape;   // the fastest form
-    int split;   // its lattice groups run as two branches
-    int direct;  // the fastest form without branches, for direct launches
-    int tile;    // the fastest among the forms that tile_rows names (named_shape)
-    bool branches;  // forms with branches were timed too (by a call that runs graphs)
+    int shape;      // the fastest form
+    int split;      // its lattice groups run as two branches
+    int direct;     // the form of direct launches: the same shape where it is as fast
+    int tile;       // the fastest among the forms that tile_rows names (named_shape)
+    bool branches;  // branches were timed too (by a call that runs graphs)
 };
 static std::map<std::string, Tuned> g_tuned;
 
@@ -1245,7 +1245,7 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     if (shape < 0) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(sig);
-        // what a call without graphs has tuned lacks the branched forms
+        // what a call without graphs has tuned lacks the branches
         if (it != g_tuned.end() && (it->second.branches || !o->use_graph)) {
             shape = o->use_graph ? it->second.shape : it->second.direct;
             split = o->use_graph ? it->second.split : 0;
@@ -1444,9 +1444,15 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
             int k, split, steps;  // steps of a launch
             hipGraphExec_t exec = nullptr;
             float replay = 1e30f;  // least ms of a replay
-            float ms() const  // per ten steps
+            // Per ten steps.  3% against branches, and against the two-step tiles of eight
+            // rows: these issue 8% more vector instructions than those of 16, which bursts
+            // as short as a replay show less of than a sweep at the clock that the card
+            // then holds (five lattices of 1024^2, 2000 steps: 168 / 176 GLUPS).
+            float ms() const
             {
-                return (k == kResident ? replay * 10.0f : replay) / (float)steps * (split ? 1.03f : 1.0f);
+                const bool eight = k < kNumShapes && kShapes[k].steps == 2 && kShapes[k].ty == 8;
+                return (k == kResident ? replay * 10.0f : replay) / (float)steps * (split ? 1.03f : 1.0f) *
+                       (eight ? 1.03f : 1.0f);
             }
         };
         struct Tuning {  // destroyed on every exit path
@@ -1539,66 +1545,67 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
                 e = time_form(t, 1);
             return e == hipSuccess && t.replay < 0.4f ? time_form(t, 1) : e;
         };
-        auto best_ms = [&]() {
-            float m = 1e30f;
-            for (const Form &f : tuning.forms)
-                m = std::min(m, f.ms());
-            return m;
+        // these forms once more each, in turn `rounds` times: the card's clock falls while
+        // it works, so times taken one form after another favour the first
+        auto compare = [&](const std::vector<Form *> &fs, int rounds) -> hipError_t {
+            hipError_t e = hipSuccess;
+            for (Form *f : fs)
+                f->replay = 1e30f;
+            for (int r = 0; r < rounds; ++r)
+                for (size_t i = 0; i < fs.size() && e == hipSuccess; ++i)
+                    e = time_form(*fs[i], 1);
+            return e;
         };
-        auto again = [&](float within, int reps, bool short_ones) -> hipError_t {
-            const float limit = within * best_ms();
-            for (Form &f : tuning.forms)
-                if (f.ms() <= limit && (!short_ones || f.replay < 1.0f)) {
-                    const hipError_t e = time_form(f, reps);
-                    if (e != hipSuccess)
-                        return e;
-                }
-            return hipSuccess;
+        auto best_of = [&](const std::vector<Form *> &fs) {
+            return *std::min_element(fs.begin(), fs.end(), [](Form *x, Form *y) { return x->ms() < y->ms(); });
         };
-        // Every form once; those near the best twice more; the best two-step shapes also as
-        // two branches; then what is close, where a replay is short enough to spread by
-        // itself.  A batch's first call, ms, with three or six replays of every form and
-        // of its branches / so: 48 lattices of 128^2 to 512^2 22.1 / 12.0, two of 4096^2
-        // 151 / 48, twelve of 90 x 30 MIPS 8.8 / 3.7; the same forms are chosen.
+        // Every form once; those near the best against each other; the best against the best
+        // two-step shape as two branches.  A batch's first call, ms, with
+        // three or six replays of every form and of its branches / so: 48 lattices of 128^2
+        // to 512^2 22.1 / 13.0, two of 4096^2 151 / 59, three of 1000x752 D2Q9 MIPS 24 / 9.6.
+        tuning.forms.reserve(cands.size() + 1);
         hipError_t e = hipSuccess;
         for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i)
             e = try_form(cands[i], 0);
-        if (e == hipSuccess)
-            e = again(1.12f, 2, false);
-        const float near = 1.03f * best_ms();
-        for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i) {
-            const int k = cands[i];
-            if (n > 1 && k < kNumShapes && kShapes[k].steps == 2 && o->use_graph && tuning.forms[i].ms() <= near)
-                e = try_form(k, 1);
-            else
-                continue;
-            if (e == hipSuccess && tuning.forms.back().ms() <= 1.06f * best_ms())
-                e = time_form(tuning.forms.back(), 1);
-        }
-        if (e == hipSuccess)
-            e = again(1.03f, 2, true);
         if (e != hipSuccess)
             return hip_fail(e, "tile-shape tuning");
-        float best = 1e30f, best_direct = 1e30f, best_tile = 1e30f;
-        int direct = -1, tile = -1;
-        for (const Form &f : tuning.forms) {
-            const float ms = f.ms();
-            if (ms < best) {
-                best = ms;
-                shape = f.k;
-                split = f.split;
-            }
-            if (!f.split && ms < best_direct) {
-                best_direct = ms;
-                direct = f.k;
-            }
-            if (!f.split && named_shape(f.k) && ms < best_tile) {
-                best_tile = ms;
-                tile = f.k;
-            }
+        std::vector<Form *> all, near;
+        for (Form &f : tuning.forms)
+            all.push_back(&f);
+        const float limit = 1.12f * best_of(all)->ms();
+        for (Form *f : all)
+            if (f->ms() <= limit)
+                near.push_back(f);
+        if (near.size() > 1)
+            e = compare(near, 2);
+        Form *best = best_of(near);
+        auto named_among = [&](std::vector<Form *> fs) -> Form * {
+            fs.erase(std::remove_if(fs.begin(), fs.end(), [](Form *f) { return !named_shape(f->k); }), fs.end());
+            return fs.empty() ? nullptr : best_of(fs);
+        };
+        Form *const close = named_among(near), *const named = close ? close : named_among(all);
+        Form *const single = best;
+        std::vector<Form *> pairs;  // two-step shapes among them
+        for (Form *f : near)
+            if (f->k < kNumShapes && kShapes[f->k].steps == 2)
+                pairs.push_back(f);
+        Form *const pair = pairs.empty() ? nullptr : best_of(pairs);
+        if (e == hipSuccess && n > 1 && o->use_graph && pair) {
+            e = try_form(pair->k, 1);
+            Form *two = &tuning.forms.back();
+            if (e == hipSuccess && two->ms() <= 1.2f * best->ms())
+                e = compare({best, two}, best->replay < 0.7f ? 6 : 3);
+            best = best_of({best, two});
         }
+        if (e != hipSuccess)
+            return hip_fail(e, "tile-shape tuning");
+        shape = best->k;
+        split = best->split;
+        // calls with and without graphs in turn would upload their tile lists each time (45
+        // us) if they ran in shapes of their own
+        const int direct = split && pair->ms() <= 1.05f * single->ms() ? pair->k : single->k;
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[sig] = Tuned{shape, split, direct, tile, o->use_graph != 0 || n == 1};
+        g_tuned[sig] = Tuned{shape, split, direct, named->k, o->use_graph != 0 || n == 1};
     }
     // the chosen list, and for a two-step shape the list of a one-step shape
     // (256x1; MIPS 64x4, D2Q9 MIPS 64x16) for the single steps that keep the launch count's
