@@ -39,16 +39,16 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # per lane.  valu_per_site_update() reads the current figure from the counter
 # summary in profiles/; this is the last measured value, used when that
 # summary was taken on other kernel sources.
-VALU_PER_SITE_UPDATE = 185
+VALU_PER_SITE_UPDATE = 177
 # the same for the square lattice (D2Q9): the one-step batch kernel with one
 # site per lane (256 x 1 tiles), CIL, FP32, tau 1, noise on
-Q9_VALU_PER_SITE_UPDATE = 223
+Q9_VALU_PER_SITE_UPDATE = 219
 # MIPS, two steps per launch on 64 x 16 tiles (4096^2, FP32, tau 2, noise
 # on): every VALU instruction of the launch (both rings included) per
 # site-update of the tile
-MIPS2_VALU_PER_SITE_UPDATE = 267
+MIPS2_VALU_PER_SITE_UPDATE = 257
 # the same on the square lattice (D2Q9)
-MIPS2_Q9_VALU_PER_SITE_UPDATE = 308
+MIPS2_Q9_VALU_PER_SITE_UPDATE = 292
 
 
 def parse():
