@@ -42,7 +42,7 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 VALU_PER_SITE_UPDATE = 177
 # the same for the square lattice (D2Q9): the one-step batch kernel with one
 # site per lane (256 x 1 tiles), CIL, FP32, tau 1, noise on
-Q9_VALU_PER_SITE_UPDATE = 219
+Q9_VALU_PER_SITE_UPDATE = 223
 # MIPS, two steps per launch on 64 x 16 tiles (4096^2, FP32, tau 2, noise
 # on): every VALU instruction of the launch (both rings included) per
 # site-update of the tile
