@@ -1368,9 +1368,9 @@ int32_t lbm_sweep_batch(const lbm_params *ps, int32_t n, const lbm_sweep_opts *o
     // Two branches of a captured graph: a lattice group's launches are cut into
     // two halves of its lattices, which need not wait for each other, so one
     // half's launches fill the CUs that the other's last blocks and its next
-    // launch's first loads leave idle (launches of about 50 us, three to five
-    // rounds of blocks, issue vector instructions in 70 to 83% of the cycles where
-    // a 4096^2 lattice's reach 99%).  Taken where the tuning finds it 3% faster:
+    // launch's first loads leave idle (whole launches of 35 to 47 us, two to five
+    // rounds of blocks, issue vector instructions in 68 to 72% of the cycles, a
+    // 4096^2 lattice's in 81%).  Taken where the tuning finds it 3% faster:
     // 48 lattices of 128^2 to 512^2 2.54 -> 2.29 ms per 100 steps, the 50 steps
     // of 64 lattices of 256^2 in a surrogate's judge 1.36 -> 1.18 ms, 20 steps of
     // five lattices of 1024^2 713 -> 697 us; three or four branches are slower.
